@@ -160,7 +160,7 @@ int mg_segment_ids(const mg_graph *g, uint32_t *out);
  * tensor), so that the library holds no device allocation of its own:
  * mg_device_bytes gives the size of one buffer that holds every array the GPU
  * path reads (the DAG's (a, b, w) triples in node order and in step order, the
- * rank table, a per-node bound on its mixture's sources, the node-ID maps of
+ * records of the nodes of rank 1 and 2 by their sources, the rank table, a per-node bound on its mixture's sources, the node-ID maps of
  * every level x fastest and y fastest, and 16-bit copies of level 0 when the
  * sources fit); mg_bind_device fills `d_buf` (device memory on `device`, at
  * least that many bytes, 256-byte aligned) with them, enqueued on `stream`,
@@ -274,15 +274,16 @@ int mg_naive_boxes(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float *d_ou
 
 /* Host-side check of the query kernels' load addresses (no GPU needed): for
  * boxes (host uint32 [n][6]) on a volume of nx x ny x nz voxels, replays every
- * load the batched query kernels issue (all `unroll` loads of every block, 4, 8
- * or 16), with the kernels' own slab builder and tile-walk helpers. flags: bit
+ * load the batched query kernels issue (every lane of every tile), with the
+ * kernels' own slab builder and tile-walk helpers; `unroll` (4, 8 or 16) is the
+ * naive scan's loads per block. flags: bit
  * 0 = level 0 from the 16-bit copy, bit 1 = also the naive scan's loads, bit 2
  * = slabs with rows of at least run_min cubes summed from row runs (every level
  * and orientation the run builder accepts), bits 8..31 = run_min (0: the
  * default of mg_launch_cfg.run_min_row). Checks that each load lies inside its
  * slab and inside the map buffer, that each consumed load reads exactly the
  * element of a footprint cube (or voxel) of the box, for run slabs that each
- * row segment lies in the box on its row and indexes its row and skip entry in
+ * row segment lies in the box on its row and indexes its row and skip entries in
  * range (run loads are clamped to the run array by the kernel), and that every
  * cube of the footprint is read once. counts host uint64 [4]: boxes, slabs,
  * lane loads (run segments for run slabs), cubes. MG_ELIMIT with the first
@@ -390,7 +391,7 @@ typedef struct {
                                built with defer = 1). Same colours either way                  */
     uint32_t run_min_row;   /* footprint slabs whose rows are at least this many cubes long are
                                summed from the rows' runs of equal node IDs where the graph
-                               has them; shorter rows stream cube by cube. 0: default (128);
+                               has them; shorter rows stream cube by cube. 0: default (16);
                                0xFFFFFFFF: never (every slab streams)                          */
 } mg_launch_cfg;
 

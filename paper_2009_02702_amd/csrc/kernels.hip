@@ -52,8 +52,7 @@ constexpr uint32_t kHashGlobal = 1u << 16;    // fewest per-worker hash slots in
 constexpr uint32_t kSegLdsMax = 2048;         // sources kept in LDS
 constexpr uint32_t kFallbackWorkers = 128;    // workers of the final global-table launch (budget)
 constexpr uint32_t kRunSeg = 256;             // cells of a row one thread sums from the runs
-constexpr int kRunBatch = 4;                   // runs a thread loads at once per segment
-constexpr uint32_t kRunMinRow = 128;           // rows shorter than this stream cube by cube (default)
+constexpr uint32_t kRunMinRow = 16;           // rows shorter than this stream cube by cube (default)
 constexpr uint32_t kTfPlanes = 4;             // transfer functions per thread of a propagation step
 constexpr uint32_t kTfTailPairs = 4096;        // steps of at most this many node x TF pairs may share a launch
 constexpr uint32_t kTfTailSteps = 16;          // at most this many of them
@@ -61,7 +60,7 @@ constexpr uint32_t kTfTailBlock = 1024;        // threads of that launch (one wo
 constexpr uint32_t kMidWorkers = 256;         // workers of the mid-size global-table launch
 constexpr uint32_t kQueues = 8;                // work queues per tier
 constexpr uint32_t kQueueStride = 64;          // u32 between queue counters (256 bytes)
-constexpr int kUnroll = 4;                     // node-ID loads in flight per lane (plain, fallback)
+constexpr int kGroup = 4;                      // tiles per load group (plain, fallback)
 constexpr uint32_t kMaxSteps = 64;              // graph depth the step table holds
 constexpr uint32_t kDeferSlots = 128;           // per-wave ring of deferred internal-node runs (dense state)
 
@@ -97,11 +96,12 @@ struct LevelTable {
 
 // Row runs of one level and orientation as the kernels read them (the device copy
 // of the host's LevelRuns): runs[j] = exclusive end << 32 | node; skip[r][c] =
-// index of the run holding cell 64 c of row r.
+// index of the run holding cell kRunSkipCells c of row r.
 struct RunLevel {
     const uint32_t *skip;      // [rows][chunks]
     const uint64_t *runs;      // [n_runs]
     uint32_t rows, chunks, n_runs;
+    uint32_t first;            // index of runs[0] from the graph's first run (GraphView::runs)
 };
 
 // A slab of cubes at one level, as the query kernels read it: e2 slices (slow
@@ -151,19 +151,25 @@ __host__ __device__ inline bool clip_box(const uint32_t *b, const LevelTable &lt
     return ok;
 }
 
-// The slab of level `lev` covering cells [x0, x1) x [y0, y1) x [z0, z1): the
+// One level's extents and its first element in maps: what the slab builder reads of the
+// level table (a copy in LDS for the kernels, whose lanes each work on another level).
+struct LevelRow {
+    uint32_t X, Y, Z, pad;
+    uint64_t off;
+};
+
+__host__ __device__ inline LevelRow level_row(const LevelTable &lt, uint32_t lev)
+{
+    return LevelRow{lt.dims[lev][0], lt.dims[lev][1], lt.dims[lev][2], 0u, lt.off[lev]};
+}
+
+// The slab of level `lev` covering cells [x0, x1) x [y0, y1) x [z0, z1) (not empty): the
 // fast axis is x (rows from maps) unless the block is thinner in x than in y
 // (rows along y from maps_t); of the other two, the thinner is the slow axis.
 // Level 0 uses the 16-bit copy when lt.use16.
-template <bool WRITE>
-__host__ __device__ inline void put_slab(Slab *out, int *n, const LevelTable &lt, uint32_t lev, uint32_t x0,
-                                         uint32_t x1, uint32_t y0, uint32_t y1, uint32_t z0, uint32_t z1)
+__host__ __device__ inline Slab make_slab(const LevelTable &lt, const LevelRow &lr, uint32_t lev, uint32_t x0,
+                                          uint32_t x1, uint32_t y0, uint32_t y1, uint32_t z0, uint32_t z1)
 {
-    if (x1 <= x0 || y1 <= y0 || z1 <= z0) return;
-    if (!WRITE) {
-        ++*n;
-        return;
-    }
     const uint32_t ex = x1 - x0, ey = y1 - y0, ez = z1 - z0;
     Slab s;
     s.level = uint8_t(lev);
@@ -184,11 +190,10 @@ __host__ __device__ inline void put_slab(Slab *out, int *n, const LevelTable &lt
     if (ef >= lt.run_min && ((lt.runs_mask >> (2 * lev + f)) & 1u) &&
         uint64_t(em) * ew * ((ef + kRunSeg - 1) / kRunSeg) < (1ull << 30)) {
         s.kind = 2, s.odd = 0, s.base = 0, s.s1b = s.s2b = 0, s.units = ef;
-        out[(*n)++] = s;
-        return;
+        return s;
     }
     // element strides of the mid and slow axes in the chosen copy, and the first element
-    const uint32_t X = lt.dims[lev][0], Y = lt.dims[lev][1], Z = lt.dims[lev][2];
+    const uint32_t X = lr.X, Y = lr.Y, Z = lr.Z;
     const bool pairs = lev == 0 && lt.use16;
     const uint32_t px = pairs ? lt.pitch_x : X, py = pairs ? lt.pitch_y : Y;
     s.kind = pairs ? 1 : 0;
@@ -196,11 +201,11 @@ __host__ __device__ inline void put_slab(Slab *out, int *n, const LevelTable &lt
     if (f) {  // y fastest: element y + py (z + Z x)
         const uint64_t sz = py, sx = uint64_t(py) * Z;
         sm = m == 2 ? sz : sx, sw = m == 2 ? sx : sz;
-        first = (pairs ? lt.total16 : lt.total + lt.off[lev]) + y0 + uint64_t(py) * (z0 + uint64_t(Z) * x0);
+        first = (pairs ? lt.total16 : lt.total + lr.off) + y0 + uint64_t(py) * (z0 + uint64_t(Z) * x0);
     } else {  // x fastest: element x + px (y + Y z)
         const uint64_t sy = px, sz = uint64_t(px) * Y;
         sm = m == 1 ? sy : sz, sw = m == 1 ? sz : sy;
-        first = (pairs ? 0 : lt.off[lev]) + x0 + uint64_t(px) * (y0 + uint64_t(Y) * z0);
+        first = (pairs ? 0 : lr.off) + x0 + uint64_t(px) * (y0 + uint64_t(Y) * z0);
     }
     const uint32_t odd = pairs ? ((f == 1 ? y0 : x0) & 1u) : 0u;
     const uint32_t esz = pairs ? 2u : 4u;
@@ -209,14 +214,14 @@ __host__ __device__ inline void put_slab(Slab *out, int *n, const LevelTable &lt
     s.s1b = em > 1 ? uint32_t(esz * sm) : 0u;  // < 2^32 whenever the extent is above 1
     s.s2b = ew > 1 ? uint32_t(esz * sw) : 0u;
     s.units = pairs ? (ef + odd + 1) >> 1 : ef;
-    out[(*n)++] = s;
+    return s;
 }
 
-// Slabs of level `lev` of the box's footprint (at most 6), written to out[0..]
-// when WRITE. Returns their count.
-template <bool WRITE>
-__host__ __device__ inline int level_slabs(const LevelTable &lt, const uint32_t lo[3], const uint32_t hi[3],
-                                           uint32_t lev, Slab *out)
+// Slab `face` (0 .. 5) of level `lev` of the box's footprint, if it holds any cube: the faces
+// of the hollow shell (x low, x high, y low, y high, z low, z high, each cut short by the ones
+// before it), or the whole block as face 0 where no coarser cube lies inside the box.
+__host__ __device__ inline bool face_slab(const LevelTable &lt, const LevelRow &lr, const uint32_t lo[3],
+                                          const uint32_t hi[3], uint32_t lev, uint32_t face, Slab *out)
 {
     uint32_t a[3], b[3], ia[3], ib[3];
     bool outer = true, inner = true;
@@ -231,38 +236,91 @@ __host__ __device__ inline int level_slabs(const LevelTable &lt, const uint32_t 
         ia[d] = 2 * pa;
         ib[d] = 2 * pb;
     }
-    int n = 0;
-    if (!outer) return 0;
-    if (!inner) {
-        put_slab<WRITE>(out, &n, lt, lev, a[0], b[0], a[1], b[1], a[2], b[2]);
-        return n;
+    if (!outer || (!inner && face > 0)) return false;
+    uint32_t x0 = a[0], x1 = b[0], y0 = a[1], y1 = b[1], z0 = a[2], z1 = b[2];
+    if (inner) {
+        if (face == 0) x1 = ia[0];
+        if (face == 1) x0 = ib[0];
+        if (face >= 2) x0 = ia[0], x1 = ib[0];
+        if (face == 2) y1 = ia[1];
+        if (face == 3) y0 = ib[1];
+        if (face >= 4) y0 = ia[1], y1 = ib[1];
+        if (face == 4) z1 = ia[2];
+        if (face == 5) z0 = ib[2];
     }
-    put_slab<WRITE>(out, &n, lt, lev, a[0], ia[0], a[1], b[1], a[2], b[2]);       // x low face
-    put_slab<WRITE>(out, &n, lt, lev, ib[0], b[0], a[1], b[1], a[2], b[2]);       // x high face
-    put_slab<WRITE>(out, &n, lt, lev, ia[0], ib[0], a[1], ia[1], a[2], b[2]);     // y low face
-    put_slab<WRITE>(out, &n, lt, lev, ia[0], ib[0], ib[1], b[1], a[2], b[2]);     // y high face
-    put_slab<WRITE>(out, &n, lt, lev, ia[0], ib[0], ia[1], ib[1], a[2], ia[2]);   // z low face
-    put_slab<WRITE>(out, &n, lt, lev, ia[0], ib[0], ia[1], ib[1], ib[2], b[2]);   // z high face
-    return n;
+    if (x1 <= x0 || y1 <= y0 || z1 <= z0) return false;
+    *out = make_slab(lt, lr, lev, x0, x1, y0, y1, z0, z1);
+    return true;
 }
 
-// Wave 0 fills the slab table of one box in LDS; returns via LDS the slab
-// count. Lane l handles level l. Must be called by all threads of the block
-// (contains no barrier itself).
-__device__ inline void build_slabs(const LevelTable &lt, const uint32_t lo[3], const uint32_t hi[3], Slab *slabs,
-                                   int *n_slabs)
+// Tiles of a streamed slab (kind 0 or 1). A tile is what a wave loads at once, one 4-byte
+// unit per lane: 2^ltx units of 2^(6 - ltx) rows, lane (lx, ly) = (lane mod 2^ltx,
+// lane / 2^ltx). ltx is the smallest power of two that holds a row, at most 64 units; rows
+// at least 2^24 bytes apart take one row per tile, so that a lane's byte offset is a 24-bit
+// product below 2^32.
+__host__ __device__ inline uint32_t tile_ltx(const Slab &sl)
 {
-    const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 64) {
-        const int k = lane < int(lt.n_levels) ? level_slabs<false>(lt, lo, hi, uint32_t(lane), nullptr) : 0;
-        // exclusive prefix over lanes of k
-        int incl = k;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += v;
+    uint32_t ltx = 0;
+    while (ltx < 6 && (1u << ltx) < sl.units) ++ltx;
+    return sl.s1b >= (1u << 24) ? 6u : ltx;
+}
+
+__host__ __device__ inline uint32_t slab_tiles(const Slab &sl)
+{
+    if (sl.kind == 2) return 0;
+    const uint32_t ltx = tile_ltx(sl), ty = 64u >> ltx;
+    return ((sl.units + (1u << ltx) - 1) >> ltx) * ((sl.e1 + ty - 1) / ty) * sl.e2;
+}
+
+// Segments per row of a kind-2 slab, as log2 of the power of two >= ceil(e0 / kRunSeg).
+__host__ __device__ inline uint32_t run_lseg(uint32_t e0)
+{
+    uint32_t lseg = 0;
+    while ((kRunSeg << lseg) < e0) ++lseg;
+    return lseg;
+}
+
+// (row, segment) items of a slab summed from row runs.
+__host__ __device__ inline uint32_t slab_items(const Slab &sl)
+{
+    return sl.kind == 2 ? (sl.e1 * sl.e2) << run_lseg(sl.e0) : 0u;
+}
+
+// Wave 0 fills the slab table of one box in LDS, lane (level, face) one slab (two rounds
+// where there are more than 64 such pairs), with the prefix sums of the slabs' tiles and run
+// items (tile0 / item0, entry *n_slabs the totals; null: not wanted). `rows` holds the levels'
+// extents in LDS. All threads may call; contains no barrier.
+__device__ inline void build_slabs(const LevelTable &lt, const LevelRow *rows, const uint32_t lo[3],
+                                   const uint32_t hi[3], Slab *slabs, int *n_slabs, uint32_t *tile0,
+                                   uint32_t *item0)
+{
+    if (threadIdx.x >= 64) return;
+    const uint32_t lane = threadIdx.x;
+    uint32_t n = 0, tiles = 0, items = 0;
+    for (uint32_t r = 0; r < 6 * lt.n_levels; r += 64) {
+        const uint32_t id = r + lane, lev = (id * 43) >> 8;  // id / 6 (exact below 128)
+        Slab sl;
+        const bool have = lev < lt.n_levels && face_slab(lt, rows[lev], lo, hi, lev, id - 6 * lev, &sl);
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(have);
+        const uint32_t at = n + __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u));
+        uint32_t t = have ? slab_tiles(sl) : 0u, k = have ? slab_items(sl) : 0u;
+        const uint32_t t1 = t, k1 = k;
+        for (int off = 1; off < 64; off <<= 1) {  // inclusive sums over the lanes
+            const uint32_t vt = uint32_t(__shfl_up(int(t), off, 64)), vk = uint32_t(__shfl_up(int(k), off, 64));
+            if (lane >= uint32_t(off)) t += vt, k += vk;
         }
-        if (k) level_slabs<true>(lt, lo, hi, uint32_t(lane), slabs + (incl - k));
-        if (lane == 63) *n_slabs = incl;
+        if (have) {
+            slabs[at] = sl;
+            if (tile0) tile0[at] = tiles + t - t1, item0[at] = items + k - k1;
+        }
+        n += uint32_t(__builtin_popcountll(mask));
+        tiles += uint32_t(__builtin_amdgcn_readlane(int(t), 63));
+        items += uint32_t(__builtin_amdgcn_readlane(int(k), 63));
+    }
+    if (lane == 0) {
+        *n_slabs = int(n);
+        if (tile0) tile0[n] = tiles, item0[n] = items;
     }
 }
 
@@ -289,11 +347,26 @@ struct QueryState {
     uint32_t *seg_cnt;  // [S] exact integer counts (dense mode)
     float *seg_hi, *seg_lo;  // [S] pushed mass and its compensation (dense mode)
     Slab *slabs;        // [6 * levels] the box's slabs (LDS)
+    uint32_t *tile0, *item0;  // [6 * levels + 1] tiles and run items before each slab (LDS)
     float *seg_var;     // [S] accumulated variance per source (uncertainty queries), or null
 };
 
+// A node of rank 1 or 2 by its sources: (1 - w) of it goes to the a side, w to the b side;
+// the a side is (1 - wa) s[0] + wa s[1], the b side (1 - wb) s[2] + wb s[3]. A side that is a
+// source itself has weight 0 (and names it twice); every other weight is above 0. One 32-byte
+// record instead of the node's triple and then its predecessors': a node met on a cube costs one
+// load latency and one cache line, where rank 2 took two in a row and three lines.
+struct Leaf {
+    uint32_t s[4];
+    float w, wa, wb;
+    uint32_t pad;
+};
+static_assert(sizeof(Leaf) == 32, "Leaf must stay 32 bytes");
+
 struct GraphView {
     const NodeTriple *__restrict__ nodes;
+    const Leaf *__restrict__ leaf;   // [node - nseg] for the nodes of rank 1 and 2
+    const uint64_t *__restrict__ runs;   // the graph's first run: RunLevel::first counts from here
     uint32_t nseg;     // sources are IDs [0, nseg)
     uint32_t r1_end;   // rank-1 nodes are IDs [nseg, r1_end)
     uint32_t r2_end;   // rank-2 nodes are IDs [r1_end, r2_end)
@@ -385,34 +458,30 @@ __device__ inline void add_source_mass(const QueryState &st, uint32_t s, float h
     }
 }
 
-// Mass (h, l) on a rank-1 node with predecessors (a, b), both sources.
+// Mass (h, l) on one side of a node of rank 1 or 2.
 template <bool SPARSE>
-__device__ inline void push_pair(const QueryState &st, const NodeTriple &t, float h, float l)
+__device__ inline void push_side(const QueryState &st, uint32_t s0, uint32_t s1, float w, float h, float l)
 {
+    if (w == 0.0f) {
+        add_source_mass<SPARSE>(st, s0, h, l);
+        return;
+    }
     float ah, al, bh, bl;
-    scale_pair(1.0f - t.w, h, l, &ah, &al);
-    scale_pair(t.w, h, l, &bh, &bl);
-    add_source_mass<SPARSE>(st, t.a, ah, al);
-    add_source_mass<SPARSE>(st, t.b, bh, bl);
+    scale_pair(1.0f - w, h, l, &ah, &al);
+    scale_pair(w, h, l, &bh, &bl);
+    add_source_mass<SPARSE>(st, s0, ah, al);
+    add_source_mass<SPARSE>(st, s1, bh, bl);
 }
 
-// Mass (h, l) on a rank-2 node: each predecessor is a source or a rank-1 node,
-// so it is pushed to the sources at once (at most two hops), without a table entry.
+// Mass (h, l) on a node of rank 1 or 2, straight to its sources.
 template <bool SPARSE>
-__device__ inline void push_rank2(const QueryState &st, const GraphView &gv, const NodeTriple &t, float h, float l)
+__device__ inline void push_leaf(const QueryState &st, const Leaf &t, float h, float l)
 {
     float ah, al, bh, bl;
     scale_pair(1.0f - t.w, h, l, &ah, &al);
     scale_pair(t.w, h, l, &bh, &bl);
-    // both predecessors' triples in flight before the first addition
-    const bool na = t.a >= gv.nseg, nb = t.b >= gv.nseg;
-    NodeTriple ta = {0u, 0u, 0.0f}, tb = {0u, 0u, 0.0f};
-    if (na) ta = gv.nodes[t.a];
-    if (nb) tb = gv.nodes[t.b];
-    if (na) push_pair<SPARSE>(st, ta, ah, al);
-    else add_source_mass<SPARSE>(st, t.a, ah, al);
-    if (nb) push_pair<SPARSE>(st, tb, bh, bl);
-    else add_source_mass<SPARSE>(st, t.b, bh, bl);
+    push_side<SPARSE>(st, t.s[0], t.s[1], t.wa, ah, al);
+    push_side<SPARSE>(st, t.s[2], t.s[3], t.wb, bh, bl);
 }
 
 // Mass pushed into `node` during the reverse push. Nodes of rank <= 2 go straight
@@ -422,10 +491,8 @@ __device__ inline void route_mass(const QueryState &st, const GraphView &gv, uin
 {
     if (node < gv.nseg) {
         add_source_mass<SPARSE>(st, node, h, l);
-    } else if (node < gv.r1_end) {
-        push_pair<SPARSE>(st, gv.nodes[node], h, l);
     } else if (node < gv.r2_end) {
-        push_rank2<SPARSE>(st, gv, gv.nodes[node], h, l);
+        push_leaf<SPARSE>(st, gv.leaf[node - gv.nseg], h, l);
     } else {
         const uint32_t slot = table_slot(st, node);
         if (slot != kEmpty) add_mass_at(&st.hi[slot], &st.lo[slot], h, l);
@@ -441,10 +508,8 @@ __device__ inline void scatter_count(const QueryState &st, const GraphView &gv, 
         return;
     }
     const float h = float(c & 0xFFFFFF00u), l = float(c & 0xFFu);  // both exact in fp32
-    if (node < gv.r1_end) {
-        push_pair<SPARSE>(st, gv.nodes[node], h, l);
-    } else if (node < gv.r2_end) {
-        push_rank2<SPARSE>(st, gv, gv.nodes[node], h, l);
+    if (node < gv.r2_end) {
+        push_leaf<SPARSE>(st, gv.leaf[node - gv.nseg], h, l);
     } else {
         const uint32_t slot = table_slot(st, node);
         if (slot != kEmpty) add_mass_at(&st.hi[slot], &st.lo[slot], h, l);
@@ -489,9 +554,9 @@ __device__ inline bool run_head(uint32_t v, uint64_t above, uint32_t *len)
 
 __device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// ---------------------------------------------------------------- tiled slab walk
+// ---------------------------------------------------------------- tiled slab walk (naive scan)
 //
-// A slab is read as e2 slices of e1 rows of `units` 4-byte units (32-bit node
+// The naive scan's box is read as e2 slices of e1 rows of `units` 4-byte units (32-bit node
 // IDs, or aligned pairs of 16-bit level-0 IDs). A wave covers a tile of 2^ltx
 // units x 2^(6 - ltx) rows (lane (lx, ly) = (lane mod 2^ltx, lane / 2^ltx)),
 // and a block is UNROLL tiles stacked along the rows, so a lane's UNROLL loads
@@ -502,7 +567,7 @@ __device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstla
 // (the wave-uniform bound n_u) and load from the last tile that starts inside
 // it; lanes outside the slab read their tile's first unit (inside the slab) and
 // see kEmpty, so every load stays inside the slab. The same helpers give the
-// addresses to the kernels and to the host-side replay (mg_check_load_addresses).
+// addresses to the kernel and to the host-side replay (mg_check_load_addresses).
 
 struct TileWalk {
     uint32_t units, e1, e2;   // units per row, rows per slice, slices
@@ -658,7 +723,7 @@ __device__ inline bool stream_slab(const char *__restrict__ p, const TileWalk &t
 }
 
 // Streams a slab of the 16-bit level-0 copy, two elements per unit; `use(lo, hi)`
-// gets kEmpty for elements outside the slab (e0 elements per row, the row's first
+// gets 0xFFFF (no source: there are fewer than 65,535) for elements outside the slab (e0 elements per row, the row's first
 // unit one element early when `odd`). Three blocks in flight (level 0 is most of
 // the cubes, and its 32-bit words leave registers to spare): a block past the
 // wave's last one is replaced by the block before it (valid addresses, never consumed).
@@ -713,7 +778,7 @@ __device__ inline void stream_pairs(const char *__restrict__ p, const TileWalk &
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
             if (uint32_t(u) < n_u)
-                use(uint32_t(u) < n_lo ? (v[u] & 0xFFFFu) : kEmpty, uint32_t(u) < n_hi ? (v[u] >> 16) : kEmpty);
+                use(uint32_t(u) < n_lo ? (v[u] & 0xFFFFu) : 0xFFFFu, uint32_t(u) < n_hi ? (v[u] >> 16) : 0xFFFFu);
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) v[u] = w[u], w[u] = x[u];
         n_u = w_n_u, n_lo = w_n_lo, n_hi = w_n_hi;
@@ -724,7 +789,8 @@ __device__ inline void stream_pairs(const char *__restrict__ p, const TileWalk &
 
 // Counts a wave's 128 level-0 elements (lane l holds elements 2l and 2l+1) into
 // integer per-source counters: a run of equal sources over elements a..b adds
-// -a at its start element and b+1 at its end element (uint32 wrap-around).
+// -a at its start element and b+1 at its end element (uint32 wrap-around); 0xFFFF marks
+// an element outside.
 __device__ inline void count_pairs(uint32_t *cnt, uint32_t lo, uint32_t hi, uint32_t lane)
 {
     const uint32_t prev_hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(hi), 0x138, 0xF, 0xF, true));
@@ -732,21 +798,11 @@ __device__ inline void count_pairs(uint32_t *cnt, uint32_t lo, uint32_t hi, uint
     const bool s_lo = lo != prev_hi || lane == 0;   // element 2l starts a run
     const bool e_lo = lo != hi;                     // element 2l ends one, 2l+1 starts one
     const bool e_hi = hi != next_lo || lane == 63;  // element 2l+1 ends one
-    if (lo != kEmpty && (s_lo || e_lo)) atomicAdd(&cnt[lo], (s_lo ? 0u - 2 * lane : 0u) + (e_lo ? 2 * lane + 1 : 0u));
-    if (hi != kEmpty && (e_lo || e_hi))
+    if (lo != 0xFFFFu && (s_lo || e_lo)) atomicAdd(&cnt[lo], (s_lo ? 0u - 2 * lane : 0u) + (e_lo ? 2 * lane + 1 : 0u));
+    if (hi != 0xFFFFu && (e_lo || e_hi))
         atomicAdd(&cnt[hi], (e_lo ? 0u - (2 * lane + 1) : 0u) + (e_hi ? 2 * lane + 2 : 0u));
 }
 
-// Kind-2 slab: every row segment is summed from its row's runs. The block's
-// threads take (row, segment) items, a segment being at most kRunSeg cells of
-// one row, one at a time: the skip entry of its 64-cell chunk gives the
-// run holding the chunk's first cell (runs before the segment end at or before
-// its first cell and add nothing); runs are loaded kRunBatch at a time, and
-// each adds (cells of it inside the segment) x 8^level to its node. A row's
-// last run ends at the row's end, so a walk never passes it; run loads are also
-// clamped to the array. (Two or four segments per thread in flight, or the
-// wave's first runs merged per node before their atomics, measured slower:
-// the tier kernels then need more registers.)
 // A load through a pointer that was itself read from memory (the run table): the
 // cast tells the compiler it is global memory, so it issues a global load rather
 // than a flat one.
@@ -756,17 +812,21 @@ __device__ inline T load_global(const T *p)
     return *(const __attribute__((address_space(1))) T *)(p);
 }
 
-// Segments per row of a kind-2 slab, as log2 of the power of two >= ceil(e0 / kRunSeg).
-__host__ __device__ inline uint32_t run_lseg(uint32_t e0)
+// The skip entries that bound the runs of cells [p0, p1) of row r: the chunk of p0, and the one
+// after p1's, which past the row's last chunk is the next row's first. True if that lies past
+// the last row (the level's runs end there: no entry).
+__host__ __device__ inline bool run_skips(uint32_t rows, uint32_t chunks, uint32_t r, uint32_t p0, uint32_t p1,
+                                          uint64_t *c0, uint64_t *c1)
 {
-    uint32_t lseg = 0;
-    while ((kRunSeg << lseg) < e0) ++lseg;
-    return lseg;
+    *c0 = uint64_t(r) * chunks + p0 / kRunSkipCells;
+    *c1 = uint64_t(r) * chunks + (p1 - 1) / kRunSkipCells + 1;
+    return *c1 == uint64_t(rows) * chunks;
 }
 
 // Item `it` of a kind-2 slab: its row index r in the level's runs of orientation
-// f and its cells [p0, p1) along the row; false for a padding item past the row.
-__host__ __device__ inline bool run_item(const Slab &sp, const LevelTable &lt, uint32_t f, uint32_t lseg,
+// f (the level is Y cells deep in y and Z in z) and its cells [p0, p1) along the row;
+// false for a padding item past the row.
+__host__ __device__ inline bool run_item(const Slab &sp, uint32_t Y, uint32_t Z, uint32_t f, uint32_t lseg,
                                          uint32_t it, uint32_t *r, uint32_t *p0, uint32_t *p1)
 {
     const uint32_t c = it & ((1u << lseg) - 1), row = it >> lseg;
@@ -776,15 +836,14 @@ __host__ __device__ inline bool run_item(const Slab &sp, const LevelTable &lt, u
     const uint32_t fa = f == 0 ? x : y;
     *p0 = fa + c * kRunSeg;
     *p1 = min(*p0 + kRunSeg, fa + sp.e0);
-    *r = f == 0 ? y + lt.dims[sp.level][1] * z : z + lt.dims[sp.level][2] * x;
+    *r = f == 0 ? y + Y * z : z + Z * x;
     return *p0 < *p1;
 }
 
 // Runs of cubes on internal nodes (dense state), deferred per wave: entries (node,
 // run length | level << 9) in a ring in LDS, resolved 64 at a time, one per lane.
-// Resolving one loads the node's (a, b, w) triple (and, at rank 2, its
-// predecessors'), so the load chains of 64 runs are in flight together instead
-// of one chain in nearly every step of a slab walk. At most 63 entries wait
+// Resolving one loads the node's record, so the loads of 64 runs are in flight
+// together instead of one in nearly every step of a slab walk. At most 63 entries wait
 // after an append; the ring holds those plus the 64 one append can add.
 struct DeferRing {
     uint32_t *node;  // [waves][kDeferSlots]
@@ -811,46 +870,24 @@ __device__ inline void resolve_count(const QueryState &st, const GraphView &gv, 
                                      uint32_t lev)
 {
     if (!SPARSE && node < gv.r2_end) {
-        const NodeTriple t = gv.nodes[node];
-        const uint32_t c = len << (3u * lev);
+        const Leaf t = gv.leaf[node - gv.nseg];
         const uint32_t cube = 1u << (3u * lev);
         const float kf = t.w * float(cube);  // exact: a power-of-two scale
         const uint32_t k = uint32_t(kf);
-        if (node >= gv.r1_end) {
-            if (!(lev <= 7u && float(k) == kf && k <= cube)) {
-                push_rank2<SPARSE>(st, gv, t, float(c & 0xFFFFFF00u), float(c & 0xFFu));
-                return;
-            }
-            const bool na = t.a >= gv.nseg, nb = t.b >= gv.nseg;
-            NodeTriple ta = {0u, 0u, 0.0f}, tb = {0u, 0u, 0.0f};
-            if (na) ta = gv.nodes[t.a];
-            if (nb) tb = gv.nodes[t.b];
-            // n voxels per cube on one side: to a source, or split by a rank-1 node
-            auto side = [&](uint32_t s, bool isnode, const NodeTriple &u, uint32_t n) {
-                if (n == 0u) return;
-                if (!isnode) {
-                    atomicAdd(&st.seg_cnt[s], len * n);
-                    return;
-                }
-                const float mf = u.w * float(n), m = rintf(mf);
-                if (fabsf(mf - m) <= float(n) * 0x1p-22f && m >= 0.0f && m <= float(n)) {
-                    atomicAdd(&st.seg_cnt[u.a], len * (n - uint32_t(m)));
-                    atomicAdd(&st.seg_cnt[u.b], len * uint32_t(m));
-                    return;
-                }
-                const uint32_t cs = len * n;
-                push_pair<SPARSE>(st, u, float(cs & 0xFFFFFF00u), float(cs & 0xFFu));
-            };
-            side(t.a, na, ta, cube - k);
-            side(t.b, nb, tb, k);
+        // voxels of one cube on the a side and the b side, and of those the ones on s[1] and s[3]
+        const uint32_t na = cube - k, nb = k;
+        const float fa = t.wa * float(na), fb = t.wb * float(nb), ra = rintf(fa), rb = rintf(fb);
+        if (lev <= 7u && float(k) == kf && k <= cube && fabsf(fa - ra) <= float(na) * 0x1p-22f && ra >= 0.0f &&
+            ra <= float(na) && fabsf(fb - rb) <= float(nb) * 0x1p-22f && rb >= 0.0f && rb <= float(nb)) {
+            const uint32_t ma = uint32_t(ra), mb = uint32_t(rb);
+            if (na != ma) atomicAdd(&st.seg_cnt[t.s[0]], len * (na - ma));
+            if (ma) atomicAdd(&st.seg_cnt[t.s[1]], len * ma);
+            if (nb != mb) atomicAdd(&st.seg_cnt[t.s[2]], len * (nb - mb));
+            if (mb) atomicAdd(&st.seg_cnt[t.s[3]], len * mb);
             return;
         }
-        if (lev <= 7u && float(k) == kf && k <= cube) {
-            atomicAdd(&st.seg_cnt[t.a], len * (cube - k));
-            atomicAdd(&st.seg_cnt[t.b], len * k);
-            return;
-        }
-        push_pair<SPARSE>(st, t, float(c & 0xFFFFFF00u), float(c & 0xFFu));
+        const uint32_t c = len << (3u * lev);
+        push_leaf<SPARSE>(st, t, float(c & 0xFFFFFF00u), float(c & 0xFFu));
         return;
     }
     scatter_count<SPARSE>(st, gv, node, len << (3u * lev));
@@ -862,12 +899,17 @@ __device__ inline void ring_resolve(DeferRing &q, const QueryState &st, const Gr
 {
     const uint32_t lane = threadIdx.x & 63;
     __builtin_amdgcn_wave_barrier();
-    if (lane < n) {
+    // nothing more into a table that has overflowed (a full one is probed end to end)
+    if (lane < n && (ld(st.flags) & 1u) == 0) {
         const uint32_t k = q.wbase + ((q.head + lane) & (kDeferSlots - 1));
         const uint32_t code = q.code[k];
         resolve_count<SPARSE>(st, gv, q.node[k], code & 511u, code >> 9);
     }
     q.head += n;
+    // vmcnt(0): no load of a resolve is left pending on any path out of it. Without it the
+    // compiler waits for all loads, the walk's prefetched tiles among them, wherever a register
+    // is used again that some path of a resolve loaded, which is in every step of the walk.
+    __builtin_amdgcn_s_waitcnt(0x0f70);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -890,164 +932,306 @@ __device__ inline void ring_put(DeferRing &q, const QueryState &st, const GraphV
     if (q.tail - q.head >= 64u) ring_resolve<SPARSE>(q, st, gv, 64u);
 }
 
-// A kind-2 slab: each lane sums one (row, segment) item from the row runs. In
-// dense mode the loops are wave-uniform (lanes whose segment is done idle), so
-// that internal-node runs can go to the wave's ring; in sparse mode each lane
-// walks its items on its own.
-template <int BLOCK, bool SPARSE>
-__device__ inline void scatter_runs(const Slab &sp, const RunLevel &rl, const LevelTable &lt, const QueryState &st,
-                                    const GraphView &gv, DeferRing &dq)
+// ---------------------------------------------------------------- scatter
+//
+// Every cube of every slab adds 8^level to its node. The work of a box is one
+// sequence of tiles (the streamed slabs, slab after slab) and one of (row, segment)
+// items (the slabs summed from row runs); each wave that answers the box (of one
+// workgroup, or of several that share it) takes one contiguous range of both. A
+// wave so meets few slabs instead of a share of every one: a box of 25,000 cubes has
+// ~30 slabs, most of them a tile or two, and walking all of them with every wave
+// cost one exposed load latency per slab and wave. What bounds it is the issue of
+// vector instructions (about 75 per tile, 70 per 64 runs), so rows go to runs from
+// kRunMinRow cubes on. 100,000 boxes of a 512^3 volume, default launch: 2.82 ms with
+// the waves of a box dealt the blocks of every slab in turn and one lane per row
+// segment, 1.54 ms so.
+
+// One tile of a streamed slab: the byte offset of its first unit in its buffer, the bytes
+// between its rows, and, packed: ltx (3 bits), units and rows of it inside the slab (7 bits
+// each), level (5), kind (1), and whether its first unit's low element (23: kind 1, the row
+// starts one element before the slab) or its last unit's high element (24) lies outside.
+struct TileDesc {
+    uint64_t off;
+    uint32_t s1b, pack;
+};
+
+__host__ __device__ inline uint32_t tile_ltx_of(uint32_t pack) { return pack & 7u; }
+__host__ __device__ inline uint32_t tile_units(uint32_t pack) { return (pack >> 3) & 127u; }
+__host__ __device__ inline uint32_t tile_rows(uint32_t pack) { return (pack >> 10) & 127u; }
+__host__ __device__ inline uint32_t tile_level(uint32_t pack) { return (pack >> 17) & 31u; }
+__host__ __device__ inline bool tile_pairs(uint32_t pack) { return (pack >> 22) & 1u; }
+constexpr uint32_t kTileSpan = (127u << 3) | (127u << 10);  // no unit inside: nothing to consume
+
+// Tile `o` of a slab: along the row first, then down the rows, then the slices.
+__host__ __device__ inline TileDesc tile_desc(const Slab &sl, uint32_t o)
 {
-    const uint32_t f = uni(sp.axes) & 3u, lev = uni(sp.level), lw8 = 3 * lev;
-    const uint32_t lseg = run_lseg(uni(sp.e0));
-    const uint32_t items = (uni(sp.e1) * uni(sp.e2)) << lseg;
-    const uint32_t top = rl.n_runs - 1;
-    const uint32_t lane = threadIdx.x & 63;
-    // runs v[0 .. kRunBatch): each adds its cells in [pos, p1)
-    auto consume = [&](const uint64_t *v, uint32_t &pos, uint32_t p1) {
+    const uint32_t ltx = tile_ltx(sl), lty = 6u - ltx, ty = 1u << lty;
+    const uint32_t n_t0 = (sl.units + (1u << ltx) - 1) >> ltx, n_rt = (sl.e1 + ty - 1) >> lty;
+    uint32_t t0 = 0, r = o;
+    if (n_t0 > 1) r = o / n_t0, t0 = o - r * n_t0;
+    uint32_t rt = r, k2 = 0;
+    if (sl.e2 > 1) k2 = r / n_rt, rt = r - k2 * n_rt;
+    const uint32_t left = sl.units - (t0 << ltx), ucap = left < (1u << ltx) ? left : 1u << ltx;
+    const uint32_t below = sl.e1 - (rt << lty), rcap = below < ty ? below : ty;
+    const bool pairs = sl.kind == 1;
+    TileDesc d;
+    d.off = sl.base + uint64_t(k2) * sl.s2b + uint64_t(rt << lty) * sl.s1b + (uint64_t(t0) << ltx) * 4u;
+    d.s1b = sl.s1b;
+    d.pack = ltx | (ucap << 3) | (rcap << 10) | (uint32_t(sl.level) << 17) | (pairs ? 1u << 22 : 0u) |
+             (pairs && sl.odd && t0 == 0 ? 1u << 23 : 0u) |
+             (pairs && ((sl.e0 + sl.odd) & 1u) && t0 == n_t0 - 1 ? 1u << 24 : 0u);
+    return d;
+}
+
+// A lane's byte offset in its tile (0, the tile's first unit, where its own unit is outside
+// the slab: every load stays inside) and the bits its loaded word is OR-ed with: all ones in
+// every part outside the slab, so that kEmpty (kind 0) or 0xFFFF (kind 1) marks it.
+__host__ __device__ inline uint32_t tile_lane(uint32_t pack, uint32_t s1b, uint32_t lane, uint32_t *mask)
+{
+    const uint32_t ltx = tile_ltx_of(pack), lx = lane & ((1u << ltx) - 1), ly = lane >> ltx;
+    const uint32_t ucap = tile_units(pack);
+    const bool ok = lx < ucap && ly < tile_rows(pack);
+    const uint32_t part = (((pack >> 23) & 1u) && lx == 0 ? 0xFFFFu : 0u) |
+                          (((pack >> 24) & 1u) && lx + 1 == ucap ? 0xFFFF0000u : 0u);
+    *mask = ok ? part : kEmpty;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t off = __umul24(ly, s1b) + lx * 4u;  // s1b < 2^24 unless ly == 0
+#else
+    const uint32_t off = ly * s1b + lx * 4u;
+#endif
+    return ok ? off : 0u;
+}
+
+// The slab that holds tile (or item) `t`: the last one with first[i] <= t.
+__device__ inline uint32_t find_slab(const uint32_t *first, uint32_t n_slabs, uint32_t t)
+{
+    uint32_t i = 0;
 #pragma unroll
-        for (int q = 0; q < kRunBatch; ++q) {
-            const uint32_t end = uint32_t(v[q] >> 32), node = uint32_t(v[q]);
-            const bool act = pos < p1 && end > pos;
-            const uint32_t hi = min(end, p1);
-            if (SPARSE) {
-                if (act) scatter_count<SPARSE>(st, gv, node, (hi - pos) << lw8);
-            } else {
-                if (act && node < gv.nseg) atomicAdd(&st.seg_cnt[node], (hi - pos) << lw8);
-                ring_put<SPARSE>(dq, st, gv, act && node >= gv.nseg, node, hi - pos, lev);
-            }
-            if (act) pos = hi;
+    for (uint32_t step = 64; step > 0; step >>= 1)
+        if (i + step < n_slabs && first[i + step] <= t) i += step;
+    return i;
+}
+
+// One wave's tiles [a, b), b > a. The descriptors of 64 tiles are computed at once, one per
+// lane; a tile's load then takes its scalars from the lane that holds it. GROUP tiles are
+// loaded while the GROUP before them are consumed (2 GROUP loads in flight per lane), across
+// slabs and levels alike; past the range the last tile's first unit is loaded and not
+// consumed.
+template <int GROUP, bool SPARSE>
+__device__ __attribute__((always_inline)) inline void stream_tiles(const char *maps, const char *maps16,
+                                                                   const QueryState &st, const GraphView &gv,
+                                                                   uint32_t n_slabs, uint32_t a, uint32_t b,
+                                                                   DeferRing &dq, const uint32_t *flags_lds)
+{
+    typedef uint32_t Words __attribute__((ext_vector_type(GROUP)));
+    const uint32_t lane = threadIdx.x & 63, nseg = gv.nseg;
+    const uint64_t above = lane_above_mask();
+    uint64_t d_at = 0;
+    uint32_t d_s1b = 0, d_pack = 0;
+    auto describe = [&](uint32_t first) {  // lane i: tile first + i
+        const uint32_t t = min(first + lane, b - 1);
+        const uint32_t i = find_slab(st.tile0, n_slabs, t);
+        const TileDesc d = tile_desc(st.slabs[i], t - st.tile0[i]);
+        d_at = reinterpret_cast<uint64_t>(tile_pairs(d.pack) ? maps16 : maps) + d.off;
+        d_s1b = d.s1b;
+        d_pack = first + lane < b ? d.pack : d.pack & ~kTileSpan;
+    };
+    auto load = [&](Words &v, Words &m, uint32_t i0) {  // tiles i0 .. i0 + GROUP - 1 of the described 64
+#pragma unroll
+        for (int u = 0; u < GROUP; ++u) {
+            const int i = int(i0) + u;
+            const uint64_t at = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(d_at)), i))) |
+                                (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(d_at >> 32)), i))) << 32);
+            const uint32_t s1b = uint32_t(__builtin_amdgcn_readlane(int(d_s1b), i));
+            const uint32_t pack = uint32_t(__builtin_amdgcn_readlane(int(d_pack), i));
+            uint32_t mask;
+            const uint32_t off = tile_lane(pack, s1b, lane, &mask);
+            typedef const __attribute__((address_space(1))) char *Global;
+            v[u] = *(const __attribute__((address_space(1))) uint32_t *)(Global(at) + off);
+            m[u] = mask;
         }
     };
-    if constexpr (SPARSE) {  // no ring: each lane walks its own items
-        for (uint32_t it = threadIdx.x; it < items; it += BLOCK) {
-            uint32_t r, p0, p1;
-            if (!run_item(sp, lt, f, lseg, it, &r, &p0, &p1)) continue;
-            uint32_t j = load_global(rl.skip + uint64_t(r) * rl.chunks + p0 / kRunSkipCells);
-            uint64_t v[kRunBatch];
-#pragma unroll
-            for (int q = 0; q < kRunBatch; ++q) v[q] = load_global(rl.runs + min(j + q, top));
-            uint32_t pos = p0;
-            consume(v, pos, p1);
-            while (pos < p1) {  // segments that cross more runs
-                j += kRunBatch;
-                uint64_t w[kRunBatch];
-#pragma unroll
-                for (int q = 0; q < kRunBatch; ++q) w[q] = load_global(rl.runs + min(j + q, top));
-                consume(w, pos, p1);
+    Words v, m;
+    describe(a);
+    load(v, m, 0);
+    uint32_t packs = d_pack, i0 = 0;  // the descriptors and position of the group in v
+    uint32_t iter = 0;
+    for (uint32_t t = a; t < b; t += GROUP) {
+        if ((++iter & 7u) == 0 && (uni(*flags_lds) & 1u)) return;  // overflowed: the box is redone elsewhere
+        uint32_t n0 = i0 + GROUP;
+        if (n0 == 64) {
+            n0 = 0;
+            describe(t + GROUP < b ? t + GROUP : b - 1);
+            if (t + GROUP >= b) d_pack &= ~kTileSpan;
+        }
+        Words w, wm;
+        load(w, wm, n0);
+        const uint32_t n_u = min(uint32_t(GROUP), b - t);
+#pragma unroll 1
+        for (uint32_t u = 0; u < n_u; ++u) {
+            const uint32_t pack = uint32_t(__builtin_amdgcn_readlane(int(packs), int(i0 + u)));
+            const uint32_t x = v[u] | m[u];
+            if (!SPARSE && tile_pairs(pack)) {  // level 0: every node is a source; two cubes per unit
+                count_pairs(st.seg_cnt, x & 0xFFFFu, x >> 16, lane);
+                continue;
+            }
+            const uint32_t lev = tile_level(pack), lw8 = 3 * lev;
+            if (SPARSE) {
+                uint32_t len;
+                if (run_head(x, above, &len)) scatter_count<SPARSE>(st, gv, x, len << lw8);
+                continue;
+            }
+            // a run of lanes [a, b] on one source adds (b + 1 - a) 8^l as -a 8^l at its start
+            // lane and (b + 1) 8^l at its end lane (uint32 wrap-around; the counts stay below
+            // 2^32); neighbours by DPP wave shifts (lane 0 / lane 63 read 0 and are a start / an end)
+            const uint32_t prev = uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x138, 0xF, 0xF, true));
+            const uint32_t next = uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x130, 0xF, 0xF, true));
+            const bool start = x != prev || lane == 0;
+            const bool end = x != next || lane == 63;
+            if (x < nseg) {  // a source (kEmpty is not)
+                if (start) atomicAdd(&st.seg_cnt[x], 0u - (lane << lw8));
+                if (end) atomicAdd(&st.seg_cnt[x], (lane + 1) << lw8);
+            }
+            // runs on internal nodes: a branch the wave skips unless a lane needs it
+            // (wave masks straight from the vector compares: every lane is active here)
+            const bool isint = x - nseg < kEmpty - nseg;
+            const uint64_t internal = __builtin_amdgcn_uicmp(x - nseg, kEmpty - nseg, 36 /* ult */);
+            if (internal != 0) {
+                const uint64_t put = internal & (__builtin_amdgcn_uicmp(x, prev, 33 /* ne */) | 1u);
+                const uint64_t ends = __builtin_amdgcn_uicmp(x, next, 33 /* ne */) | (1ull << 63);
+                if (start && isint) {
+                    // the run ends at the first end lane at or above this one
+                    const uint32_t len = uint32_t(__builtin_ctzll(ends >> lane)) + 1u;
+                    const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                        uint32_t(put >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(put), 0u));
+                    const uint32_t k = dq.wbase + ((dq.tail + below) & (kDeferSlots - 1));
+                    dq.node[k] = x;
+                    dq.code[k] = uint16_t(len | (lev << 9));
+                }
+                dq.tail += uint32_t(__builtin_popcountll(put));
+                if (dq.tail - dq.head >= 64u) ring_resolve<SPARSE>(dq, st, gv, 64u);
             }
         }
-        return;
+        v = w, m = wm;
+        packs = d_pack, i0 = n0;
     }
-    for (uint32_t b0 = uni(threadIdx.x - lane); b0 < items; b0 += BLOCK) {
+}
+
+// One wave's run items [a, b). 64 items (one row segment each, at most kRunSeg cells) are
+// described at once, one per lane: its cells [p0, p1), and from two skip entries the runs that
+// may cross it (from the one holding the first cell of p0's chunk to the one holding the first
+// cell past p1's chunk, or the row's last). The wave then takes the 64 items' runs as one
+// sequence, a run per lane and step: every load is coalesced and issued one step ahead, and no
+// lane waits for another's longer segment. (One lane per segment, four runs at a time, spent
+// a load latency on every four runs of the longest of 64 segments.) A run starts where the one
+// before it ends: the lane below's, the step before's for lane 0; of an item's first run every
+// cell from p0 on counts.
+template <bool SPARSE>
+__device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *runs, const LevelRow *rows,
+                                                               const QueryState &st, const GraphView &gv,
+                                                               uint32_t n_slabs, uint32_t a, uint32_t b,
+                                                               DeferRing &dq, const uint32_t *flags_lds)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint32_t b0 = a; b0 < b; b0 += 64) {
+        if (uni(*flags_lds) & 1u) return;
         const uint32_t it = b0 + lane;
-        uint32_t r, p0 = 0, p1 = 0, j = 0;
-        if (!(it < items && run_item(sp, lt, f, lseg, it, &r, &p0, &p1))) p0 = p1 = 0;
-        uint64_t v[kRunBatch] = {};
-        if (p0 < p1) {
-            j = load_global(rl.skip + uint64_t(r) * rl.chunks + p0 / kRunSkipCells);
-#pragma unroll
-            for (int q = 0; q < kRunBatch; ++q) v[q] = load_global(rl.runs + min(j + q, top));
-        }
-        uint32_t pos = p0;
-        consume(v, pos, p1);
-        while (__builtin_amdgcn_ballot_w64(pos < p1) != 0) {  // segments that cross more runs
-            uint64_t w[kRunBatch] = {};
-            if (pos < p1) {
-                j += kRunBatch;
-#pragma unroll
-                for (int q = 0; q < kRunBatch; ++q) w[q] = load_global(rl.runs + min(j + q, top));
+        uint32_t span = 0, lev = 0, j0 = 0, cnt = 0;  // span: p0 | p1 << 16 (rows hold at most 2^15 cells)
+        if (it < b) {
+            const uint32_t i = find_slab(st.item0, n_slabs, it);
+            const Slab &sp = st.slabs[i];
+            lev = sp.level;
+            const uint32_t f = sp.axes & 3u;
+            const RunLevel &rl = runs[2 * lev + f];
+            uint32_t r, p0, p1;
+            if (run_item(sp, rows[lev].Y, rows[lev].Z, f, run_lseg(sp.e0), it - st.item0[i], &r, &p0, &p1)) {
+                span = p0 | (p1 << 16);
+                uint64_t c0, c1;
+                const bool last = run_skips(rl.rows, rl.chunks, r, p0, p1, &c0, &c1);
+                const uint32_t lo = load_global(rl.skip + c0);
+                uint32_t hi = last ? rl.n_runs : load_global(rl.skip + c1);  // a row's first run or one inside it
+                if ((p1 - 1) / kRunSkipCells + 1 == rl.chunks) --hi;         // the run before the next row's first
+                hi = min(hi, rl.n_runs - 1);
+                j0 = rl.first + lo;
+                cnt = hi >= lo ? hi - lo + 1 : 0u;
             }
-            consume(w, pos, p1);
+        }
+        // position of each item's first run in the sequence
+        uint32_t pos = cnt;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = uint32_t(__shfl_up(int(pos), off, 64));
+            if (lane >= uint32_t(off)) pos += v;
+        }
+        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(pos), 63));
+        if (total == 0) continue;
+        pos -= cnt;
+        j0 -= pos;  // run index less position
+        auto from = [](uint32_t v, uint32_t src) {
+            return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
+        };
+        // this lane's run of the step at s: the last item that starts at or before it
+        auto fetch = [&](uint32_t s, uint64_t *v, uint32_t *cells, uint32_t *lv, bool *first) {
+            const uint32_t x = min(s + lane, total - 1);
+            uint32_t i = 0, at = 0;
+#pragma unroll
+            for (uint32_t step = 32; step > 0; step >>= 1) {
+                const uint32_t p = from(pos, i + step);
+                if (p <= x) i += step, at = p;
+            }
+            *v = load_global(gv.runs + (from(j0, i) + x));
+            const uint32_t sc = from(span, i);
+            *cells = s + lane < total ? sc : 0u;  // no cells past the end
+            *lv = from(lev, i);
+            *first = x == at;
+        };
+        uint64_t v, w;
+        uint32_t cells, lv, cells1, lv1, carry = 0;
+        bool first, first1;
+        fetch(0, &v, &cells, &lv, &first);
+        for (uint32_t s = 0; s < total; s += 64) {
+            fetch(s + 64, &w, &cells1, &lv1, &first1);  // past the end: the last run again, not counted
+            const uint32_t end = uint32_t(v >> 32), node = uint32_t(v);
+            uint32_t begin = uint32_t(__builtin_amdgcn_update_dpp(int(carry), int(end), 0x138, 0xF, 0xF, false));
+            carry = uint32_t(__builtin_amdgcn_readlane(int(end), 63));
+            begin = max(first ? 0u : begin, cells & 0xFFFFu);
+            const uint32_t to = min(end, cells >> 16);
+            const bool act = to > begin;
+            const uint32_t len = to - begin;
+            if (SPARSE) {
+                if (act) scatter_count<SPARSE>(st, gv, node, len << (3 * lv));
+            } else {
+                if (act && node < gv.nseg) atomicAdd(&st.seg_cnt[node], len << (3 * lv));
+                ring_put<SPARSE>(dq, st, gv, act && node >= gv.nseg, node, len, lv);
+            }
+            v = w, cells = cells1, lv = lv1, first = first1;
         }
     }
 }
 
-// Scatter: every cube of every slab adds 8^level to its node. Neighbouring
-// lanes usually hold the same node (mixtures are spatially coherent), so a run
-// of equal nodes in a wave adds its total once. Runs on sources add to an
-// integer counter through their two end lanes (start: -a 8^l, end: (b+1) 8^l
-// for lanes a..b), which needs no run length; runs on internal nodes take a
-// branch that the whole wave skips when no lane needs it, where each start lane
-// hands (node, run length, level) to the wave's deferral ring (dense state) or
-// scatters run length * 8^level at once (sparse state). Level-0 slabs of the
-// 16-bit copy (kind 1) hold two sources per unit (count_pairs).
-template <int BLOCK, int UNROLL, bool SPARSE>
-__device__ __attribute__((always_inline)) inline void scatter_slabs(
-    const Slab *slabs, int n_slabs, const char *__restrict__ maps, const char *__restrict__ maps16,
-    const RunLevel *runs, const LevelTable &lt, const QueryState &st, const GraphView &gv, const uint32_t *flags_lds)
+// Part `part` of `parts` of a box's scatter, by one workgroup. Runs on sources add to an
+// integer counter; runs on internal nodes go through the wave's deferral ring (dense state)
+// or are scattered at once (sparse state).
+template <int BLOCK, int GROUP, bool SPARSE>
+__device__ __attribute__((always_inline)) inline void scatter_box(const char *maps, const char *maps16,
+                                                                  const RunLevel *runs, const LevelRow *rows,
+                                                                  const QueryState &st, const GraphView &gv,
+                                                                  uint32_t n_slabs, uint32_t part, uint32_t parts,
+                                                                  const uint32_t *flags_lds)
 {
     constexpr uint32_t kWaves = BLOCK / 64;
-    const uint32_t nseg = gv.nseg;
-    const uint64_t above = lane_above_mask();
-    const uint32_t lane = threadIdx.x & 63;
-    // Runs on internal nodes met while streaming the 32-bit levels (dense state) are
-    // deferred to a per-wave ring in LDS, (node, run length | level << 7), and resolved
-    // 64 at a time, one per lane: resolving one loads the node's (a, b, w) triple (and,
-    // at rank 2, its predecessors'), so the load chains of 64 runs are in flight together
-    // instead of one chain in nearly every wave step. At most 63 entries wait after a
-    // step; the ring holds those plus the 64 a step can add.
     __shared__ uint32_t dq_node[kWaves * (SPARSE ? 1u : kDeferSlots)];
     __shared__ uint16_t dq_code[kWaves * (SPARSE ? 1u : kDeferSlots)];
-    DeferRing dq{dq_node, dq_code, uni(threadIdx.x >> 6) * kDeferSlots, 0u, 0u};
-    for (int si = 0; si < n_slabs; ++si) {
-        const Slab &sp = slabs[si];
-        if (uni(*flags_lds) & 1u) return;  // overflowed: the box goes to the retry launch
-        if (uni(sp.kind) == 2) {
-            scatter_runs<BLOCK, SPARSE>(sp, runs[2 * uni(sp.level) + (uni(sp.axes) & 3u)], lt, st, gv, dq);
-            continue;
-        }
-        const uint64_t base = (uint64_t(uni(uint32_t(sp.base >> 32))) << 32) | uni(uint32_t(sp.base));
-        const TileWalk tw = tile_walk(uni(sp.units), uni(sp.e1), uni(sp.e2), uni(sp.s1b), uni(sp.s2b), UNROLL);
-        if (!SPARSE && uni(sp.kind) == 1) {
-            // level 0: every node is a source; two cubes per unit
-            stream_pairs<UNROLL, kWaves>(maps16 + base, tw, uni(sp.e0), uni(sp.odd), uint32_t(si) % kWaves,
-                                         [&](uint32_t lo, uint32_t hi) { count_pairs(st.seg_cnt, lo, hi, lane); });
-            continue;
-        }
-        const uint32_t lev = uni(sp.level), lw8 = 3 * lev;
-        // a run of lanes [a, b] on one source adds (b + 1 - a) 8^l as -a 8^l at its start lane
-        // and (b + 1) 8^l at its end lane (uint32 wrap-around; the counts stay below 2^32)
-        const uint32_t w_start = 0u - (lane << lw8), w_end = (lane + 1) << lw8;
-        const bool go = stream_slab<UNROLL, kWaves>(
-            maps + base, tw, uint32_t(si) % kWaves,
-            [&](uint32_t v) {
-                if (SPARSE) {
-                    uint32_t len;
-                    if (run_head(v, above, &len)) scatter_count<SPARSE>(st, gv, v, len << lw8);
-                    return;
-                }
-                // neighbours by DPP wave shifts (lane 0 / lane 63 read 0 and are a start / an end)
-                const uint32_t prev = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x138, 0xF, 0xF, true));
-                const uint32_t next = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x130, 0xF, 0xF, true));
-                const bool start = v != prev || lane == 0;
-                const bool end = v != next || lane == 63;
-                if (v < nseg) {  // a source (kEmpty is not)
-                    if (start) atomicAdd(&st.seg_cnt[v], w_start);
-                    if (end) atomicAdd(&st.seg_cnt[v], w_end);
-                }
-                // runs on internal nodes: a branch the wave skips unless a lane needs it
-                // (wave masks straight from the vector compares: every lane is active here)
-                const bool isint = v - nseg < kEmpty - nseg;
-                const uint64_t internal = __builtin_amdgcn_uicmp(v - nseg, kEmpty - nseg, 36 /* ult */);
-                if (__builtin_expect(internal != 0, 0)) {
-                    const uint64_t put = internal & (__builtin_amdgcn_uicmp(v, prev, 33 /* ne */) | 1u);
-                    const uint64_t ends = __builtin_amdgcn_uicmp(v, next, 33 /* ne */) | (1ull << 63);
-                    if (start && isint) {
-                        // the run ends at the first end lane at or above this one
-                        const uint32_t len = uint32_t(__builtin_ctzll(ends >> lane)) + 1u;
-                        const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                            uint32_t(put >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(put), 0u));
-                        const uint32_t k = dq.wbase + ((dq.tail + below) & (kDeferSlots - 1));
-                        dq_node[k] = v;
-                        dq_code[k] = uint16_t(len | (lev << 9));
-                    }
-                    dq.tail += uint32_t(__builtin_popcountll(put));
-                    if (dq.tail - dq.head >= 64u) ring_resolve<SPARSE>(dq, st, gv, 64u);
-                }
-            },
-            [&]() { return (uni(*flags_lds) & 1u) != 0; });
-        if (!go) return;
+    const uint32_t wave = uni(threadIdx.x >> 6);
+    DeferRing dq{dq_node, dq_code, wave * kDeferSlots, 0u, 0u};
+    const uint32_t waves = parts * kWaves, w = part * kWaves + wave;
+    const uint32_t tiles = uni(st.tile0[n_slabs]), items = uni(st.item0[n_slabs]);
+    if (tiles) {
+        const uint32_t per = (tiles + waves - 1) / waves, a = w * per;
+        if (a < tiles) stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, a, min(a + per, tiles), dq, flags_lds);
+    }
+    if (items) {  // from the other end of the waves, which got the fewer tiles
+        const uint32_t per = ((items + 63) / 64 + waves - 1) / waves * 64, a = (waves - 1 - w) * per;
+        if (a < items) sum_runs<SPARSE>(runs, rows, st, gv, n_slabs, a, min(a + per, items), dq, flags_lds);
     }
     if (!SPARSE && dq.tail != dq.head) ring_resolve<SPARSE>(dq, st, gv, dq.tail - dq.head);
 }
@@ -1137,17 +1321,17 @@ struct QueryArgs {
 template <int BLOCK, bool SPARSE, bool ERR>
 __device__ inline void expand_lut(const QueryArgs &A, const QueryState &st)
 {
-    constexpr uint32_t kGroup = 8;
+    constexpr uint32_t kLanes = 8;
     const uint32_t nu = ld(st.n_used);
     if (nu == 0 || (ld(st.flags) & 1u)) return;  // uniform
-    const uint32_t g = threadIdx.x & (kGroup - 1);
-    for (uint32_t i = threadIdx.x / kGroup; i < nu; i += BLOCK / kGroup) {
+    const uint32_t g = threadIdx.x & (kLanes - 1);
+    for (uint32_t i = threadIdx.x / kLanes; i < nu; i += BLOCK / kLanes) {
         const uint32_t slot = ld(&st.used[i]);
         const uint32_t key = ld(&st.keys[slot]);
         if (key < A.gv.r1_end) continue;  // a source (sparse mode); rank-1 nodes never enter the table
         const float mh = ld(&st.hi[slot]), ml = ld(&st.lo[slot]);
         const uint64_t e = A.lut_ptr[key + 1];
-        for (uint64_t j = A.lut_ptr[key] + g; j < e; j += kGroup) {
+        for (uint64_t j = A.lut_ptr[key] + g; j < e; j += kLanes) {
             float ph, pl;
             scale_pair(A.lut_val[j], mh, ml, &ph, &pl);
             add_source_mass<SPARSE>(st, A.lut_seg[j], ph, pl);
@@ -1166,14 +1350,21 @@ __host__ __device__ inline uint32_t lds_state_bytes(uint32_t nseg, uint32_t cap,
 {
     return ((sparse ? cap * 20u : nseg * 12u + cap * 16u) + 15u) & ~15u;
 }
+// The slab list and its two prefix arrays.
+__host__ __device__ inline uint32_t lds_slab_bytes(uint32_t n_levels)
+{
+    return 6u * n_levels * uint32_t(sizeof(Slab)) + 2u * (6u * n_levels + 1u) * 4u;
+}
 __host__ __device__ inline uint32_t lds_bytes(uint32_t nseg, uint32_t cap, bool sparse, uint32_t n_levels,
                                               bool err = false)
 {
-    return lds_state_bytes(nseg, cap, sparse) + 6u * n_levels * uint32_t(sizeof(Slab)) + (err ? 4u * nseg : 0u);
+    return lds_state_bytes(nseg, cap, sparse) + lds_slab_bytes(n_levels) + (err ? 4u * nseg : 0u);
 }
 
 struct QueryShared {
     uint32_t rank_ptr[kMaxSteps + 2];
+    LevelRow rows[kMaxLevelsDev];          // extents of every level
+    RunLevel runs[2 * kMaxLevelsDev];      // row runs of every level and orientation
     int n_slabs;
     uint32_t n_used;
     uint32_t flags;
@@ -1292,7 +1483,7 @@ __device__ inline void write_failure(const QueryArgs &A, uint32_t q)
 // One query, by the whole block. `st` must be clean (keys empty, values 0).
 // ERR: lookup-table expansion that also accumulates uncertainties (dense output).
 // (always inlined: each query kernel is one function, whatever the inliner's size limit)
-template <int BLOCK, int UNROLL, bool SPARSE, bool ERR>
+template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
 __device__ __attribute__((always_inline)) inline void run_query(const QueryArgs &A, QueryShared &sh,
                                                                 const QueryState &st, uint32_t q,
                                                                 bool report_overflow)
@@ -1306,11 +1497,13 @@ __device__ __attribute__((always_inline)) inline void run_query(const QueryArgs 
         sh.n_slabs = 0;
     }
     __syncthreads();
-    if (nonempty) build_slabs(A.lt, lo, hi, st.slabs, &sh.n_slabs);
+    if (nonempty) build_slabs(A.lt, sh.rows, lo, hi, st.slabs, &sh.n_slabs, st.tile0, st.item0);
     __syncthreads();
-    scatter_slabs<BLOCK, UNROLL, SPARSE>(st.slabs, sh.n_slabs, reinterpret_cast<const char *>(A.maps),
-                                         reinterpret_cast<const char *>(A.maps16), A.runs, A.lt, st, A.gv,
-                                         &sh.flags);
+    const uint32_t n_slabs = uni(uint32_t(sh.n_slabs));
+    if (n_slabs)
+        scatter_box<BLOCK, GROUP, SPARSE>(reinterpret_cast<const char *>(A.maps),
+                                          reinterpret_cast<const char *>(A.maps16), sh.runs, sh.rows, st, A.gv,
+                                          n_slabs, 0u, 1u, &sh.flags);
     __syncthreads();
     if (ERR || A.lut_ptr)
         expand_lut<BLOCK, SPARSE, ERR>(A, st);
@@ -1358,9 +1551,19 @@ __device__ __attribute__((always_inline)) inline void run_query(const QueryArgs 
 }
 
 template <int BLOCK>
-__device__ inline void load_rank_ptr(const QueryArgs &A, QueryShared &sh)
+__device__ inline void load_graph_tables(const QueryArgs &A, QueryShared &sh)
 {
     for (uint32_t i = threadIdx.x; i < A.depth + 2; i += BLOCK) sh.rank_ptr[i] = A.rank_ptr[i];
+    for (uint32_t i = threadIdx.x; i < A.lt.n_levels; i += BLOCK) sh.rows[i] = level_row(A.lt, i);
+    for (uint32_t i = threadIdx.x; i < 2 * A.lt.n_levels; i += BLOCK) sh.runs[i] = A.runs[i];
+}
+
+// The slab list and its prefix arrays at `p` (LDS, lds_slab_bytes).
+__device__ inline void place_slabs(QueryState &st, char *p, uint32_t n_levels)
+{
+    st.slabs = reinterpret_cast<Slab *>(p);
+    st.tile0 = reinterpret_cast<uint32_t *>(p + 6u * n_levels * uint32_t(sizeof(Slab)));
+    st.item0 = st.tile0 + 6u * n_levels + 1u;
 }
 
 template <bool SPARSE>
@@ -1368,9 +1571,8 @@ __device__ inline QueryState lds_state(char *dyn, QueryShared &sh, uint32_t nseg
                                       bool err)
 {
     QueryState st;
-    st.slabs = reinterpret_cast<Slab *>(dyn + lds_state_bytes(nseg, cap, SPARSE));
-    st.seg_var = err ? reinterpret_cast<float *>(dyn + lds_state_bytes(nseg, cap, SPARSE) +
-                                                 6u * n_levels * uint32_t(sizeof(Slab)))
+    place_slabs(st, dyn + lds_state_bytes(nseg, cap, SPARSE), n_levels);
+    st.seg_var = err ? reinterpret_cast<float *>(dyn + lds_state_bytes(nseg, cap, SPARSE) + lds_slab_bytes(n_levels))
                      : nullptr;
     uint32_t *t = reinterpret_cast<uint32_t *>(dyn);
     if (SPARSE) {
@@ -1421,24 +1623,23 @@ __global__ __launch_bounds__(kBlock) void query_plain_kernel(QueryArgs A)
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
     const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, false);
-    load_rank_ptr<kBlock>(A, sh);
+    load_graph_tables<kBlock>(A, sh);
     clear_lds_state<kBlock, SPARSE, false>(st, A.gv.nseg);
     __syncthreads();
-    run_query<kBlock, kUnroll, SPARSE, false>(A, sh, st, blockIdx.x, A.ovf_out != nullptr);
+    run_query<kBlock, kGroup, SPARSE, false>(A, sh, st, blockIdx.x, A.ovf_out != nullptr);
 }
 
 // Batched tiers: persistent blocks take queries from the largest-first order.
 // BIG: positions [0, counters[8]); otherwise [counters[8], n).
-template <int BLOCK, bool BIG, int UNROLL, bool SPARSE, bool ERR>
-// Six waves per SIMD (24 per CU: 1536 threads): the register budget the kernel is
-// tuned for (at most 80 VGPRs), so that the memory latency of the streamed node
-// IDs stays hidden.
-__global__ __launch_bounds__(BLOCK, 1536 / BLOCK) void query_tier_kernel(QueryArgs A)
+// Six waves per SIMD (the second argument counts them): at most 80 VGPRs, so that
+// the memory latency of the streamed node IDs stays hidden.
+template <int BLOCK, bool BIG, int GROUP, bool SPARSE, bool ERR>
+__global__ __launch_bounds__(BLOCK, 6) void query_tier_kernel(QueryArgs A)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
     const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
-    load_rank_ptr<BLOCK>(A, sh);
+    load_graph_tables<BLOCK>(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
     const uint32_t split = ld(&A.counters[8]);
     const uint32_t begin = BIG ? 0u : split, end = BIG ? split : A.n;
@@ -1465,20 +1666,20 @@ __global__ __launch_bounds__(BLOCK, 1536 / BLOCK) void query_tier_kernel(QueryAr
         for (uint32_t i = 0; i < chunk; ++i) {
             const uint32_t k = k0 + i * nq;
             if (k >= end) break;
-            run_query<BLOCK, UNROLL, SPARSE, ERR>(A, sh, st, A.order[k], A.ovf_out != nullptr);
+            run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, A.order[k], A.ovf_out != nullptr);
         }
     }
 }
 
 // Retry of boxes whose tier table overflowed (list 1), with a larger LDS table;
 // what overflows again goes to list 2.
-template <int BLOCK, int UNROLL, bool SPARSE, bool ERR>
+template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
 __global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
     const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
-    load_rank_ptr<BLOCK>(A, sh);
+    load_graph_tables<BLOCK>(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
     const uint32_t n_list = ld(&A.counters[1]);
     for (;;) {
@@ -1486,7 +1687,7 @@ __global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A)
         __syncthreads();
         const uint32_t k = sh.q;
         if (k >= n_list) break;  // uniform
-        run_query<BLOCK, UNROLL, SPARSE, ERR>(A, sh, st, A.overflow[k], true);
+        run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, A.overflow[k], true);
     }
 }
 
@@ -1514,7 +1715,7 @@ __global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A)
     st.lo = A.g_lo + w * gs;
     st.used = A.g_used + w * gs;
     st.cap = A.g_slots;
-    st.slabs = reinterpret_cast<Slab *>(dyn);  // the only dynamic LDS of this kernel
+    place_slabs(st, dyn, A.lt.n_levels);  // the only dynamic LDS of this kernel
     st.limit = st.cap / 4 * 3;
     st.n_used = &sh.n_used;
     st.flags = &sh.flags;
@@ -1523,7 +1724,7 @@ __global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A)
     st.seg_hi = A.g_seg_hi + w * A.gv.nseg;
     st.seg_lo = A.g_seg_lo + w * A.gv.nseg;
     st.seg_var = ERR ? A.g_seg_var + w * A.gv.nseg : nullptr;
-    load_rank_ptr<kBlock>(A, sh);
+    load_graph_tables<kBlock>(A, sh);
     __syncthreads();
     const uint32_t n_over = ld(&A.counters[A.g_count_idx]);
     for (;;) {
@@ -1531,7 +1732,7 @@ __global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A)
         __syncthreads();
         const uint32_t k = sh.q;
         if (k >= n_over) break;  // uniform
-        run_query<kBlock, kUnroll, false, ERR>(A, sh, st, A.g_list[k], A.ovf_out != nullptr);
+        run_query<kBlock, kGroup, false, ERR>(A, sh, st, A.g_list[k], A.ovf_out != nullptr);
     }
 }
 
@@ -1671,13 +1872,15 @@ __global__ __launch_bounds__(kBlock) void footprint_kernel(LevelTable lt, const 
     __shared__ Slab slabs[kMaxSlabs];
     __shared__ int n_slabs;
     __shared__ uint32_t per_level[MG_MAX_LEVELS];
+    __shared__ LevelRow rows[kMaxLevelsDev];
     const uint32_t q = blockIdx.x;
     if (threadIdx.x == 0) n_slabs = 0;
+    if (threadIdx.x < lt.n_levels) rows[threadIdx.x] = level_row(lt, threadIdx.x);
     if (threadIdx.x < MG_MAX_LEVELS) per_level[threadIdx.x] = 0;
     uint32_t lo[3], hi[3];
     const bool nonempty = clip_box(boxes + 6 * uint64_t(q), lt, lo, hi);
     __syncthreads();
-    if (nonempty) build_slabs(lt, lo, hi, slabs, &n_slabs);
+    if (nonempty) build_slabs(lt, rows, lo, hi, slabs, &n_slabs, nullptr, nullptr);
     __syncthreads();
     for (int si = 0; si < n_slabs; ++si) {
         const Slab sl = slabs[si];
@@ -1903,13 +2106,15 @@ __global__ __launch_bounds__(kColourBlock) void box_colour_kernel(LevelTable lt,
     __shared__ Slab slabs[kMaxSlabs];
     __shared__ int n_slabs;
     __shared__ double part[kColourBlock / 64][4];
+    __shared__ LevelRow rows[kMaxLevelsDev];
+    if (threadIdx.x < lt.n_levels) rows[threadIdx.x] = level_row(lt, threadIdx.x);
     const uint32_t q = blockIdx.x;
     const uint32_t t = pal_of_box[q];
     uint32_t lo[3], hi[3];
     const bool nonempty = clip_box(boxes + 6 * uint64_t(q), lt, lo, hi) && t < T;
     if (threadIdx.x == 0) n_slabs = 0;
     __syncthreads();
-    if (nonempty) build_slabs(lt, lo, hi, slabs, &n_slabs);
+    if (nonempty) build_slabs(lt, rows, lo, hi, slabs, &n_slabs, nullptr, nullptr);
     __syncthreads();
     const float4 *pal = palette + uint64_t(t < T ? t : 0) * n_nodes;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -2043,6 +2248,27 @@ __global__ void transpose_level_kernel(const uint32_t *src, uint32_t *dst, uint3
     const uint64_t yz = i / X;
     const uint32_t y = uint32_t(yz % Y), z = uint32_t(yz / Y);
     dst[y + uint64_t(Y) * (z + uint64_t(Z) * x)] = src[i];
+}
+
+// The records of the nodes of rank 1 and 2 from their triples.
+__global__ void leaf_kernel(const NodeTriple *__restrict__ nodes, uint32_t nseg, uint32_t n, Leaf *__restrict__ out)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const NodeTriple t = nodes[nseg + i];
+    Leaf r;
+    r.s[0] = r.s[1] = t.a;
+    r.s[2] = r.s[3] = t.b;
+    r.w = t.w, r.wa = r.wb = 0.0f, r.pad = 0;
+    if (t.a >= nseg) {
+        const NodeTriple u = nodes[t.a];
+        r.s[0] = u.a, r.s[1] = u.b, r.wa = u.w;
+    }
+    if (t.b >= nseg) {
+        const NodeTriple u = nodes[t.b];
+        r.s[2] = u.a, r.s[3] = u.b, r.wb = u.w;
+    }
+    out[i] = r;
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v)
@@ -2222,12 +2448,12 @@ template <int BLOCK, bool BIG, bool SPARSE, bool ERR>
 QueryKernel tier_kernel(uint32_t unroll)
 {
     if constexpr (ERR) {
-        return query_tier_kernel<BLOCK, BIG, 8, SPARSE, true>;  // one unroll for uncertainty queries
-    } else {
+        return query_tier_kernel<BLOCK, BIG, 4, SPARSE, true>;  // one group size for uncertainty queries
+    } else {  // loads in flight per lane: two groups
         switch (unroll) {
-        case 4: return query_tier_kernel<BLOCK, BIG, 4, SPARSE, false>;
-        case 8: return query_tier_kernel<BLOCK, BIG, 8, SPARSE, false>;
-        default: return query_tier_kernel<BLOCK, BIG, 16, SPARSE, false>;
+        case 4: return query_tier_kernel<BLOCK, BIG, 2, SPARSE, false>;
+        case 8: return query_tier_kernel<BLOCK, BIG, 4, SPARSE, false>;
+        default: return query_tier_kernel<BLOCK, BIG, 8, SPARSE, false>;
         }
     }
 }
@@ -2350,8 +2576,67 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
     for (int k = 0; k < 4; ++k) counts[k] = 0;
     std::vector<Slab> slabs(kMaxSlabs);
     std::string where;
-    // Replays every load of a tile walk (all UNROLL loads of every block, consumed or
-    // not) and hands each consumed in-slab unit to unit(t, row, slice, pair bits).
+    // Replays every load of a streamed slab's tiles, one per lane, and hands each in-slab
+    // unit to unit(t, row, slice, pair bits).
+    auto replay_slab = [&](const Slab &sl, uint64_t buf, auto unit) -> bool {
+        const uint64_t extent = uint64_t(sl.e2 - 1) * sl.s2b + uint64_t(sl.e1 - 1) * sl.s1b + 4ull * sl.units;
+        if (sl.base % 4 != 0) {
+            where = "unaligned slab base";
+            return false;
+        }
+        const uint32_t ltx = tile_ltx(sl), ty = 64u >> ltx, n_t0 = (sl.units + (1u << ltx) - 1) >> ltx,
+                       n_rt = (sl.e1 + ty - 1) / ty, tiles = slab_tiles(sl);
+        if (tiles != uint64_t(n_t0) * n_rt * sl.e2) {
+            where = "tile count";
+            return false;
+        }
+        uint64_t seen = 0;
+        for (uint32_t o = 0; o < tiles; ++o) {
+            const TileDesc d = tile_desc(sl, o);
+            const uint32_t t0 = o % n_t0, rt = o / n_t0 % n_rt, k2 = o / n_t0 / n_rt;
+            for (uint32_t lane = 0; lane < 64; ++lane) {
+                uint32_t mask;
+                const uint64_t off = d.off + tile_lane(d.pack, d.s1b, lane, &mask);
+                const uint32_t ly = lane >> ltx;
+                if (ly && ly < tile_rows(d.pack) &&
+                    (d.s1b >= (1u << 24) || uint64_t(ly) * d.s1b + 256u >= (1ull << 32))) {
+                    where = "lane offset is no 24-bit product";
+                    return false;
+                }
+                ++counts[2];
+                if (off < sl.base || off + 4 > sl.base + extent) {
+                    where = "load past the slab";
+                    return false;
+                }
+                if (off + 4 > buf) {
+                    where = "load past the buffer";
+                    return false;
+                }
+                if (mask == kEmpty) continue;  // no part of the unit is inside
+                const uint32_t x = (t0 << ltx) + (lane & ((1u << ltx) - 1)), row = rt * ty + ly;
+                const uint32_t pb = sl.kind ? (mask & 0xFFFFu ? 0u : 1u) | (mask >> 16 ? 0u : 2u) : 1u;
+                if (pb != (sl.kind ? pair_bits(x, sl.e0, sl.odd) : 1u) || (sl.kind == 0 && mask)) {
+                    where = "elements inside the slab";
+                    return false;
+                }
+                if (x >= sl.units || row >= sl.e1 || tile_level(d.pack) != sl.level ||
+                    tile_pairs(d.pack) != (sl.kind == 1) ||
+                    off != sl.base + uint64_t(k2) * sl.s2b + uint64_t(row) * sl.s1b + 4ull * x) {
+                    where = "load is not its unit";
+                    return false;
+                }
+                ++seen;
+                if (!unit(x, row, k2, pb)) return false;
+            }
+        }
+        if (seen != uint64_t(sl.units) * sl.e1 * sl.e2) {
+            where = "units read " + std::to_string(seen) + " of " + std::to_string(uint64_t(sl.units) * sl.e1 * sl.e2);
+            return false;
+        }
+        return true;
+    };
+    // Replays every load of the naive scan's tile walk (all UNROLL loads of every block, consumed
+    // or not) and hands each consumed in-slab unit to unit(t, row, slice, pair bits).
     auto replay = [&](const TileWalk &tw, uint64_t base, uint64_t buf, uint32_t e0, uint32_t odd, bool pairs,
                       auto unit) -> bool {
         const uint64_t extent = uint64_t(tw.e2 - 1) * tw.s2b + uint64_t(tw.e1 - 1) * tw.s1b + 4ull * tw.units;
@@ -2413,13 +2698,9 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
         int ns = 0;
         uint64_t cubes_closed = 0;
         for (uint32_t l = 0; l < lt.n_levels; ++l) {
-            const int k = level_slabs<false>(lt, lo, hi, l, nullptr);
-            if (k > 6) {  // the LDS slab table holds 6 per level
-                *err = "box " + std::to_string(q) + ": more than 6 slabs at one level";
-                return MG_ELIMIT;
-            }
-            level_slabs<true>(lt, lo, hi, l, slabs.data() + ns);
-            ns += k;
+            const LevelRow row = level_row(lt, l);
+            for (uint32_t face = 0; face < 6; ++face)
+                if (face_slab(lt, row, lo, hi, l, face, &slabs[ns])) ++ns;
             uint64_t outer = 1, inner = 1;
             for (int d = 0; d < 3; ++d) {
                 const uint64_t one = uint64_t(1) << l;
@@ -2440,13 +2721,15 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
                 const uint64_t len = lt.dims[L][f], rows = f == 0 ? uint64_t(lt.dims[L][1]) * lt.dims[L][2]
                                                                  : uint64_t(lt.dims[L][2]) * lt.dims[L][0];
                 const uint64_t chunks = (len + kRunSkipCells - 1) / kRunSkipCells;
-                const uint64_t items = (uint64_t(sl.e1) * sl.e2) << lseg;
-                if (f > 1 || items >= (1ull << 32)) where = "run slab orientation or size";
+                const uint64_t items = slab_items(sl);
+                if (f > 1 || items != (uint64_t(sl.e1) * sl.e2) << lseg) where = "run slab orientation or size";
                 for (uint64_t it = 0; where.empty() && it < items; ++it) {
                     uint32_t r, p0, p1;
-                    if (!run_item(sl, lt, f, lseg, uint32_t(it), &r, &p0, &p1)) continue;
+                    if (!run_item(sl, lt.dims[L][1], lt.dims[L][2], f, lseg, uint32_t(it), &r, &p0, &p1)) continue;
                     ++counts[2];
-                    if (r >= rows || uint64_t(r) * chunks + p0 / kRunSkipCells >= rows * chunks || p1 > len) {
+                    uint64_t c0, c1;
+                    const bool last = run_skips(uint32_t(rows), uint32_t(chunks), r, p0, p1, &c0, &c1);
+                    if (r >= rows || c0 >= rows * chunks || (!last && c1 >= rows * chunks) || p1 > len || p1 >= 65536) {
                         where = "run row or skip entry out of range";
                         break;
                     }
@@ -2474,7 +2757,6 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
                 }
                 continue;
             }
-            const TileWalk tw = tile_walk(sl.units, sl.e1, sl.e2, sl.s1b, sl.s2b, unroll);
             const bool tr = (sl.axes & 3) == 1;
             const uint32_t X = lt.dims[L][0], Y = lt.dims[L][1], Z = lt.dims[L][2];
             auto unit = [&](uint32_t x, uint32_t row, uint32_t k2, uint32_t pb) -> bool {
@@ -2504,7 +2786,7 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
                 }
                 return true;
             };
-            if (!replay(tw, sl.base, sl.kind ? bytes16 : bytes32, sl.e0, sl.odd, sl.kind != 0, unit)) {
+            if (!replay_slab(sl, sl.kind ? bytes16 : bytes32, unit)) {
                 *err = "box " + std::to_string(q) + " level " + std::to_string(L) + " slab " + std::to_string(sl.e0) +
                        "x" + std::to_string(sl.e1) + " kind " + std::to_string(sl.kind) + ": " + where;
                 return MG_ELIMIT;
@@ -2559,12 +2841,16 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
 // Byte offsets of the graph's device arrays inside one buffer (each 256-byte
 // aligned): what mg_device_bytes sizes and mg_bind_device fills.
 struct DeviceLayout {
-    uint64_t nodes, sched, rank_ptr, mixlen, maps, maps16;
+    uint64_t nodes, leaf, sched, rank_ptr, mixlen, maps, maps16;
     uint64_t n16, n16t;   // elements of the two 16-bit level-0 copies (0 if none)
     uint64_t run_table;   // RunLevel [2 n_levels]
     std::vector<uint64_t> run_sk, run_rn;  // per level and orientation: skip, runs
     uint64_t bytes;
 };
+
+// The nodes of rank 1 and 2 are IDs [nseg, rank1_end) and [rank1_end, rank2_end).
+uint32_t rank1_end(const Graph &g) { return g.depth >= 1 ? g.rank_ptr[2] : g.nseg; }
+uint32_t rank2_end(const Graph &g) { return g.depth >= 2 ? g.rank_ptr[3] : rank1_end(g); }
 
 DeviceLayout device_layout(const Graph &g)
 {
@@ -2577,6 +2863,7 @@ DeviceLayout device_layout(const Graph &g)
     };
     const uint64_t nmap = g.lev_off[g.n_levels];
     L.nodes = take(uint64_t(g.n_nodes) * sizeof(NodeTriple));
+    L.leaf = take(uint64_t(rank2_end(g) - g.nseg) * sizeof(Leaf));
     L.sched = take(uint64_t(g.n_nodes) * sizeof(SchedNode));
     L.rank_ptr = take(g.rank_ptr.size() * 4);
     L.mixlen = take(uint64_t(g.n_nodes) * 4);
@@ -2715,6 +3002,7 @@ int dev_bind(Graph *g, int device, void *base, uint64_t bytes, hipStream_t s, bo
     d.device = device;
     d.bytes = L.bytes;
     d.nodes = reinterpret_cast<NodeTriple *>(b + L.nodes);
+    d.leaf = b + L.leaf;
     d.sched = reinterpret_cast<SchedNode *>(b + L.sched);
     d.rank_ptr = reinterpret_cast<uint32_t *>(b + L.rank_ptr);
     d.mixlen = reinterpret_cast<uint32_t *>(b + L.mixlen);
@@ -2722,6 +3010,11 @@ int dev_bind(Graph *g, int device, void *base, uint64_t bytes, hipStream_t s, bo
     d.maps_t = d.maps + nmap;
     d.maps16 = L.n16 ? reinterpret_cast<uint16_t *>(b + L.maps16) : nullptr;
     HIP_TRY(hipMemcpyAsync(d.nodes, nodes.data(), nodes.size() * sizeof(NodeTriple), hipMemcpyHostToDevice, s));
+    if (const uint32_t n_leaf = rank2_end(*g) - g->nseg) {
+        hipLaunchKernelGGL(leaf_kernel, dim3((n_leaf + 255) / 256), dim3(256), 0, s, d.nodes, g->nseg, n_leaf,
+                           static_cast<Leaf *>(d.leaf));
+        HIP_TRY(hipGetLastError());
+    }
     HIP_TRY(hipMemcpyAsync(d.sched, sched.data(), sched.size() * sizeof(SchedNode), hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d.rank_ptr, g->rank_ptr.data(), g->rank_ptr.size() * 4, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d.mixlen, mixlen.data(), mixlen.size() * 4, hipMemcpyHostToDevice, s));
@@ -2748,14 +3041,22 @@ int dev_bind(Graph *g, int device, void *base, uint64_t bytes, hipStream_t s, bo
     // row runs and their table
     std::vector<RunLevel> table(2 * size_t(g->n_levels));
     d.runs_mask = 0;
+    d.runs = nullptr;
     for (size_t k = 0; k < g->runs.size() && k < table.size(); ++k) {
         const LevelRuns &r = g->runs[k];
         RunLevel &t = table[k];
-        t = RunLevel{nullptr, nullptr, 0, 0, 0};
+        t = RunLevel{nullptr, nullptr, 0, 0, 0, 0};
         if (!r.rows || r.runs.empty()) continue;
         t.skip = reinterpret_cast<const uint32_t *>(b + L.run_sk[k]);
         t.runs = reinterpret_cast<const uint64_t *>(b + L.run_rn[k]);
         t.rows = r.rows, t.chunks = r.chunks, t.n_runs = uint32_t(r.runs.size());
+        // runs are read by their 32-bit index from the first array (levels past that keep none)
+        if (!d.runs) d.runs = t.runs;
+        if (uint64_t(t.runs - d.runs) + t.n_runs > 0xFFFFFFFFull) {
+            t = RunLevel{nullptr, nullptr, 0, 0, 0, 0};
+            continue;
+        }
+        t.first = uint32_t(t.runs - d.runs);
         HIP_TRY(hipMemcpyAsync(b + L.run_sk[k], r.skip.data(), r.skip.size() * 4, hipMemcpyHostToDevice, s));
         HIP_TRY(hipMemcpyAsync(b + L.run_rn[k], r.runs.data(), r.runs.size() * 8, hipMemcpyHostToDevice, s));
         if (k < 32) d.runs_mask |= 1u << k;
@@ -3040,7 +3341,7 @@ int launch_query(Graph *g, QueryArgs &A, const Workspace &w, const LevelTable &l
         HIP_TRY(hipGetLastError());
     }
     // boxes whose table overflowed: once more with a larger LDS table, then in global memory
-    const QueryKernel kretry = query_retry_kernel<kBlockBig, 8, SPARSE, ERR>;
+    const QueryKernel kretry = query_retry_kernel<kBlockBig, 4, SPARSE, ERR>;
     uint32_t cap_retry = d.cfg.table_retry;
     if (!cap_retry) {  // the largest table up to kHashRetry that fits the LDS of a workgroup
         uint32_t stat = 0;
@@ -3064,7 +3365,7 @@ int launch_query(Graph *g, QueryArgs &A, const Workspace &w, const LevelTable &l
     // mid-size tables (overflow: list 3), then the few whose tables hold the whole graph
     A.stats_tag = 0x80000000u;
     const QueryKernel kfallback = query_fallback_kernel<ERR>;
-    const uint32_t dyn_fb = 6u * L * uint32_t(sizeof(Slab));
+    const uint32_t dyn_fb = lds_slab_bytes(L);
     auto use_pool = [&](const GlobalPool &p) {
         A.g_slots = p.slots;
         A.g_keys = p.keys, A.g_cnt = p.cnt, A.g_used = p.used, A.g_hi = p.hi, A.g_lo = p.lo;
@@ -3154,8 +3455,10 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     A.maps16 = g->dev.maps16;
     A.gv.nodes = g->dev.nodes;
     A.gv.nseg = g->nseg;
-    A.gv.r1_end = g->depth >= 1 ? g->rank_ptr[2] : g->nseg;
-    A.gv.r2_end = g->depth >= 2 ? g->rank_ptr[3] : A.gv.r1_end;
+    A.gv.leaf = reinterpret_cast<const Leaf *>(g->dev.leaf);
+    A.gv.runs = g->dev.runs;
+    A.gv.r1_end = rank1_end(*g);
+    A.gv.r2_end = rank2_end(*g);
     A.rank_ptr = g->dev.rank_ptr;
     A.depth = g->depth;
     A.n = n;

@@ -32,6 +32,7 @@ struct DeviceState {
     void *base = nullptr;          // the one buffer holding every array below (except the table)
     bool owned = false;            // base was allocated by mg_upload (else bound by the caller)
     NodeTriple *nodes = nullptr;   // [n_nodes]
+    void *leaf = nullptr;          // records of the nodes of rank 1 and 2 (Leaf)
     uint32_t *mixlen = nullptr;    // [n_nodes] bound on the sources in each node's mixture
     uint32_t *rank_ptr = nullptr;  // [depth + 2]
     SchedNode *sched = nullptr;    // [n_nodes] in step order
@@ -39,6 +40,7 @@ struct DeviceState {
     uint32_t *maps_t = nullptr;    // all levels, y fastest then z then x
     uint16_t *maps16 = nullptr;    // level 0 as 16-bit IDs, both orientations (rows padded to even)
     void *run_table = nullptr;     // row runs per level and orientation (RunLevel [2 n_levels])
+    const uint64_t *runs = nullptr;  // the first run of the first level that has them
     uint32_t runs_mask = 0;        // bit 2 l + o: level l has runs along x (o = 0) / y (o = 1)
     uint64_t *lut_ptr = nullptr;   // [n_nodes + 1] mixture lookup table rows (optional)
     uint32_t *lut_seg = nullptr;   // [lut nnz]
@@ -62,9 +64,9 @@ struct DeviceState {
 
 // Runs of equal node IDs along the rows of one level in one orientation
 // (runs.cpp): row_ptr[rows + 1] into runs, runs[j] = (exclusive end along the
-// row) << 32 | node, skip[rows][chunks] = index of the run holding cell 64 c of
-// row r. Empty (rows == 0) where the level keeps no runs.
-constexpr uint32_t kRunSkipCells = 64;  // cells of a row per skip entry
+// row) << 32 | node, skip[rows][chunks] = index of the run holding cell
+// kRunSkipCells c of row r. Empty (rows == 0) where the level keeps no runs.
+constexpr uint32_t kRunSkipCells = 16;  // cells of a row per skip entry
 struct LevelRuns {
     uint32_t rows = 0, len = 0, chunks = 0;
     std::vector<uint32_t> row_ptr;

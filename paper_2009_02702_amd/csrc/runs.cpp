@@ -12,9 +12,10 @@
 // Per level and orientation: row_ptr[r] = first run of row r (row_ptr[rows] =
 // runs), runs[j] = (end << 32) | node with `end` the exclusive end of run j
 // along the row, and skip[r * chunks + c] = index of the run that holds cell
-// 64 c of row r (a segment starting at cell f begins its walk at most 63 cells
-// before f; the row's last run ends at the row's end, so a walk that stops at
-// the segment's end never leaves the row). Built only where the runs are at
+// kRunSkipCells c of row r: the runs of a segment lie between the entries of its
+// first cell's chunk and of the chunk after its last cell's. 16 cells per entry
+// bound a short row's runs closely (with 64, rows of 20 cells met three times the
+// runs that cross them: 1.61 ms per 100,000 boxes of a 512^3 volume, 1.53 with 16). Built only where the runs are at
 // most a quarter of the level's cells (long runs).
 #include <algorithm>
 #include <thread>
