@@ -180,7 +180,8 @@ int mg_upload(mg_graph *g, int device);
 /* Bytes of device workspace that query calls of up to `max_boxes` boxes need. */
 int mg_workspace_bytes(const mg_graph *g, uint32_t max_boxes, uint64_t *bytes);
 
-/* Prepare a workspace once after allocating it (enqueued on `stream`). */
+/* Prepare a workspace once after allocating it (enqueued on `stream`): clears the counters,
+ * queues and tables that every query expects clean and leaves clean. */
 int mg_workspace_init(mg_graph *g, void *d_work, uint64_t work_bytes, void *stream);
 
 /* Box histograms, the batched path (Sec. "Fast Sub-Volume Queries"; the
@@ -368,7 +369,9 @@ int mg_query_boxes_err(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float *
 /* Launch configuration of the GPU kernels (per graph, after mg_upload).
  * Defaults: 16, 8, 16, 256, then zeros (sizes chosen per mode). */
 typedef struct {
-    uint32_t unroll_big;    /* node-ID loads in flight per lane, boxes of >= 2^14 cubes: 4, 8 or 16 */
+    uint32_t unroll_big;    /* node-ID loads in flight per lane, boxes of >= 2^14 cubes: 4, 8 or 16.
+                               (Batches of at most 1,024 boxes take one launch that uses only
+                               table_big and table_retry.)                                    */
     uint32_t unroll_small;  /* the same for smaller boxes: 4, 8 or 16 */
     uint32_t unroll_naive;  /* level-0 loads in flight per lane of the naive scan: 4, 8 or 16 */
     uint32_t tf_block;      /* threads per workgroup of the propagation kernel: 64, 128, 256, 512, 1024 */

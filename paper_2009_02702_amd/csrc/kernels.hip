@@ -51,6 +51,7 @@ constexpr uint32_t kBigLog2 = 14;             // boxes of >= 2^14 cubes go to th
 constexpr uint32_t kHashGlobal = 1u << 16;    // fewest per-worker hash slots in the fallback tables
 constexpr uint32_t kSegLdsMax = 2048;         // sources kept in LDS
 constexpr uint32_t kFallbackWorkers = 128;    // workers of the final global-table launch (budget)
+constexpr uint32_t kLeastItems = 8;            // row segments worth a wave's while
 constexpr uint32_t kRunSeg = 256;             // cells of a row one thread sums from the runs
 constexpr uint32_t kRunMinRow = 16;           // rows shorter than this stream cube by cube (default)
 constexpr uint32_t kTfPlanes = 4;             // transfer functions per thread of a propagation step
@@ -58,6 +59,19 @@ constexpr uint32_t kTfTailPairs = 4096;        // steps of at most this many nod
 constexpr uint32_t kTfTailSteps = 16;          // at most this many of them
 constexpr uint32_t kTfTailBlock = 1024;        // threads of that launch (one workgroup)
 constexpr uint32_t kMidWorkers = 256;         // workers of the mid-size global-table launch
+constexpr uint32_t kMaxSlots = 1024;           // boxes of one call that several workgroups may share
+constexpr uint64_t kSlotBytes = 32ull << 20;  // their accumulators take at most this much of a workspace
+constexpr uint32_t kMinSlots = 16;            // (but hold at least this many boxes)
+// Fewest cubes worth a workgroup of their own: when others idle (one box of 205,000 cubes of a
+// 400x375x263 volume in parts of 2,048 / 4,096 / 8,192 / 16,384 / 32,768: 36 / 36 / 40 / 46 / 55 us,
+// whole: 105), and in a large batch (5,000 boxes of 199x181x163, parts of 16,384 / 32,768 /
+// 65,536 / 131,072: 254 / 174 / 126 / 135 us, whole: 160).
+constexpr uint32_t kMinPart = 4096;
+constexpr uint32_t kMinPartBatch = 1u << 16;
+constexpr uint32_t kDirectMax = 1024;         // boxes of a call answered without a planning launch
+constexpr uint32_t kNoallocSlots = 256;        // the same on the library's static scratch
+constexpr int kBlockDirect = 256;             // workgroup size of that path
+constexpr uint32_t kHashDirect = 1024;        // its LDS hash slots (per-source arrays in LDS)
 constexpr uint32_t kQueues = 8;                // work queues per tier
 constexpr uint32_t kQueueStride = 64;          // u32 between queue counters (256 bytes)
 constexpr int kGroup = 4;                      // tiles per load group (plain, fallback)
@@ -1223,16 +1237,22 @@ __device__ __attribute__((always_inline)) inline void scatter_box(const char *ma
     __shared__ uint16_t dq_code[kWaves * (SPARSE ? 1u : kDeferSlots)];
     const uint32_t wave = uni(threadIdx.x >> 6);
     DeferRing dq{dq_node, dq_code, wave * kDeferSlots, 0u, 0u};
-    const uint32_t waves = parts * kWaves, w = part * kWaves + wave;
+    // The part's range first, then the wave's range of it: a part is the same work whatever
+    // the size of the workgroup that answers it.
+    auto range = [&](uint32_t n, uint32_t least, uint32_t p, uint32_t of, uint32_t *a, uint32_t *b) {
+        const uint32_t per = max(least, (n + of - 1) / of);
+        *a = min(n, p * per), *b = min(n, *a + per);
+    };
     const uint32_t tiles = uni(st.tile0[n_slabs]), items = uni(st.item0[n_slabs]);
-    if (tiles) {
-        const uint32_t per = (tiles + waves - 1) / waves, a = w * per;
-        if (a < tiles) stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, a, min(a + per, tiles), dq, flags_lds);
+    uint32_t t0 = 0, t1 = tiles, i0 = 0, i1 = items, a, b;
+    if (parts > 1) {
+        range(tiles, 1, part, parts, &t0, &t1);
+        range(items, kLeastItems, parts - 1 - part, parts, &i0, &i1);  // from the end that got the fewer tiles
     }
-    if (items) {  // from the other end of the waves, which got the fewer tiles
-        const uint32_t per = ((items + 63) / 64 + waves - 1) / waves * 64, a = (waves - 1 - w) * per;
-        if (a < items) sum_runs<SPARSE>(runs, rows, st, gv, n_slabs, a, min(a + per, items), dq, flags_lds);
-    }
+    range(t1 - t0, 1, wave, kWaves, &a, &b);
+    if (a < b) stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, t0 + a, t0 + b, dq, flags_lds);
+    range(i1 - i0, kLeastItems, kWaves - 1 - wave, kWaves, &a, &b);
+    if (a < b) sum_runs<SPARSE>(runs, rows, st, gv, n_slabs, i0 + a, i0 + b, dq, flags_lds);
     if (!SPARSE && dq.tail != dq.head) ring_resolve<SPARSE>(dq, st, gv, dq.tail - dq.head);
 }
 
@@ -1268,6 +1288,15 @@ __device__ inline void push_mass(const QueryState &st, const GraphView &gv, cons
     }
 }
 
+// Per-worker tables in global memory: node table and per-source arrays.
+struct GlobalPool {
+    uint32_t workers, slots;
+    uint32_t *keys, *cnt, *used;
+    float *hi, *lo;
+    uint32_t *seg_cnt;
+    float *seg_hi, *seg_lo, *seg_var;
+};
+
 struct QueryArgs {
     LevelTable lt;
     const uint32_t *boxes;
@@ -1284,35 +1313,47 @@ struct QueryArgs {
     const uint32_t *rank_ptr;     // [depth + 2]
     uint32_t depth;
     uint32_t n;
-    const uint32_t *order;        // query order (batched) or nullptr (identity)
-    uint32_t *counters;           // [0] next big-tier box, [1] boxes in list 1, [2] next box of the
-                                  // final global tables, [3] next small-tier box, [4] next retry
-                                  // box, [5] boxes in list 2, [6] boxes in list 3, [7] next box of
-                                  // the mid-size global tables, [8] number of big-tier boxes
+    const uint32_t *order;        // query order (batched; kEmpty: a box whose parts are in `split`)
+    uint32_t *counters;           // kCount* below
     uint32_t table_cap;           // LDS hash slots of this launch
     uint32_t chunk;               // small tier: boxes per dequeue (0: automatic)
-    uint32_t g_slots;             // hash slots of each fallback worker's global table
     uint32_t *queues;             // tier work queues: counter of queue j at [j * kQueueStride]
-    uint32_t *overflow;           // list 1: boxes whose tier table overflowed
-    uint32_t *overflow2;          // list 2: boxes whose retry table overflowed too
-    const uint32_t *g_list;       // global-table launches: the boxes they answer,
-    uint32_t g_count_idx;         // counters[] entry holding how many,
-    uint32_t g_next_idx;          // and the one they dequeue with
-    uint32_t *ovf_out;            // where this launch reports overflowed boxes (nullptr: mark NaN)
-    uint32_t ovf_out_idx;         // counters[] entry that counts them
-    uint32_t stats_tag;           // OR-ed into stats[q][1]: which launch answered the box
+    uint32_t *buckets;            // box counts by size, for the order
+    uint32_t *overflow;           // list 1: boxes (and parts) whose LDS table overflowed
+    uint32_t *overflow2;          // list 2: those no LDS table holds
+    uint32_t *overflow3;          // list 3: those the mid-size global tables do not hold either
+    // boxes that several workgroups share: their parts, and per box the sources' sums so far
+    uint32_t n_slots;             // boxes there is room for (0: every box is one workgroup's)
+    uint4 *split;                 // [2 n_slots] parts (box, part, parts, slot) of a planned call
+    uint4 *split_over;            // [2 n_slots] parts in list 1 (entry: kPartFlag | index here)
+    uint32_t *slot_done;          // [n_slots] parts finished
+    uint32_t *slot_cnt;           // [n_slots][S] exact integer counts
+    float *slot_hi, *slot_lo;     // [n_slots][S] mass and its compensation
     uint32_t *stats;              // optional [n][2]: cubes, table entries (graph nodes) touched
     const uint64_t *lut_ptr;      // mixture lookup table rows: expand instead of push (nullptr: push)
     const uint32_t *lut_seg;
     const float *lut_val;
     const float *lut_err;         // propagated uncertainty of each row entry (uncertainty queries)
     float *out_err;               // [n][S] uncertainty of each fraction, or null (dense output only)
-    // fallback global regions (per worker)
-    uint32_t *g_keys, *g_cnt, *g_used;
-    float *g_hi, *g_lo;
-    uint32_t *g_seg_cnt;
-    float *g_seg_hi, *g_seg_lo, *g_seg_var;
 };
+
+// Counters of a workspace. Every call leaves all of them (and the queues, buckets and slots)
+// zero, so no call needs a launch to clear them.
+enum : uint32_t {
+    kCountOver = 1,     // entries of list 1
+    kCountOver2 = 2,    // entries of list 2
+    kCountOver3 = 3,    // entries of list 3
+    kCountRetry = 4,    // next entry of list 1
+    kCountNext2 = 5,    // next entry of list 2
+    kCountNext3 = 6,    // next entry of list 3
+    kCountBig = 8,      // boxes of the big tier
+    kCountExit = 9,     // workgroups of the last launch that are done
+    kCountSplit = 10,   // parts in `split`
+    kCountSlot = 11,    // slots taken
+    kCountSplitOver = 12,  // parts in `split_over`
+    kCountTotal = 14,   // cubes of all boxes (64 bits)
+};
+constexpr uint32_t kPartFlag = 0x80000000u;
 
 // Mixture lookup expansion (the paper's query through per-node mixtures):
 // every graph node in the table adds its mass times its mixture row to the
@@ -1370,6 +1411,7 @@ struct QueryShared {
     uint32_t flags;
     uint32_t max_key;
     uint32_t q;
+    uint32_t last;   // this workgroup finished its box's last part
     uint32_t nnz;    // sparse output: entries of this box
     uint32_t base;   // sparse output: first entry of this box
 };
@@ -1480,14 +1522,61 @@ __device__ inline void write_failure(const QueryArgs &A, uint32_t q)
     }
 }
 
+// One box (parts == 1) or one part of a box that several workgroups share.
+struct Item {
+    uint32_t q, part, parts, slot;
+};
+
+__device__ inline Item whole_box(uint32_t q) { return Item{q, 0u, 1u, 0u}; }
+__device__ inline Item part_of(const uint4 &p) { return Item{p.x, p.y, p.z, p.w}; }
+
+// The item of a list-1 (or list-2) entry.
+__device__ inline Item listed_item(const QueryArgs &A, uint32_t e)
+{
+    if (A.n_slots && (e & kPartFlag)) return part_of(A.split_over[e & ~kPartFlag]);
+    return whole_box(e);
+}
+
+// Adds the sources of this workgroup's part to its box's sums. Returns true in the workgroup
+// that finished the box's last part: its sums are then complete. Every thread must call.
+template <int BLOCK, bool SPARSE>
+__device__ inline bool merge_part(const QueryArgs &A, QueryShared &sh, const QueryState &st, const Item &it)
+{
+    const uint64_t at = uint64_t(it.slot) * A.gv.nseg;
+    auto add = [&](uint32_t s, uint32_t c, float h, float l) {
+        if (c) atomicAdd(&A.slot_cnt[at + s], c);
+        if ((__float_as_uint(h) | __float_as_uint(l)) != 0u) add_mass_at(&A.slot_hi[at + s], &A.slot_lo[at + s], h, l);
+    };
+    if (SPARSE) {
+        const uint32_t nu = min(sh.n_used, st.cap);
+        for (uint32_t i = threadIdx.x; i < nu; i += BLOCK) {
+            const uint32_t slot = ld(&st.used[i]), key = ld(&st.keys[slot]);
+            if (key < A.gv.nseg) add(key, ld(&st.cnt[slot]), ld(&st.hi[slot]), ld(&st.lo[slot]));
+        }
+    } else {
+        for (uint32_t s = threadIdx.x; s < A.gv.nseg; s += BLOCK)
+            add(s, ld(&st.seg_cnt[s]), ld(&st.seg_hi[s]), ld(&st.seg_lo[s]));
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) sh.last = atomicAdd(&A.slot_done[it.slot], 1u) + 1u == it.parts;
+    __syncthreads();
+    if (!uni(sh.last)) return false;
+    __threadfence();
+    return true;
+}
+
 // One query, by the whole block. `st` must be clean (keys empty, values 0).
 // ERR: lookup-table expansion that also accumulates uncertainties (dense output).
+// tag: OR-ed into the box's stats (which launch answered it). Returns true where the table
+// overflowed: nothing was written then, or, with `fail`, the box is marked as failed.
 // (always inlined: each query kernel is one function, whatever the inliner's size limit)
 template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
-__device__ __attribute__((always_inline)) inline void run_query(const QueryArgs &A, QueryShared &sh,
-                                                                const QueryState &st, uint32_t q,
-                                                                bool report_overflow)
+__device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs &A, QueryShared &sh,
+                                                                const QueryState &st, const Item it, bool fail,
+                                                                uint32_t tag)
 {
+    const uint32_t q = uni(it.q);
     uint32_t lo[3], hi[3];
     const bool nonempty = clip_box(A.boxes + 6 * uint64_t(q), A.lt, lo, hi);
     if (threadIdx.x == 0) {
@@ -1503,32 +1592,36 @@ __device__ __attribute__((always_inline)) inline void run_query(const QueryArgs 
     if (n_slabs)
         scatter_box<BLOCK, GROUP, SPARSE>(reinterpret_cast<const char *>(A.maps),
                                           reinterpret_cast<const char *>(A.maps16), sh.runs, sh.rows, st, A.gv,
-                                          n_slabs, 0u, 1u, &sh.flags);
+                                          n_slabs, uni(it.part), uni(it.parts), &sh.flags);
     __syncthreads();
     if (ERR || A.lut_ptr)
         expand_lut<BLOCK, SPARSE, ERR>(A, st);
     else
         push_mass<BLOCK, SPARSE>(st, A.gv, sh.rank_ptr, A.depth);
     __syncthreads();
-    const bool overflow = (sh.flags & 1u) != 0;
-    if (A.stats && threadIdx.x == 0 && (!overflow || !report_overflow)) {
+    const bool overflow = (uni(sh.flags) & 1u) != 0;
+    if (A.stats && threadIdx.x == 0 && (!overflow || fail)) {
         uint32_t cubes = 0;
         for (int i = 0; i < sh.n_slabs; ++i) cubes += slab_count(st.slabs[i]);
         A.stats[2 * uint64_t(q)] = cubes;
-        // bit 30: answered by the retry launch, bit 31: by the global-table fallback
-        A.stats[2 * uint64_t(q) + 1] = sh.n_used | A.stats_tag;
+        // bit 30: answered by the retry launch, bit 31: by a global-memory one
+        A.stats[2 * uint64_t(q) + 1] = sh.n_used | tag;
     }
     const uint32_t nseg = A.gv.nseg;
-    if (!overflow) {
-        const double vol = nonempty ? double(hi[0] - lo[0]) * double(hi[1] - lo[1]) * double(hi[2] - lo[2]) : 0.0;
+    const double vol = nonempty ? double(hi[0] - lo[0]) * double(hi[1] - lo[1]) * double(hi[2] - lo[2]) : 0.0;
+    if (overflow) {
+        if (fail) write_failure<BLOCK>(A, q);  // even a table for the whole graph overflowed
+    } else if (uni(it.parts) == 1) {
         write_result<BLOCK, SPARSE, ERR>(A, sh, st, q, nonempty, vol);
-    } else if (report_overflow) {
-        if (threadIdx.x == 0) {
-            const uint32_t k = atomicAdd(&A.counters[A.ovf_out_idx], 1u);
-            A.ovf_out[k] = q;
-        }
-    } else {
-        write_failure<BLOCK>(A, q);  // even the per-worker global table overflowed
+    } else if (!ERR && merge_part<BLOCK, SPARSE>(A, sh, st, it)) {
+        QueryState all = st;  // the box's sums, and zeros for the next call
+        const uint64_t at = uint64_t(it.slot) * nseg;
+        all.seg_cnt = A.slot_cnt + at, all.seg_hi = A.slot_hi + at, all.seg_lo = A.slot_lo + at;
+        write_result<BLOCK, false, false>(A, sh, all, q, nonempty, vol);
+        __syncthreads();
+        for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK)
+            all.seg_cnt[s] = 0, all.seg_hi[s] = 0.f, all.seg_lo[s] = 0.f;
+        if (threadIdx.x == 0) A.slot_done[it.slot] = 0;
     }
     __syncthreads();
     // restore a clean state for the next query
@@ -1548,15 +1641,51 @@ __device__ __attribute__((always_inline)) inline void run_query(const QueryArgs 
             if (ERR) st.seg_var[s] = 0.f;
         }
     __syncthreads();
+    return overflow;
 }
 
-template <int BLOCK>
-__device__ inline void load_graph_tables(const QueryArgs &A, QueryShared &sh)
+// Hands an item whose table overflowed to the retry launch (list 1). Any thread, once.
+__device__ inline void report_overflow(const QueryArgs &A, const Item &it)
 {
-    for (uint32_t i = threadIdx.x; i < A.depth + 2; i += BLOCK) sh.rank_ptr[i] = A.rank_ptr[i];
-    for (uint32_t i = threadIdx.x; i < A.lt.n_levels; i += BLOCK) sh.rows[i] = level_row(A.lt, i);
-    for (uint32_t i = threadIdx.x; i < 2 * A.lt.n_levels; i += BLOCK) sh.runs[i] = A.runs[i];
+    uint32_t e = it.q;
+    if (it.parts > 1) {
+        const uint32_t k = atomicAdd(&A.counters[kCountSplitOver], 1u);
+        A.split_over[k] = make_uint4(it.q, it.part, it.parts, it.slot);
+        e = kPartFlag | k;
+    }
+    A.overflow[atomicAdd(&A.counters[kCountOver], 1u)] = e;
 }
+
+template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
+__device__ __attribute__((always_inline)) inline void answer(const QueryArgs &A, QueryShared &sh,
+                                                             const QueryState &st, const Item it)
+{
+    if (run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it, false, 0u) && threadIdx.x == 0) report_overflow(A, it);
+}
+
+// The graph's tables every query reads, copied to LDS. The loads are issued together and ahead
+// of other set-up work; put() stores them.
+struct GraphTables {
+    static_assert(kMaxSteps + 2 <= 128 && 2 * kMaxLevelsDev <= 128, "one entry per thread of any workgroup");
+    uint32_t rank_ptr = 0;
+    LevelRow row;
+    RunLevel run;
+
+    __device__ explicit GraphTables(const QueryArgs &A)
+    {
+        const uint32_t i = threadIdx.x;
+        if (i < A.depth + 2) rank_ptr = A.rank_ptr[i];
+        if (i < 2 * A.lt.n_levels) run = A.runs[i];
+        if (i < A.lt.n_levels) row = level_row(A.lt, i);
+    }
+    __device__ void put(const QueryArgs &A, QueryShared &sh) const
+    {
+        const uint32_t i = threadIdx.x;
+        if (i < A.depth + 2) sh.rank_ptr[i] = rank_ptr;
+        if (i < 2 * A.lt.n_levels) sh.runs[i] = run;
+        if (i < A.lt.n_levels) sh.rows[i] = row;
+    }
+};
 
 // The slab list and its prefix arrays at `p` (LDS, lds_slab_bytes).
 __device__ inline void place_slabs(QueryState &st, char *p, uint32_t n_levels)
@@ -1623,14 +1752,115 @@ __global__ __launch_bounds__(kBlock) void query_plain_kernel(QueryArgs A)
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
     const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, false);
-    load_graph_tables<kBlock>(A, sh);
+    GraphTables(A).put(A, sh);
     clear_lds_state<kBlock, SPARSE, false>(st, A.gv.nseg);
     __syncthreads();
-    run_query<kBlock, kGroup, SPARSE, false>(A, sh, st, blockIdx.x, A.ovf_out != nullptr);
+    answer<kBlock, kGroup, SPARSE, false>(A, sh, st, whole_box(blockIdx.x));
+}
+
+// Cubes of a box's footprint, level by level in closed form (below 2^31, the volume's voxels).
+__device__ inline uint32_t box_cubes(const LevelTable &lt, const uint32_t *box)
+{
+    uint32_t lo[3], hi[3], cubes = 0;
+    if (!clip_box(box, lt, lo, hi)) return 0;
+    for (uint32_t l = 0; l < lt.n_levels; ++l) {
+        uint32_t outer = 1, inner = 1;
+        for (int d = 0; d < 3; ++d) {
+            const uint32_t one = 1u << l;  // extents are at most 2^15: no sum leaves 32 bits
+            const uint32_t a = (lo[d] + one - 1) >> l, b = hi[d] >> l;
+            const uint32_t pa = (lo[d] + 2 * one - 1) >> (l + 1), pb = hi[d] >> (l + 1);
+            outer *= b > a ? b - a : 0u;
+            inner *= pb > pa ? 2 * (pb - pa) : 0u;
+        }
+        if (outer == 0) break;  // nothing at coarser levels either
+        cubes += outer - inner;
+    }
+    return cubes;
+}
+
+// Cubes above which a box is split, and the parts it is split into (about that many cubes
+// each): the share of one of `ways` workgroups in all boxes' cubes, so that no workgroup
+// works much longer than the others, but at least `least`. At most `ways` boxes exceed their
+// share, in at most 2 `ways` parts.
+__device__ inline uint32_t part_cubes(uint64_t total, uint32_t ways, uint32_t least)
+{
+    if (ways == 0) return 0xFFFFFFFFu;
+    return uint32_t(max(uint64_t(least), min(total / ways + 1, uint64_t(0xFFFFFFFFu))));
+}
+__device__ inline uint32_t parts_of(uint32_t cubes, uint32_t target)
+{
+    return cubes > target ? (cubes + target - 1) / target : 1u;
+}
+
+// Calls of at most kDirectMax boxes, in one launch: every workgroup counts the cubes of all
+// boxes (a few per thread, closed form), so each knows the parts of every box without a
+// planning launch, and takes items blockIdx, blockIdx + gridDim, ... of the boxes' parts in
+// order. A box's part count does not depend on the workgroup, so all agree. The slot of a
+// shared box is its rank among the shared ones.
+template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
+__global__ __launch_bounds__(BLOCK, 6) void query_direct_kernel(QueryArgs A, uint32_t ways, uint32_t least)
+{
+    extern __shared__ __align__(16) char dyn[];
+    __shared__ QueryShared sh;
+    __shared__ uint32_t first[kDirectMax + 1];  // items before box q | shared boxes before it << 16
+    __shared__ uint64_t wave_sum[BLOCK / 64];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const GraphTables tables(A);
+    uint64_t mine = 0;
+    for (uint32_t q = threadIdx.x; q < A.n; q += BLOCK) {
+        const uint32_t c = box_cubes(A.lt, A.boxes + 6 * q);
+        first[q] = c;
+        mine += c;
+    }
+    for (int off = 32; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);
+    if (lane == 0) wave_sum[wave] = mine;
+    __syncthreads();
+    uint64_t total = 0;
+    for (int w = 0; w < BLOCK / 64; ++w) total += wave_sum[w];
+    const uint32_t target = part_cubes(total, ways, least);
+    __syncthreads();
+    // exclusive sums over the boxes, a contiguous stretch per thread
+    const uint32_t per = (A.n + BLOCK - 1) / BLOCK, b0 = min(A.n, threadIdx.x * per), b1 = min(A.n, b0 + per);
+    uint32_t sum = 0;
+    for (uint32_t q = b0; q < b1; ++q) {
+        const uint32_t p = parts_of(first[q], target);
+        sum += p + (p > 1 ? 1u << 16 : 0u);
+    }
+    uint32_t incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = uint32_t(__shfl_up(int(incl), off, 64));
+        if (lane >= uint32_t(off)) incl += v;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - sum;
+    for (uint32_t w = 0; w < wave; ++w) before += uint32_t(wave_sum[w]);
+    for (uint32_t q = b0; q < b1; ++q) {
+        const uint32_t p = parts_of(first[q], target);
+        first[q] = before;
+        before += p + (p > 1 ? 1u << 16 : 0u);
+    }
+    if (b1 == A.n && b0 < b1) first[A.n] = before;
+    __syncthreads();
+    const uint32_t items = uni(first[A.n]) & 0xFFFFu;
+    if (blockIdx.x >= items) return;
+    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
+    tables.put(A, sh);
+    clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
+    for (uint32_t i = blockIdx.x; i < items; i += gridDim.x) {
+        uint32_t q = 0;  // the last box whose items start at or before i
+        for (uint32_t step = kDirectMax / 2; step > 0; step >>= 1)
+            if (q + step < A.n && (first[q + step] & 0xFFFFu) <= i) q += step;
+        q = uni(q);
+        const uint32_t f = uni(first[q]), e = uni(first[q + 1]);
+        answer<BLOCK, GROUP, SPARSE, ERR>(A, sh, st,
+                                          Item{q, i - (f & 0xFFFFu), (e & 0xFFFFu) - (f & 0xFFFFu), f >> 16});
+    }
 }
 
 // Batched tiers: persistent blocks take queries from the largest-first order.
-// BIG: positions [0, counters[8]); otherwise [counters[8], n).
+// BIG: the parts of shared boxes, then positions [0, counters[kCountBig]); otherwise the
+// positions from there to n.
 // Six waves per SIMD (the second argument counts them): at most 80 VGPRs, so that
 // the memory latency of the streamed node IDs stays hidden.
 template <int BLOCK, bool BIG, int GROUP, bool SPARSE, bool ERR>
@@ -1639,10 +1869,10 @@ __global__ __launch_bounds__(BLOCK, 6) void query_tier_kernel(QueryArgs A)
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
     const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
-    load_graph_tables<BLOCK>(A, sh);
+    GraphTables(A).put(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
-    const uint32_t split = ld(&A.counters[8]);
-    const uint32_t begin = BIG ? 0u : split, end = BIG ? split : A.n;
+    const uint32_t big = uni(A.counters[kCountBig]), n_split = BIG ? uni(A.counters[kCountSplit]) : 0u;
+    const uint32_t begin = BIG ? 0u : big, end = BIG ? n_split + big : A.n;
     // Work queues: a single counter that every workgroup increments serialises
     // at one L2 atomic unit (about 12 ns per box), so the tier's positions of
     // the largest-first order are dealt to kQueues interleaved queues (queue j:
@@ -1658,7 +1888,7 @@ __global__ __launch_bounds__(BLOCK, 6) void query_tier_kernel(QueryArgs A)
     for (;;) {
         if (threadIdx.x == 0) sh.q = atomicAdd(qc, chunk);
         __syncthreads();
-        const uint32_t i0 = sh.q;
+        const uint32_t i0 = uni(sh.q);
         if (i0 >= end) break;  // uniform; keeps begin + qn + i0 * nq below 2^32
         const uint32_t k0 = begin + qn + i0 * nq;
         if (k0 >= end) break;  // uniform
@@ -1666,73 +1896,118 @@ __global__ __launch_bounds__(BLOCK, 6) void query_tier_kernel(QueryArgs A)
         for (uint32_t i = 0; i < chunk; ++i) {
             const uint32_t k = k0 + i * nq;
             if (k >= end) break;
-            run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, A.order[k], A.ovf_out != nullptr);
+            Item it;
+            if (BIG && k < n_split) {
+                it = part_of(A.split[k]);
+            } else {
+                const uint32_t q = uni(A.order[k - n_split]);
+                if (q == kEmpty) {  // its parts are in `split` (uniform)
+                    __syncthreads();
+                    continue;
+                }
+                it = whole_box(q);
+            }
+            answer<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it);
         }
     }
 }
 
-// Retry of boxes whose tier table overflowed (list 1), with a larger LDS table;
-// what overflows again goes to list 2.
+// State in worker w's tables of a global pool (slab list in LDS at `slabs`).
+__device__ inline QueryState pool_state(const GlobalPool &p, uint32_t w, char *slabs, QueryShared &sh, uint32_t nseg,
+                                        uint32_t n_levels, bool err)
+{
+    QueryState st;
+    const uint64_t at = uint64_t(w) * p.slots, sat = uint64_t(w) * nseg;
+    st.keys = p.keys + at;
+    st.cnt = p.cnt + at;
+    st.hi = p.hi + at;
+    st.lo = p.lo + at;
+    st.used = p.used + at;
+    st.cap = p.slots;
+    st.limit = st.cap / 4 * 3;
+    place_slabs(st, slabs, n_levels);
+    st.n_used = &sh.n_used;
+    st.flags = &sh.flags;
+    st.max_key = &sh.max_key;
+    st.seg_cnt = p.seg_cnt + sat;
+    st.seg_hi = p.seg_hi + sat;
+    st.seg_lo = p.seg_lo + sat;
+    st.seg_var = err ? p.seg_var + sat : nullptr;
+    return st;
+}
+
+// What overflowed its LDS table (list 1; usually nothing, and then every workgroup leaves at
+// once) with the largest LDS table of a workgroup; what overflows again goes to list 2. The
+// first workgroup also clears what the launches before this one counted with.
 template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
 __global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < kQueues * kQueueStride; i += BLOCK) A.queues[i] = 0;
+        if (threadIdx.x < 64) A.buckets[threadIdx.x] = 0;
+        if (threadIdx.x == 0) {
+            A.counters[kCountBig] = A.counters[kCountSplit] = A.counters[kCountSlot] = 0;
+            A.counters[kCountTotal] = A.counters[kCountTotal + 1] = 0;
+        }
+    }
+    const uint32_t n_list = uni(A.counters[kCountOver]);  // final: the launches before this one counted it
+    if (n_list == 0) return;
     const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
-    load_graph_tables<BLOCK>(A, sh);
+    GraphTables(A).put(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
-    const uint32_t n_list = ld(&A.counters[1]);
     for (;;) {
-        if (threadIdx.x == 0) sh.q = atomicAdd(&A.counters[4], 1u);
+        if (threadIdx.x == 0) sh.q = atomicAdd(&A.counters[kCountRetry], 1u);
         __syncthreads();
-        const uint32_t k = sh.q;
-        if (k >= n_list) break;  // uniform
-        run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, A.overflow[k], true);
+        const uint32_t k = uni(sh.q);
+        if (k >= n_list) break;
+        const uint32_t e = uni(A.overflow[k]);
+        if (run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, listed_item(A, e), false, 0x40000000u) &&
+            threadIdx.x == 0)
+            A.overflow2[atomicAdd(&A.counters[kCountOver2], 1u)] = e;
     }
 }
 
-// Boxes that overflowed every LDS table, answered with per-worker tables and
-// source arrays in the workspace (global memory): first by many workers with
-// mid-size tables (list 2; what overflows those goes to list 3), then by a few
-// workers whose tables hold every node of the graph (list 3, or list 2 when
-// the graph is small enough for those tables alone). Sources always have
-// per-worker arrays here (dense state, whatever the output): a cube run on a
-// source is one global atomic add without a returned value, where a table
-// entry would take a probe round trip.
-// Boxes that overflowed every LDS table, in per-worker global-memory tables (node
-// table and per-source arrays): each workgroup takes boxes from list A.g_list.
+// What overflowed every LDS table (list 2), with per-worker tables and source arrays in global
+// memory: first by many workers with mid-size tables (what overflows those goes to list 3),
+// then by a few workers whose tables hold every node of the graph (list 3, or list 2 where the
+// graph is small enough for those tables alone). Sources always have per-worker arrays here
+// (dense state, whatever the output): a cube run on a source is one global atomic add without
+// a returned value, where a table entry would take a probe round trip. The last workgroup of
+// the last of these launches clears the counters of the lists for the next call.
 template <bool ERR>
-__global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A)
+__global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A, GlobalPool pool, uint32_t list,
+                                                                uint32_t last)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
-    QueryState st;
-    const uint64_t w = blockIdx.x;
-    const uint64_t gs = A.g_slots;
-    st.keys = A.g_keys + w * gs;
-    st.cnt = A.g_cnt + w * gs;
-    st.hi = A.g_hi + w * gs;
-    st.lo = A.g_lo + w * gs;
-    st.used = A.g_used + w * gs;
-    st.cap = A.g_slots;
-    place_slabs(st, dyn, A.lt.n_levels);  // the only dynamic LDS of this kernel
-    st.limit = st.cap / 4 * 3;
-    st.n_used = &sh.n_used;
-    st.flags = &sh.flags;
-    st.max_key = &sh.max_key;
-    st.seg_cnt = A.g_seg_cnt + w * A.gv.nseg;
-    st.seg_hi = A.g_seg_hi + w * A.gv.nseg;
-    st.seg_lo = A.g_seg_lo + w * A.gv.nseg;
-    st.seg_var = ERR ? A.g_seg_var + w * A.gv.nseg : nullptr;
-    load_graph_tables<kBlock>(A, sh);
-    __syncthreads();
-    const uint32_t n_over = ld(&A.counters[A.g_count_idx]);
-    for (;;) {
-        if (threadIdx.x == 0) sh.q = atomicAdd(&A.counters[A.g_next_idx], 1u);
+    if (uni(A.counters[kCountOver]) == 0) return;  // nothing overflowed at all: the same in every workgroup
+    const uint32_t *const entries = list == 2 ? A.overflow2 : A.overflow3;
+    const uint32_t n_list = uni(A.counters[list == 2 ? kCountOver2 : kCountOver3]);
+    const uint32_t next = list == 2 ? kCountNext2 : kCountNext3;
+    if (n_list) {
+        const QueryState st = pool_state(pool, blockIdx.x, dyn, sh, A.gv.nseg, A.lt.n_levels, ERR);
+        GraphTables(A).put(A, sh);
         __syncthreads();
-        const uint32_t k = sh.q;
-        if (k >= n_over) break;  // uniform
-        run_query<kBlock, kGroup, false, ERR>(A, sh, st, A.g_list[k], A.ovf_out != nullptr);
+        for (;;) {
+            if (threadIdx.x == 0) sh.q = atomicAdd(&A.counters[next], 1u);
+            __syncthreads();
+            const uint32_t k = uni(sh.q);
+            if (k >= n_list) break;
+            const uint32_t e = uni(entries[k]);
+            if (run_query<kBlock, kGroup, false, ERR>(A, sh, st, listed_item(A, e), last != 0, 0x80000000u) &&
+                !last && threadIdx.x == 0)
+                A.overflow3[atomicAdd(&A.counters[kCountOver3], 1u)] = e;
+        }
+    }
+    if (last && threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&A.counters[kCountExit], 1u) + 1u == gridDim.x) {  // every workgroup is past its counters
+            A.counters[kCountOver] = A.counters[kCountOver2] = A.counters[kCountOver3] = 0;
+            A.counters[kCountRetry] = A.counters[kCountNext2] = A.counters[kCountNext3] = 0;
+            A.counters[kCountExit] = A.counters[kCountSplitOver] = 0;
+        }
     }
 }
 
@@ -1749,64 +2024,63 @@ __device__ inline void block_histogram_add(uint32_t bkt, uint32_t *bucket_count)
     if (threadIdx.x < 32 && h[threadIdx.x]) atomicAdd(&bucket_count[threadIdx.x], h[threadIdx.x]);
 }
 
-// Per-query work estimate (cubes) and log2 bucket for the largest-first order.
-__global__ void query_size_kernel(LevelTable lt, const uint32_t *boxes, uint32_t n, uint32_t *bucket_of,
-                                  uint32_t *bucket_count)
+// Size bucket of a box, largest first: bucket 0 holds >= 2^31 cubes.
+__device__ inline uint32_t size_bucket(uint32_t cubes) { return 31u - (cubes ? 31u - uint32_t(__clz(int(cubes))) : 0u); }
+
+// Planning, first launch: cubes of every box, how many boxes fall into each of 32 log2 size
+// buckets, and all boxes' cubes together. `zero` (the sparse output's total, or null) is reset.
+__global__ void query_size_kernel(LevelTable lt, const uint32_t *boxes, uint32_t n, uint32_t *work,
+                                  uint32_t *bucket_count, uint32_t *counters, uint32_t *zero)
 {
     const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t lo[3], hi[3];
-    uint64_t cubes = 0;
-    if (q < n && clip_box(boxes + 6 * uint64_t(q), lt, lo, hi)) {
-        for (uint32_t l = 0; l < lt.n_levels; ++l) {
-            uint64_t outer = 1, inner = 1;
-            for (int d = 0; d < 3; ++d) {
-                const uint64_t one = uint64_t(1) << l;
-                const uint64_t a = (uint64_t(lo[d]) + one - 1) >> l, b = hi[d] >> l;
-                const uint64_t pa = (uint64_t(lo[d]) + 2 * one - 1) >> (l + 1), pb = hi[d] >> (l + 1);
-                outer *= b > a ? b - a : 0;
-                inner *= pb > pa ? 2 * (pb - pa) : 0;
-            }
-            cubes += outer - inner;
-        }
-    }
-    // 32 buckets, largest work first: bucket 0 holds >= 2^31 cubes
-    const uint32_t lg = cubes ? 63 - __clzll(cubes) : 0;
-    const uint32_t bkt = q < n ? 31 - min(lg, 31u) : 32u;
-    if (q < n) bucket_of[q] = bkt;
-    block_histogram_add(bkt, bucket_count);  // every thread, one call site: the barriers match
+    if (q == 0 && zero) *zero = 0;
+    const uint32_t cubes = q < n ? box_cubes(lt, boxes + 6 * uint64_t(q)) : 0u;
+    if (q < n) work[q] = cubes;
+    uint64_t sum = cubes;
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+    __shared__ unsigned long long block_sum;
+    if (threadIdx.x == 0) block_sum = 0;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) atomicAdd(&block_sum, (unsigned long long)sum);
+    block_histogram_add(q < n ? size_bucket(cubes) : 32u, bucket_count);  // every thread, one call site
+    if (threadIdx.x == 0) atomicAdd(reinterpret_cast<unsigned long long *>(counters + kCountTotal), block_sum);
 }
 
-__global__ void query_order_kernel(const uint32_t *bucket_of, uint32_t n, uint32_t *bucket_count, uint32_t *order)
+// Planning, second launch: the largest-first order. bucket_count[b] holds the boxes of bucket
+// b and bucket_count[32 + b] counts those placed; each block reserves one range per bucket and
+// ranks its boxes inside it. Boxes above their share of the work (part_cubes) are split into
+// parts instead, and leave a hole.
+__global__ void query_order_kernel(const uint32_t *work, uint32_t n, uint32_t *bucket_count, uint32_t *order,
+                                   uint32_t *counters, uint4 *split, uint32_t ways, uint32_t least)
 {
-    // bucket_count[32 + b] holds, on entry, the first free position of bucket b;
-    // each block reserves one range per bucket and ranks its boxes inside it
     __shared__ uint32_t h[32], base[32];
     const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
     if (threadIdx.x < 32) h[threadIdx.x] = 0;
     __syncthreads();
-    const uint32_t bkt = q < n ? bucket_of[q] : 32u;
+    const uint32_t cubes = q < n ? work[q] : 0u, bkt = q < n ? size_bucket(cubes) : 32u;
     const uint32_t local = bkt < 32 ? atomicAdd(&h[bkt], 1u) : 0u;
     __syncthreads();
-    if (threadIdx.x < 32 && h[threadIdx.x]) base[threadIdx.x] = atomicAdd(&bucket_count[32 + threadIdx.x], h[threadIdx.x]);
-    __syncthreads();
-    if (bkt < 32) order[base[bkt] + local] = q;
-}
-
-__global__ void bucket_scan_kernel(uint32_t *bucket_count, uint32_t *counters)
-{
-    if (threadIdx.x == 0) {
-        uint32_t acc = 0;
-        for (int b = 0; b < 32; ++b) {
-            if (b == 31 - int(kBigLog2) + 1) counters[8] = acc;  // boxes of >= 2^kBigLog2 cubes come first
-            bucket_count[32 + b] = acc;
-            acc += bucket_count[b];
+    if (threadIdx.x < 64) {
+        const uint32_t c = threadIdx.x < 32 ? bucket_count[threadIdx.x] : 0u;
+        uint32_t incl = c;
+        for (int off = 1; off < 32; off <<= 1) {
+            const uint32_t v = uint32_t(__shfl_up(int(incl), off, 64));
+            if (threadIdx.x >= uint32_t(off)) incl += v;
         }
+        if (threadIdx.x < 32 && h[threadIdx.x])
+            base[threadIdx.x] = incl - c + atomicAdd(&bucket_count[32 + threadIdx.x], h[threadIdx.x]);
+        // boxes of >= 2^kBigLog2 cubes come first
+        if (blockIdx.x == 0 && threadIdx.x == 31 - kBigLog2) counters[kCountBig] = incl;
     }
-}
-
-__global__ void reset_counters_kernel(uint32_t *c, uint32_t n)
-{
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) c[i] = 0;
+    __syncthreads();
+    if (bkt >= 32) return;
+    const uint32_t target = part_cubes(*reinterpret_cast<const uint64_t *>(counters + kCountTotal), ways, least);
+    const uint32_t parts = parts_of(cubes, target);
+    order[base[bkt] + local] = parts > 1 ? kEmpty : q;
+    if (parts > 1) {
+        const uint32_t slot = atomicAdd(&counters[kCountSlot], 1u), k = atomicAdd(&counters[kCountSplit], parts);
+        for (uint32_t p = 0; p < parts; ++p) split[k + p] = make_uint4(q, p, parts, slot);
+    }
 }
 
 // ---------------------------------------------------------------- naive scan
@@ -2306,24 +2580,19 @@ LevelTable level_table(const Graph &g) { return level_table_dims(g.dims); }
 
 // ---------------------------------------------------------------- workspace layout
 
-// Per-worker global-memory tables of one global-table launch.
-struct GlobalPool {
-    uint32_t workers, slots;
-    uint32_t *keys, *cnt, *used;
-    float *hi, *lo;
-    uint32_t *seg_cnt;
-    float *seg_hi, *seg_lo, *seg_var;
-};
-
 struct Workspace {
     uint32_t *counters;   // 64 u32
     uint32_t *queues;     // kQueues * kQueueStride u32: per-queue counters of the two tiers
     uint32_t *buckets;    // 64 u32
-    uint32_t *bucket_of;  // [max_boxes]
+    uint32_t *work;       // [max_boxes] cubes of each box
     uint32_t *order;      // [max_boxes]
-    uint32_t *overflow;   // [max_boxes] list 1: overflowed a tier table
-    uint32_t *overflow2;  // [max_boxes] list 2: overflowed the retry table too
-    uint32_t *overflow3;  // [max_boxes] list 3: overflowed a mid-size global table too
+    uint32_t *overflow;   // [max_boxes + 2 n_slots] list 1: boxes and parts whose LDS table overflowed
+    uint32_t *overflow2;  // [max_boxes + 2 n_slots] list 2: overflowed the retry table too
+    uint32_t *overflow3;  // [max_boxes + 2 n_slots] list 3: overflowed a mid-size global table too
+    uint32_t n_slots;     // boxes that several workgroups may share
+    uint4 *split, *split_over;      // [2 n_slots] each
+    uint32_t *slot_done, *slot_cnt; // [n_slots], [n_slots][S]
+    float *slot_hi, *slot_lo;       // [n_slots][S]
     GlobalPool fin;       // tables that hold every node of the graph
     GlobalPool mid;       // many workers with mid-size tables (workers 0: none)
     uint64_t bytes;
@@ -2353,11 +2622,19 @@ inline uint32_t fallback_workers(const Graph &g)
 // where the final tables are larger than that.
 inline uint32_t mid_workers(const Graph &g) { return fallback_slots(g) > kHashGlobal ? kMidWorkers : 0u; }
 
+// Boxes that several workgroups may share in one call (each takes 12 bytes per source). None on
+// graphs whose boxes can overflow even the final tables.
+inline uint32_t split_slots(const Graph &g)
+{
+    if (uint64_t(g.n_nodes) * 4 / 3 + 2 > (uint64_t(1) << 26)) return 0;
+    return uint32_t(std::min<uint64_t>(kMaxSlots, std::max<uint64_t>(kMinSlots, kSlotBytes / (12ull * g.nseg))));
+}
+
 // Carves the workspace for `fin_workers` workers of the final tables (0:
-// fallback_workers(g)) and `mid_workers` of the mid-size ones (~0u: mid_workers(g));
-// with base == nullptr only computes the size.
+// fallback_workers(g)), `mid_workers` of the mid-size ones (~0u: mid_workers(g)) and n_slots
+// shared boxes (~0u: split_slots(g)); with base == nullptr only computes the size.
 Workspace carve(const Graph &g, char *base, uint32_t max_boxes, uint32_t fin_workers = 0,
-                uint32_t n_mid = ~0u)
+                uint32_t n_mid = ~0u, uint32_t n_slots = ~0u)
 {
     Workspace w;
     uint64_t off = 0;
@@ -2386,11 +2663,19 @@ Workspace carve(const Graph &g, char *base, uint32_t max_boxes, uint32_t fin_wor
     w.queues = reinterpret_cast<uint32_t *>(take(uint64_t(kQueues) * kQueueStride * 4));
     pool(w.fin, fin_workers ? fin_workers : fallback_workers(g), fallback_slots(g));
     pool(w.mid, n_mid == ~0u ? mid_workers(g) : n_mid, kHashGlobal);
-    w.bucket_of = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
+    w.n_slots = n_slots == ~0u ? split_slots(g) : n_slots;
+    const uint64_t ns = w.n_slots;
+    w.slot_done = reinterpret_cast<uint32_t *>(take(ns * 4));
+    w.slot_cnt = reinterpret_cast<uint32_t *>(take(ns * g.nseg * 4));
+    w.slot_hi = reinterpret_cast<float *>(take(ns * g.nseg * 4));
+    w.slot_lo = reinterpret_cast<float *>(take(ns * g.nseg * 4));
+    w.split = reinterpret_cast<uint4 *>(take(2 * ns * sizeof(uint4)));
+    w.split_over = reinterpret_cast<uint4 *>(take(2 * ns * sizeof(uint4)));
+    w.work = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
     w.order = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
-    w.overflow = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
-    w.overflow2 = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
-    w.overflow3 = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
+    w.overflow = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 2 * ns) * 4));
+    w.overflow2 = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 2 * ns) * 4));
+    w.overflow3 = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 2 * ns) * 4));
     w.bytes = off;
     w.max_boxes = max_boxes;
     return w;
@@ -2517,7 +2802,7 @@ static __device__ __align__(256) char scratch[kScratchBytes];
 
 struct ScratchSlot {
     char *ptr = nullptr;                // device address of `scratch` on this device
-    uint64_t layout[3] = {0, 0, 0};     // (sources, fallback slots, workers) last cleared; 0: never
+    uint64_t layout[4] = {0, 0, 0, 0};  // (sources, table slots, workers, shared boxes + 1) last cleared; 0: never
 };
 std::mutex g_scratch_mu;
 std::vector<ScratchSlot> g_scratch;      // per device ordinal
@@ -3264,10 +3549,24 @@ void clear_pool(const Graph &g, const GlobalPool &p, hipStream_t s)
     hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, reinterpret_cast<uint32_t *>(p.seg_var), ss, 0u);
 }
 
-void clear_fallback_tables(const Graph &g, const Workspace &w, hipStream_t s)
+// Everything a query expects clean and leaves clean: the fixed part of a workspace.
+void clear_workspace(const Graph &g, const Workspace &w, hipStream_t s)
 {
     clear_pool(g, w.fin, s);
     clear_pool(g, w.mid, s);
+    auto zero = [&](void *p, uint64_t n) {
+        if (n)
+            hipLaunchKernelGGL(fill_u32_kernel, dim3(uint32_t(std::min<uint64_t>((n + 255) / 256, 1024))), dim3(256), 0,
+                               s, static_cast<uint32_t *>(p), n, 0u);
+    };
+    zero(w.counters, 64);
+    zero(w.buckets, 64);
+    zero(w.queues, uint64_t(kQueues) * kQueueStride);
+    const uint64_t ns = w.n_slots;
+    zero(w.slot_done, ns);
+    zero(w.slot_cnt, ns * g.nseg);
+    zero(w.slot_hi, ns * g.nseg);
+    zero(w.slot_lo, ns * g.nseg);
 }
 
 int dev_workspace_init(Graph *g, void *work, uint64_t bytes, void *stream, std::string *err)
@@ -3281,113 +3580,103 @@ int dev_workspace_init(Graph *g, void *work, uint64_t bytes, void *stream, std::
         *err = "workspace smaller than mg_workspace_bytes(g, 1)";
         return MG_EINVAL;
     }
-    clear_fallback_tables(*g, w, static_cast<hipStream_t>(stream));
+    clear_workspace(*g, w, static_cast<hipStream_t>(stream));
     HIP_TRY(hipGetLastError());
     return MG_OK;
 }
 
 template <bool SPARSE, bool ERR>
-int launch_query(Graph *g, QueryArgs &A, const Workspace &w, const LevelTable &lt, uint32_t n, hipStream_t s,
+int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &w, uint32_t n, hipStream_t s,
                  int variant, std::string *err)
 {
     int rc = MG_OK;
     DeviceState &d = g->dev;
-    const int bbig = d.cfg.block_big == 256 ? 256 : kBlockBig;    // threads per big-tier box
-    const QueryKernel kbig = bbig == 256 ? tier_kernel<256, true, SPARSE, ERR>(d.cfg.unroll_big)
-                                         : tier_kernel<kBlockBig, true, SPARSE, ERR>(d.cfg.unroll_big);
-    const int bsmall = d.cfg.block_small == 256 ? kBlock : 128;  // threads per small-tier box
-    const QueryKernel ksmall = bsmall == 128 ? tier_kernel<128, false, SPARSE, ERR>(d.cfg.unroll_small)
-                                             : tier_kernel<kBlock, false, SPARSE, ERR>(d.cfg.unroll_small);
-    const QueryKernel kplain = query_plain_kernel<SPARSE>;
-    const uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : (SPARSE ? kHashBigSparse : kHashBig);
-    const uint32_t cap_small = d.cfg.table_small ? d.cfg.table_small : (SPARSE ? kHashSmallSparse : kHashSmall);
     const uint32_t L = g->n_levels;
-    constexpr bool E = ERR;
-    const uint32_t dyn_big = lds_bytes(g->nseg, cap_big, SPARSE, L, E),
-                   dyn_small = lds_bytes(g->nseg, cap_small, SPARSE, L, E),
-                   dyn_plain = lds_bytes(g->nseg, kHashPlain, SPARSE, L, E);
-    int occ_big = 1, occ_small = 1, occ_plain = 1;
-    if ((rc = occupancy(d, reinterpret_cast<const void *>(kbig), bbig, dyn_big, &occ_big, err)) ||
-        (rc = occupancy(d, reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &occ_small, err)) ||
-        (rc = occupancy(d, reinterpret_cast<const void *>(kplain), kBlock, dyn_plain, &occ_plain, err)))
-        return rc;
-    hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, w.counters, 64u);
-    hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(256), 0, s, w.queues, kQueues * kQueueStride);
-    A.queues = w.queues;
-    if (A.sp_total) hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, A.sp_total, 1u);
-    if (variant == kQueryBatched || variant == kQueryLut) {
-        hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, s, w.buckets, 64u);
+    auto bytes = [&](uint32_t cap) { return lds_bytes(g->nseg, cap, SPARSE, L, ERR); };
+    // workgroups of a kernel that are resident together
+    auto resident = [&](const void *k, int block, uint32_t dyn, uint32_t *out) -> int {
+        int occ = 1;
+        if (int r = occupancy(d, k, block, dyn, &occ, err)) return r;
+        *out = uint32_t(d.ncu) * uint32_t(occ);
+        return MG_OK;
+    };
+    const bool batched = variant == kQueryBatched || variant == kQueryLut;
+    if (batched && n <= kDirectMax) {
+        // few boxes: no planning launches
+        const auto kdirect = query_direct_kernel<kBlockDirect, 4, SPARSE, ERR>;
+        A.table_cap = d.cfg.table_big ? d.cfg.table_big : SPARSE ? kHashBigSparse : ERR ? kHashBig : kHashDirect;
+        const uint32_t dyn = bytes(A.table_cap);
+        uint32_t grid = 0;
+        if ((rc = resident(reinterpret_cast<const void *>(kdirect), kBlockDirect, dyn, &grid))) return rc;
+        if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
+        // about one part per CU: with four, 256 boxes of a 589x563x395 volume took 122 us instead
+        // of 63 (every part adds its sources to its box's sums with global atomics)
+        const uint32_t ways = std::min({grid, uint32_t(d.ncu), A.n_slots});
+        if ((rc = timing_begin(g, s, err))) return rc;
+        hipLaunchKernelGGL(kdirect, dim3(std::min(grid, n + 2 * ways)), dim3(kBlockDirect), dyn, s, A, ways, kMinPart);
+        HIP_TRY(hipGetLastError());
+    } else if (batched) {
+        const int bbig = d.cfg.block_big == 256 ? 256 : kBlockBig;    // threads per big-tier box
+        const QueryKernel kbig = bbig == 256 ? tier_kernel<256, true, SPARSE, ERR>(d.cfg.unroll_big)
+                                             : tier_kernel<kBlockBig, true, SPARSE, ERR>(d.cfg.unroll_big);
+        const int bsmall = d.cfg.block_small == 256 ? kBlock : 128;  // threads per small-tier box
+        const QueryKernel ksmall = bsmall == 128 ? tier_kernel<128, false, SPARSE, ERR>(d.cfg.unroll_small)
+                                                 : tier_kernel<kBlock, false, SPARSE, ERR>(d.cfg.unroll_small);
+        const uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : (SPARSE ? kHashBigSparse : kHashBig);
+        const uint32_t cap_small = d.cfg.table_small ? d.cfg.table_small : (SPARSE ? kHashSmallSparse : kHashSmall);
+        const uint32_t dyn_big = bytes(cap_big), dyn_small = bytes(cap_small);
+        uint32_t wbig = 0, wsmall = 0;
+        if ((rc = resident(reinterpret_cast<const void *>(kbig), bbig, dyn_big, &wbig)) ||
+            (rc = resident(reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &wsmall)))
+            return rc;
         const uint32_t blocks = (n + 255) / 256;
-        hipLaunchKernelGGL(query_size_kernel, dim3(blocks), dim3(256), 0, s, lt, A.boxes, n, w.bucket_of, w.buckets);
-        hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(64), 0, s, w.buckets, w.counters);
-        hipLaunchKernelGGL(query_order_kernel, dim3(blocks), dim3(256), 0, s, w.bucket_of, n, w.buckets, w.order);
+        hipLaunchKernelGGL(query_size_kernel, dim3(blocks), dim3(256), 0, s, lt, A.boxes, n, w.work, w.buckets,
+                           w.counters, A.sp_total);
+        hipLaunchKernelGGL(query_order_kernel, dim3(blocks), dim3(256), 0, s, w.work, n, w.buckets, w.order,
+                           w.counters, w.split, A.n_slots, kMinPartBatch);
         A.order = w.order;
-        const uint32_t wbig = std::max(1u, std::min<uint32_t>(n, uint32_t(d.ncu) * uint32_t(occ_big)));
-        const uint32_t wsmall = std::max(1u, std::min<uint32_t>(n, uint32_t(d.ncu) * uint32_t(occ_small)));
-        rc = timing_begin(g, s, err);
-        if (rc) return rc;
+        if ((rc = timing_begin(g, s, err))) return rc;
         A.table_cap = cap_big;
-        hipLaunchKernelGGL(kbig, dim3(wbig), dim3(bbig), dyn_big, s, A);
+        hipLaunchKernelGGL(kbig, dim3(std::min(n + 2 * A.n_slots, wbig)), dim3(bbig), dyn_big, s, A);
         HIP_TRY(hipGetLastError());
         A.table_cap = cap_small;
         A.chunk = d.cfg.chunk_small;
-        hipLaunchKernelGGL(ksmall, dim3(wsmall), dim3(bsmall), dyn_small, s, A);
+        hipLaunchKernelGGL(ksmall, dim3(std::min(n, wsmall)), dim3(bsmall), dyn_small, s, A);
         HIP_TRY(hipGetLastError());
     } else {
+        const QueryKernel kplain = query_plain_kernel<SPARSE>;
         A.table_cap = kHashPlain;
-        rc = timing_begin(g, s, err);
-        if (rc) return rc;
-        hipLaunchKernelGGL(kplain, dim3(n), dim3(kBlock), dyn_plain, s, A);
+        uint32_t all = 0;
+        if ((rc = resident(reinterpret_cast<const void *>(kplain), kBlock, bytes(kHashPlain), &all))) return rc;
+        if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
+        if ((rc = timing_begin(g, s, err))) return rc;
+        hipLaunchKernelGGL(kplain, dim3(n), dim3(kBlock), bytes(kHashPlain), s, A);
         HIP_TRY(hipGetLastError());
     }
-    // boxes whose table overflowed: once more with a larger LDS table, then in global memory
+    // what overflowed its table: once more with a larger LDS table, then in global memory
     const QueryKernel kretry = query_retry_kernel<kBlockBig, 4, SPARSE, ERR>;
     uint32_t cap_retry = d.cfg.table_retry;
     if (!cap_retry) {  // the largest table up to kHashRetry that fits the LDS of a workgroup
         uint32_t stat = 0;
         if ((rc = static_lds(reinterpret_cast<const void *>(kretry), &stat, err))) return rc;
         cap_retry = kHashRetry;
-        while (cap_retry > kHashBigSparse &&
-               uint64_t(lds_bytes(g->nseg, cap_retry, SPARSE, L, E)) + stat > uint64_t(d.lds_max))
-            cap_retry /= 2;
+        while (cap_retry > kHashBigSparse && uint64_t(bytes(cap_retry)) + stat > uint64_t(d.lds_max)) cap_retry /= 2;
     }
-    const uint32_t dyn_retry = lds_bytes(g->nseg, cap_retry, SPARSE, L, E);
-    int occ_retry = 1;
-    if ((rc = occupancy(d, reinterpret_cast<const void *>(kretry), kBlockBig, dyn_retry, &occ_retry, err)))
-        return rc;
+    uint32_t wretry = 0;
+    if ((rc = resident(reinterpret_cast<const void *>(kretry), kBlockBig, bytes(cap_retry), &wretry))) return rc;
     A.table_cap = cap_retry;
-    A.stats_tag = 0x40000000u;
-    A.ovf_out = w.overflow2;
-    A.ovf_out_idx = 5;
-    hipLaunchKernelGGL(kretry, dim3(uint32_t(d.ncu) * uint32_t(occ_retry)), dim3(kBlockBig), dyn_retry, s, A);
+    // no more workgroups than there can be entries for (a box, or its parts)
+    hipLaunchKernelGGL(kretry, dim3(std::min(wretry, n + 2 * A.n_slots)), dim3(kBlockBig), bytes(cap_retry), s, A);
     HIP_TRY(hipGetLastError());
-    // boxes that overflowed every LDS table: global-memory tables, first many workers with
-    // mid-size tables (overflow: list 3), then the few whose tables hold the whole graph
-    A.stats_tag = 0x80000000u;
-    const QueryKernel kfallback = query_fallback_kernel<ERR>;
+    const auto kfallback = query_fallback_kernel<ERR>;
     const uint32_t dyn_fb = lds_slab_bytes(L);
-    auto use_pool = [&](const GlobalPool &p) {
-        A.g_slots = p.slots;
-        A.g_keys = p.keys, A.g_cnt = p.cnt, A.g_used = p.used, A.g_hi = p.hi, A.g_lo = p.lo;
-        A.g_seg_cnt = p.seg_cnt, A.g_seg_hi = p.seg_hi, A.g_seg_lo = p.seg_lo, A.g_seg_var = p.seg_var;
-    };
     if (w.mid.workers) {
-        use_pool(w.mid);
-        A.g_list = w.overflow2, A.g_count_idx = 5, A.g_next_idx = 7;
-        A.ovf_out = w.overflow3;
-        A.ovf_out_idx = 6;
-        hipLaunchKernelGGL(kfallback, dim3(w.mid.workers), dim3(kBlock), dyn_fb, s, A);
+        hipLaunchKernelGGL(kfallback, dim3(w.mid.workers), dim3(kBlock), dyn_fb, s, A, w.mid, 2u, 0u);
         HIP_TRY(hipGetLastError());
-        A.g_list = w.overflow3, A.g_count_idx = 6;
-    } else {
-        A.g_list = w.overflow2, A.g_count_idx = 5;
     }
-    use_pool(w.fin);
-    A.g_next_idx = 2;
-    A.ovf_out = nullptr;
-    hipLaunchKernelGGL(kfallback, dim3(w.fin.workers), dim3(kBlock), dyn_fb, s, A);
+    hipLaunchKernelGGL(kfallback, dim3(w.fin.workers), dim3(kBlock), dyn_fb, s, A, w.fin, w.mid.workers ? 3u : 2u, 1u);
     HIP_TRY(hipGetLastError());
-    // the timed region: every kernel that answers boxes (tiers or plain, retry, fallback)
+    // the timed region: every kernel that answers boxes
     return timing_end(g, s, err);
 }
 
@@ -3463,11 +3752,21 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     A.depth = g->depth;
     A.n = n;
     A.counters = w.counters;
+    A.queues = w.queues;
+    A.buckets = w.buckets;
     A.overflow = w.overflow;
     A.overflow2 = w.overflow2;
-    A.ovf_out = w.overflow;
-    A.ovf_out_idx = 1;
+    A.overflow3 = w.overflow3;
     A.stats = stats;
+    // Shared boxes: not where a box's table entries are reported, nor where they all have to be
+    // in one table (uncertainties); list entries hold box numbers below kPartFlag.
+    A.n_slots = stats || variant == kQueryLutErr || variant == kQueryPlain || n >= kPartFlag ? 0u : w.n_slots;
+    A.split = w.split;
+    A.split_over = w.split_over;
+    A.slot_done = w.slot_done;
+    A.slot_cnt = w.slot_cnt;
+    A.slot_hi = w.slot_hi;
+    A.slot_lo = w.slot_lo;
     if (variant == kQueryLut || variant == kQueryLutErr) {
         if (!g->dev.lut_ptr) {
             *err = "the mixture lookup table is not on the device (mg_lut_build)";
@@ -3501,9 +3800,9 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     A.lt.runs_mask = run_min == 0xFFFFFFFFu ? 0u : g->dev.runs_mask;
     A.lt.run_min = run_min;
     A.runs = static_cast<const RunLevel *>(g->dev.run_table);
-    if (A.out_err) return launch_query<false, true>(g, A, w, lt, n, s, variant, err);
-    return sparse ? launch_query<true, false>(g, A, w, lt, n, s, variant, err)
-                  : launch_query<false, false>(g, A, w, lt, n, s, variant, err);
+    if (A.out_err) return launch_query<false, true>(g, A, lt, w, n, s, variant, err);
+    return sparse ? launch_query<true, false>(g, A, lt, w, n, s, variant, err)
+                  : launch_query<false, false>(g, A, lt, w, n, s, variant, err);
 }
 
 }  // namespace
@@ -3533,11 +3832,12 @@ int dev_query_noalloc(Graph *g, const uint32_t *boxes, uint32_t n, float *out, v
     if ((rc = scratch_slot(g->dev.device, &sl, err))) return rc;
     // as many workers of the final global tables as fit beside the per-box arrays (at least
     // one), none with mid-size tables (a speed-up only: every box fits the final tables)
-    uint32_t workers = fallback_workers(*g);
-    while (workers > 1 && carve(*g, nullptr, n, workers, 0).bytes > kScratchBytes) --workers;
-    const Workspace probe = carve(*g, nullptr, n, workers, 0);
-    if (probe.bytes > kScratchBytes) {
-        const uint64_t fixed = carve(*g, nullptr, 1, 1, 0).bytes;
+    uint32_t workers = fallback_workers(*g), slots = std::min(split_slots(*g), kNoallocSlots);
+    auto size = [&](uint32_t f, uint32_t ns) { return carve(*g, nullptr, n, f, 0, ns).bytes; };
+    if (size(std::min(workers, kMinSlots), slots) > kScratchBytes) slots = 0;  // room for the workers first
+    while (workers > 1 && size(workers, slots) > kScratchBytes) --workers;
+    if (size(workers, slots) > kScratchBytes) {
+        const uint64_t fixed = carve(*g, nullptr, 1, 1, 0, 0).bytes;
         *err = fixed > kScratchBytes
                    ? "mg_query_boxes_noalloc: the graph's global fallback table (" + std::to_string(fixed) +
                          " bytes for " + std::to_string(g->n_nodes) + " nodes) exceeds the " +
@@ -3548,12 +3848,12 @@ int dev_query_noalloc(Graph *g, const uint32_t *boxes, uint32_t n, float *out, v
         return MG_ELIMIT;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Workspace w = carve(*g, sl->ptr, n, workers, 0);
+    const Workspace w = carve(*g, sl->ptr, n, workers, 0, slots);
     // the scratch keeps the last call's contents; every query leaves the fallback
     // tables clean, so they are cleared only when their layout changes
-    const uint64_t layout[3] = {g->nseg, fallback_slots(*g), workers};
+    const uint64_t layout[4] = {g->nseg, fallback_slots(*g), workers, slots + 1ull};
     if (std::memcmp(layout, sl->layout, sizeof(layout)) != 0) {
-        clear_fallback_tables(*g, w, s);
+        clear_workspace(*g, w, s);
         HIP_TRY(hipGetLastError());
         std::memcpy(sl->layout, layout, sizeof(layout));
     }
