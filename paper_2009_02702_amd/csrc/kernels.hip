@@ -48,6 +48,10 @@ constexpr uint32_t kHashSmallSparse = 2048;   // small-box tier, sources as tabl
 constexpr uint32_t kHashBigSparse = 4096;     // big-box tier, sources as table entries
 constexpr uint32_t kHashRetry = 8192;         // boxes that overflowed a tier table
 constexpr uint32_t kBigLog2 = 14;             // boxes of >= 2^14 cubes go to the big tier
+// The same where small boxes keep sources in the table: 20,000 boxes of a 307x480x300 volume of
+// 3,980 fibres with 2^8 / 2^10 / 2^12 / 2^14: 4.70 / 4.76 / 4.88 / 5.41 ms.
+constexpr uint32_t kBigLog2Sparse = 10;
+constexpr uint32_t kStaticLds = 9216;         // LDS set aside for the query kernels' fixed arrays
 constexpr uint32_t kHashGlobal = 1u << 16;    // fewest per-worker hash slots in the fallback tables
 constexpr uint32_t kSegLdsMax = 2048;         // sources kept in LDS
 constexpr uint32_t kFallbackWorkers = 128;    // workers of the final global-table launch (budget)
@@ -2051,7 +2055,8 @@ __global__ void query_size_kernel(LevelTable lt, const uint32_t *boxes, uint32_t
 // ranks its boxes inside it. Boxes above their share of the work (part_cubes) are split into
 // parts instead, and leave a hole.
 __global__ void query_order_kernel(const uint32_t *work, uint32_t n, uint32_t *bucket_count, uint32_t *order,
-                                   uint32_t *counters, uint4 *split, uint32_t ways, uint32_t least)
+                                   uint32_t *counters, uint4 *split, uint32_t ways, uint32_t least,
+                                   uint32_t big_log2)
 {
     __shared__ uint32_t h[32], base[32];
     const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2069,8 +2074,8 @@ __global__ void query_order_kernel(const uint32_t *work, uint32_t n, uint32_t *b
         }
         if (threadIdx.x < 32 && h[threadIdx.x])
             base[threadIdx.x] = incl - c + atomicAdd(&bucket_count[32 + threadIdx.x], h[threadIdx.x]);
-        // boxes of >= 2^kBigLog2 cubes come first
-        if (blockIdx.x == 0 && threadIdx.x == 31 - kBigLog2) counters[kCountBig] = incl;
+        // boxes of >= 2^big_log2 cubes come first
+        if (blockIdx.x == 0 && threadIdx.x == 31 - big_log2) counters[kCountBig] = incl;
     }
     __syncthreads();
     if (bkt >= 32) return;
@@ -3592,7 +3597,16 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     int rc = MG_OK;
     DeviceState &d = g->dev;
     const uint32_t L = g->n_levels;
-    auto bytes = [&](uint32_t cap) { return lds_bytes(g->nseg, cap, SPARSE, L, ERR); };
+    auto bytes = [&](uint32_t cap, bool table) { return lds_bytes(g->nseg, cap, table, L, ERR); };
+    // SPARSE (sparse output, or many sources): small boxes keep their few sources as table entries.
+    // Large ones would fill any table with them, mostly after much of their work (20,000 boxes of
+    // a 307x480x300 volume of 3,980 fibres: 90 ms, nearly all of it boxes done once in a table of
+    // 4,096 slots that overflowed and once more in one of 8,192), so they get per-source arrays
+    // wherever those fit the LDS of a workgroup beside a node table of this size.
+    auto by_table = [&](uint32_t cap) {
+        return SPARSE && uint64_t(bytes(cap, false)) + kStaticLds > uint64_t(d.lds_max);
+    };
+    auto level0 = [&](bool table) { A.lt.use16 = (!table && d.maps16) ? 1u : 0u; };  // sources only: 16 bits
     // workgroups of a kernel that are resident together
     auto resident = [&](const void *k, int block, uint32_t dyn, uint32_t *out) -> int {
         int occ = 1;
@@ -3603,9 +3617,13 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     const bool batched = variant == kQueryBatched || variant == kQueryLut;
     if (batched && n <= kDirectMax) {
         // few boxes: no planning launches
-        const auto kdirect = query_direct_kernel<kBlockDirect, 4, SPARSE, ERR>;
-        A.table_cap = d.cfg.table_big ? d.cfg.table_big : SPARSE ? kHashBigSparse : ERR ? kHashBig : kHashDirect;
-        const uint32_t dyn = bytes(A.table_cap);
+        A.table_cap = d.cfg.table_big ? d.cfg.table_big : ERR ? kHashBig : kHashDirect;
+        const bool table = by_table(A.table_cap);
+        if (table && !d.cfg.table_big) A.table_cap = kHashBigSparse;
+        const auto kdirect = table ? query_direct_kernel<kBlockDirect, 4, SPARSE, ERR>
+                                   : query_direct_kernel<kBlockDirect, 4, false, ERR>;
+        const uint32_t dyn = bytes(A.table_cap, table);
+        level0(table);
         uint32_t grid = 0;
         if ((rc = resident(reinterpret_cast<const void *>(kdirect), kBlockDirect, dyn, &grid))) return rc;
         if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
@@ -3617,14 +3635,19 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         HIP_TRY(hipGetLastError());
     } else if (batched) {
         const int bbig = d.cfg.block_big == 256 ? 256 : kBlockBig;    // threads per big-tier box
-        const QueryKernel kbig = bbig == 256 ? tier_kernel<256, true, SPARSE, ERR>(d.cfg.unroll_big)
-                                             : tier_kernel<kBlockBig, true, SPARSE, ERR>(d.cfg.unroll_big);
+        uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : SPARSE ? kHashDirect : kHashBig;
+        const bool table = by_table(cap_big);
+        if (table && !d.cfg.table_big) cap_big = kHashBigSparse;
+        const QueryKernel kbig =
+            table ? (bbig == 256 ? tier_kernel<256, true, SPARSE, ERR>(d.cfg.unroll_big)
+                                 : tier_kernel<kBlockBig, true, SPARSE, ERR>(d.cfg.unroll_big))
+                  : (bbig == 256 ? tier_kernel<256, true, false, ERR>(d.cfg.unroll_big)
+                                 : tier_kernel<kBlockBig, true, false, ERR>(d.cfg.unroll_big));
         const int bsmall = d.cfg.block_small == 256 ? kBlock : 128;  // threads per small-tier box
         const QueryKernel ksmall = bsmall == 128 ? tier_kernel<128, false, SPARSE, ERR>(d.cfg.unroll_small)
                                                  : tier_kernel<kBlock, false, SPARSE, ERR>(d.cfg.unroll_small);
-        const uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : (SPARSE ? kHashBigSparse : kHashBig);
         const uint32_t cap_small = d.cfg.table_small ? d.cfg.table_small : (SPARSE ? kHashSmallSparse : kHashSmall);
-        const uint32_t dyn_big = bytes(cap_big), dyn_small = bytes(cap_small);
+        const uint32_t dyn_big = bytes(cap_big, table), dyn_small = bytes(cap_small, SPARSE);
         uint32_t wbig = 0, wsmall = 0;
         if ((rc = resident(reinterpret_cast<const void *>(kbig), bbig, dyn_big, &wbig)) ||
             (rc = resident(reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &wsmall)))
@@ -3633,13 +3656,15 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         hipLaunchKernelGGL(query_size_kernel, dim3(blocks), dim3(256), 0, s, lt, A.boxes, n, w.work, w.buckets,
                            w.counters, A.sp_total);
         hipLaunchKernelGGL(query_order_kernel, dim3(blocks), dim3(256), 0, s, w.work, n, w.buckets, w.order,
-                           w.counters, w.split, A.n_slots, kMinPartBatch);
+                           w.counters, w.split, A.n_slots, kMinPartBatch, SPARSE ? kBigLog2Sparse : kBigLog2);
         A.order = w.order;
         if ((rc = timing_begin(g, s, err))) return rc;
         A.table_cap = cap_big;
+        level0(table);
         hipLaunchKernelGGL(kbig, dim3(std::min(n + 2 * A.n_slots, wbig)), dim3(bbig), dyn_big, s, A);
         HIP_TRY(hipGetLastError());
         A.table_cap = cap_small;
+        level0(SPARSE);
         A.chunk = d.cfg.chunk_small;
         hipLaunchKernelGGL(ksmall, dim3(std::min(n, wsmall)), dim3(bsmall), dyn_small, s, A);
         HIP_TRY(hipGetLastError());
@@ -3647,29 +3672,32 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         const QueryKernel kplain = query_plain_kernel<SPARSE>;
         A.table_cap = kHashPlain;
         uint32_t all = 0;
-        if ((rc = resident(reinterpret_cast<const void *>(kplain), kBlock, bytes(kHashPlain), &all))) return rc;
+        if ((rc = resident(reinterpret_cast<const void *>(kplain), kBlock, bytes(kHashPlain, SPARSE), &all))) return rc;
         if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
         if ((rc = timing_begin(g, s, err))) return rc;
-        hipLaunchKernelGGL(kplain, dim3(n), dim3(kBlock), bytes(kHashPlain), s, A);
+        level0(SPARSE);
+        hipLaunchKernelGGL(kplain, dim3(n), dim3(kBlock), bytes(kHashPlain, SPARSE), s, A);
         HIP_TRY(hipGetLastError());
     }
     // what overflowed its table: once more with a larger LDS table, then in global memory
-    const QueryKernel kretry = query_retry_kernel<kBlockBig, 4, SPARSE, ERR>;
-    uint32_t cap_retry = d.cfg.table_retry;
-    if (!cap_retry) {  // the largest table up to kHashRetry that fits the LDS of a workgroup
-        uint32_t stat = 0;
-        if ((rc = static_lds(reinterpret_cast<const void *>(kretry), &stat, err))) return rc;
-        cap_retry = kHashRetry;
-        while (cap_retry > kHashBigSparse && uint64_t(bytes(cap_retry)) + stat > uint64_t(d.lds_max)) cap_retry /= 2;
-    }
+    uint32_t cap_retry = d.cfg.table_retry ? d.cfg.table_retry : kHashRetry;
+    if (!d.cfg.table_retry)  // the largest table up to kHashRetry that fits the LDS of a workgroup
+        while (cap_retry > kHashBig && uint64_t(bytes(cap_retry, false)) + kStaticLds > uint64_t(d.lds_max)) cap_retry /= 2;
+    const bool retry_table = by_table(cap_retry);
+    if (retry_table && !d.cfg.table_retry) cap_retry = kHashBigSparse;
+    const QueryKernel kretry = retry_table ? query_retry_kernel<kBlockBig, 4, SPARSE, ERR>
+                                           : query_retry_kernel<kBlockBig, 4, false, ERR>;
+    const uint32_t dyn_retry = bytes(cap_retry, retry_table);
     uint32_t wretry = 0;
-    if ((rc = resident(reinterpret_cast<const void *>(kretry), kBlockBig, bytes(cap_retry), &wretry))) return rc;
+    if ((rc = resident(reinterpret_cast<const void *>(kretry), kBlockBig, dyn_retry, &wretry))) return rc;
     A.table_cap = cap_retry;
+    level0(retry_table);
     // no more workgroups than there can be entries for (a box, or its parts)
-    hipLaunchKernelGGL(kretry, dim3(std::min(wretry, n + 2 * A.n_slots)), dim3(kBlockBig), bytes(cap_retry), s, A);
+    hipLaunchKernelGGL(kretry, dim3(std::min(wretry, n + 2 * A.n_slots)), dim3(kBlockBig), dyn_retry, s, A);
     HIP_TRY(hipGetLastError());
     const auto kfallback = query_fallback_kernel<ERR>;
     const uint32_t dyn_fb = lds_slab_bytes(L);
+    level0(false);  // per-source arrays
     if (w.mid.workers) {
         hipLaunchKernelGGL(kfallback, dim3(w.mid.workers), dim3(kBlock), dyn_fb, s, A, w.mid, 2u, 0u);
         HIP_TRY(hipGetLastError());
@@ -3794,7 +3822,6 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     }
     // sources in LDS arrays while they fit, else as table entries (sparse mode)
     const bool sparse = sp != nullptr || g->nseg > kSegLdsMax;
-    A.lt.use16 = (!sparse && g->dev.maps16) ? 1u : 0u;
     // row runs where the graph has them, for slabs whose rows are long enough
     const uint32_t run_min = g->dev.cfg.run_min_row ? g->dev.cfg.run_min_row : kRunMinRow;
     A.lt.runs_mask = run_min == 0xFFFFFFFFu ? 0u : g->dev.runs_mask;
