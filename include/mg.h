@@ -160,7 +160,8 @@ int mg_segment_ids(const mg_graph *g, uint32_t *out);
  * tensor), so that the library holds no device allocation of its own:
  * mg_device_bytes gives the size of one buffer that holds every array the GPU
  * path reads (the DAG's (a, b, w) triples in node order and in step order, the
- * records of the nodes of rank 1 and 2 by their sources, the rank table, a per-node bound on its mixture's sources, the node-ID maps of
+ * records of the nodes of rank 1 and 2 by their sources, the mixtures of the
+ * nodes of rank >= 3, the rank table, a per-node bound on its mixture's sources, the node-ID maps of
  * every level x fastest and y fastest, and 16-bit copies of level 0 when the
  * sources fit); mg_bind_device fills `d_buf` (device memory on `device`, at
  * least that many bytes, 256-byte aligned) with them, enqueued on `stream`,
@@ -190,8 +191,9 @@ int mg_workspace_init(mg_graph *g, void *d_work, uint64_t work_bytes, void *stre
  *   d_out    device fp32 [n][S]: fraction of each segment's voxels in the
  *            clipped box (counts divided by the box volume in fp64, rounded
  *            to fp32); all zeros for an empty box. Counts from cubes whose
- *            node is a source are exact integers; mass pushed through the DAG
- *            is accumulated in fp32 with compensated (two-sum) updates.
+ *            node is a source, or a node of rank 1 or 2 with exact weights, are
+ *            exact integers; other nodes' voxel counts times their mixtures are
+ *            accumulated in fp32 with compensated (two-sum) updates.
  *   d_work   workspace of mg_workspace_bytes(g, n) bytes, initialised once.
  * Boxes whose nodes overflow the per-box LDS tables are redone with a larger
  * LDS table, then in global-memory tables: first many workers' tables of
@@ -208,7 +210,7 @@ int mg_query_boxes_plain(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float
                          void *d_work, uint64_t work_bytes, void *stream);
 
 /* mg_query_boxes that also reports the work of each box, for roofline
- * accounting: d_stats device uint32 [n][2]. [q][0] = cubes in box q's
+ * accounting (by the rank-by-rank push, one workgroup per box): d_stats device uint32 [n][2]. [q][0] = cubes in box q's
  * footprint. [q][1] bits 0..29 = entries the box's node table held: the
  * distinct internal nodes of rank >= 3 it scattered onto or reached by the
  * push, plus, for graphs with more sources than the LDS source arrays hold,
@@ -379,10 +381,11 @@ typedef struct {
     uint32_t table_small;   /* small-box tier (0: default)                                      */
     uint32_t table_retry;   /* retry of overflowed boxes (0: the largest of 8192 that fits)     */
     uint32_t block_small;   /* threads per box in the small-box tier: 0 (128), 128 or 256       */
-    uint32_t block_big;     /* threads per box in the big-box tier: 0 (512), 256 or 512.
-                               Table sizes are 0 or powers of two in [64, 8192] (0: 2048 big,
-                               256 small with per-source arrays; 4096 and 2048 when sources are
-                               table entries); boxes that overflow every LDS table are answered
+    uint32_t block_big;     /* threads per box in the big-box tier: 0 (256 or 512, by how many
+                               fit a CU), 256 or 512.
+                               Table sizes are 0 or powers of two in [64, 8192] (0: 1024 or 2048
+                               big, 256 small with per-source arrays; 4096 and 2048 when sources
+                               are table entries); boxes that overflow every LDS table are answered
                                from global memory, so smaller tables change speed, never
                                results                                                        */
     uint32_t chunk_small;   /* boxes a small-tier workgroup takes per dequeue from its work

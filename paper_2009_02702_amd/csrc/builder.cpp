@@ -850,6 +850,129 @@ int validate_graph(const Graph &g, std::string *err)
     return MG_OK;
 }
 
+namespace {
+
+// A node's mixture by its sources, in increasing order: a view of a stored row, or, for a node
+// of rank <= 2, the row worked out in place.
+struct RowView {
+    const uint32_t *seg;
+    const double *val;
+    uint32_t n;
+    uint32_t s4[4];
+    double v4[4];
+};
+
+// a wa + b wb, both rows in increasing order of source; returns the entries.
+uint32_t merge_rows(const RowView &a, double wa, const RowView &b, double wb, uint32_t *seg, double *val)
+{
+    uint32_t i = 0, j = 0, k = 0;
+    while (i < a.n && j < b.n) {
+        const uint32_t sa = a.seg[i], sb = b.seg[j];
+        double v = 0.0;
+        if (sa <= sb) v = wa * a.val[i++];
+        if (sb <= sa) v += wb * b.val[j++];
+        seg[k] = std::min(sa, sb);
+        val[k++] = v;
+    }
+    for (; i < a.n; ++i) seg[k] = a.seg[i], val[k++] = wa * a.val[i];
+    for (; j < b.n; ++j) seg[k] = b.seg[j], val[k++] = wb * b.val[j];
+    return k;
+}
+
+// Rows of the nodes of rank >= 3, filled rank by rank.
+struct DeepRows {
+    const Graph &g;
+    const uint32_t first;                // the first such node
+    std::vector<uint32_t> ptr, seg;
+    std::vector<double> val;
+
+    explicit DeepRows(const Graph &gr) : g(gr), first(gr.rank_ptr[3]), ptr(size_t(gr.n_nodes - first) + 1, 0) {}
+
+    // Node n's row; RANK: its rank is at most this (3: any, stored).
+    template <int RANK>
+    void view(uint32_t n, RowView *r) const
+    {
+        if (RANK == 3 && n >= first) {
+            const uint32_t k = n - first;
+            r->seg = seg.data() + ptr[k], r->val = val.data() + ptr[k], r->n = ptr[k + 1] - ptr[k];
+            return;
+        }
+        r->seg = r->s4, r->val = r->v4;
+        if (RANK == 0 || n < g.nseg) {
+            r->n = 1, r->s4[0] = n, r->v4[0] = 1.0;
+            return;
+        }
+        r->n = merge<(RANK == 3 ? 1 : RANK > 0 ? RANK - 1 : 0)>(n, r->s4, r->v4);
+    }
+    // Node n's row from its predecessors' (their rank at most RANK); weights as in build_lut:
+    // exact fractions in fp64. Returns its entries, of which there is room for the sum of both.
+    template <int RANK>
+    uint32_t merge(uint32_t n, uint32_t *s, double *v) const
+    {
+        RowView a, b;
+        view<RANK>(g.child_a[n], &a);
+        view<RANK>(g.child_b[n], &b);
+        const double den = double(g.wden[n]);
+        return merge_rows(a, double(g.wden[n] - g.wnum[n]) / den, b, double(g.wnum[n]) / den, s, v);
+    }
+};
+
+}  // namespace
+
+void ensure_deep(const Graph &g)
+{
+    if (g.deep_ready) return;
+    g.deep_ready = true;
+    g.deep_ptr.clear();
+    g.deep.clear();
+    if (g.depth < 3) {  // no such node
+        g.deep_ptr.assign(1, 0);
+        return;
+    }
+    constexpr uint64_t kMaxEntries = uint64_t(1) << 25;  // 256 MiB; beyond, mass is pushed rank by rank
+    const unsigned nt = resolve_threads(0);
+    DeepRows d(g);
+    struct Part {
+        std::vector<uint32_t> seg, len;
+        std::vector<double> val;
+    };
+    for (uint32_t r = 3; r <= g.depth; ++r) {
+        const uint32_t lo = g.rank_ptr[r], hi = g.rank_ptr[r + 1];
+        std::vector<Part> parts(std::max(1u, nt));
+        parallel_chunks(hi - lo, nt, [&](uint64_t b, uint64_t e, unsigned t) {
+            Part &p = parts[t];
+            p.len.resize(e - b);
+            uint64_t at = 0;
+            for (uint64_t i = b; i < e; ++i) {
+                const uint32_t n = lo + uint32_t(i), ca = g.child_a[n], cb = g.child_b[n];
+                auto bound = [&](uint32_t c) { return c < d.first ? 4u : d.ptr[c - d.first + 1] - d.ptr[c - d.first]; };
+                const uint64_t room = at + bound(ca) + bound(cb);
+                if (room > p.seg.size()) p.seg.resize(2 * room + 1024), p.val.resize(2 * room + 1024);
+                p.len[i - b] = d.merge<3>(n, p.seg.data() + at, p.val.data() + at);
+                at += p.len[i - b];
+            }
+            p.seg.resize(at), p.val.resize(at);
+        });
+        uint32_t k = lo - d.first;
+        uint64_t total = d.ptr[k];
+        for (const Part &p : parts) {
+            total += p.seg.size();
+            if (total > kMaxEntries) return;
+            for (uint32_t len : p.len) d.ptr[k + 1] = d.ptr[k] + len, ++k;
+            d.seg.insert(d.seg.end(), p.seg.begin(), p.seg.end());
+            d.val.insert(d.val.end(), p.val.begin(), p.val.end());
+        }
+    }
+    g.deep.resize(d.seg.size());
+    for (size_t i = 0; i < d.seg.size(); ++i) {
+        const float f = float(d.val[i]);
+        uint32_t bits;
+        std::memcpy(&bits, &f, 4);
+        g.deep[i] = uint64_t(bits) << 32 | d.seg[i];
+    }
+    g.deep_ptr.swap(d.ptr);
+}
+
 // Mixture lookup table (Sec. "Decoder", mixture lookup; used by range queries in
 // Sec. "Range queries"): the mixture of every node over the segments, found by
 // carrying the unit vector of each source through the interpolations in rank

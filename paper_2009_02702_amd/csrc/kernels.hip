@@ -72,10 +72,12 @@ constexpr uint32_t kMinSlots = 16;            // (but hold at least this many bo
 // 65,536 / 131,072: 254 / 174 / 126 / 135 us, whole: 160).
 constexpr uint32_t kMinPart = 4096;
 constexpr uint32_t kMinPartBatch = 1u << 16;
+constexpr uint32_t kMinPartRedo = 1u << 14;   // the same for boxes that overflowed: the others are done
 constexpr uint32_t kDirectMax = 1024;         // boxes of a call answered without a planning launch
 constexpr uint32_t kNoallocSlots = 256;        // the same on the library's static scratch
 constexpr int kBlockDirect = 256;             // workgroup size of that path
-constexpr uint32_t kHashDirect = 1024;        // its LDS hash slots (per-source arrays in LDS)
+constexpr uint32_t kHashDirect = 1024;        // its fewest and most LDS hash slots (per-source arrays in LDS)
+constexpr uint32_t kHashDirectMax = 4096;
 constexpr uint32_t kQueues = 8;                // work queues per tier
 constexpr uint32_t kQueueStride = 64;          // u32 between queue counters (256 bytes)
 constexpr int kGroup = 4;                      // tiles per load group (plain, fallback)
@@ -354,8 +356,10 @@ __device__ inline void build_slabs(const LevelTable &lt, const LevelRow *rows, c
 // code serves both (the compiler resolves the address space after inlining).
 struct QueryState {
     uint32_t *keys;     // [cap] node ID or kEmpty
-    uint32_t *cnt;      // [cap] exact integer counts of source entries (sparse mode)
-    float *hi, *lo;     // [cap] mass and its compensation
+    uint32_t *cnt;      // [cap] exact integer counts: of source entries (sparse mode) and, with
+                        // `counts`, of nodes
+    float *hi, *lo;     // [cap] mass and its compensation (sources in sparse mode, nodes to be pushed)
+    bool counts;        // nodes collect voxel counts, to be expanded by rows; else mass, to be pushed
     uint32_t *used;     // [cap] slots in insertion order
     uint32_t *n_used;   // scalar
     uint32_t *flags;    // scalar: bit 0 = overflow
@@ -381,10 +385,19 @@ struct Leaf {
 };
 static_assert(sizeof(Leaf) == 32, "Leaf must stay 32 bytes");
 
+struct DeepEntry {
+    uint32_t seg;
+    float val;
+};
+
 struct GraphView {
     const NodeTriple *__restrict__ nodes;
     const Leaf *__restrict__ leaf;   // [node - nseg] for the nodes of rank 1 and 2
     const uint64_t *__restrict__ runs;   // the graph's first run: RunLevel::first counts from here
+    // mixtures of the nodes of rank >= 3 by their sources (node n: entries deep_ptr[n - r2_end] ..
+    // deep_ptr[n - r2_end + 1]), or null
+    const uint32_t *__restrict__ deep_ptr;
+    const DeepEntry *__restrict__ deep;
     uint32_t nseg;     // sources are IDs [0, nseg)
     uint32_t r1_end;   // rank-1 nodes are IDs [nseg, r1_end)
     uint32_t r2_end;   // rank-2 nodes are IDs [r1_end, r2_end)
@@ -530,7 +543,9 @@ __device__ inline void scatter_count(const QueryState &st, const GraphView &gv, 
         push_leaf<SPARSE>(st, gv.leaf[node - gv.nseg], h, l);
     } else {
         const uint32_t slot = table_slot(st, node);
-        if (slot != kEmpty) add_mass_at(&st.hi[slot], &st.lo[slot], h, l);
+        if (slot == kEmpty) return;
+        if (st.counts) atomicAdd(&st.cnt[slot], c);
+        else add_mass_at(&st.hi[slot], &st.lo[slot], h, l);
     }
 }
 
@@ -1292,6 +1307,67 @@ __device__ inline void push_mass(const QueryState &st, const GraphView &gv, cons
     }
 }
 
+// Expansion of the table's nodes of rank >= 3: every node adds its voxel count times its
+// mixture row to the sources. The nodes are dealt to the waves; a wave takes the entries of up
+// to 64 nodes' rows as one sequence, one per lane and step (as sum_runs does with runs). One
+// pass of independent additions instead of a pass per rank of the push, each with a table
+// insertion or two per node: the part of a 205,000-cube box that held 147 such nodes pushed for
+// 20,000 cycles. All threads of the block must call.
+template <int BLOCK, bool SPARSE>
+__device__ inline void expand_rows(const QueryState &st, const GraphView &gv)
+{
+    constexpr uint32_t kWaves = BLOCK / 64;
+    const uint32_t nu = uni(ld(st.n_used));
+    if (nu == 0 || (uni(ld(st.flags)) & 1u)) return;
+    const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
+    const uint32_t per = max(8u, (nu + kWaves - 1) / kWaves), n0 = min(nu, wave * per), n1 = min(nu, n0 + per);
+    for (uint32_t b0 = n0; b0 < n1; b0 += 64) {
+        uint32_t c = 0, j0 = 0, len = 0;
+        if (b0 + lane < n1) {
+            const uint32_t slot = ld(&st.used[b0 + lane]), key = ld(&st.keys[slot]);
+            if (key >= gv.r2_end) {  // (sparse mode: sources are entries too)
+                j0 = gv.deep_ptr[key - gv.r2_end];
+                len = gv.deep_ptr[key - gv.r2_end + 1] - j0;
+                c = ld(&st.cnt[slot]);
+            }
+        }
+        uint32_t pos = len;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = uint32_t(__shfl_up(int(pos), off, 64));
+            if (lane >= uint32_t(off)) pos += v;
+        }
+        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(pos), 63));
+        if (total == 0) continue;
+        pos -= len;
+        j0 -= pos;
+        auto from = [](uint32_t v, uint32_t src) {
+            return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
+        };
+        auto fetch = [&](uint32_t s, DeepEntry *e, uint32_t *cc) {
+            const uint32_t x = min(s + lane, total - 1);
+            uint32_t i = 0;
+#pragma unroll
+            for (uint32_t step = 32; step > 0; step >>= 1)
+                if (from(pos, i + step) <= x) i += step;
+            *e = gv.deep[from(j0, i) + x];
+            const uint32_t v = from(c, i);
+            *cc = s + lane < total ? v : 0u;
+        };
+        DeepEntry e, e1;
+        uint32_t cc, cc1;
+        fetch(0, &e, &cc);
+        for (uint32_t s = 0; s < total; s += 64) {
+            fetch(s + 64, &e1, &cc1);  // past the end: the last entry again, not added
+            if (cc) {
+                float ph, pl;
+                scale_pair(e.val, float(cc & 0xFFFFFF00u), float(cc & 0xFFu), &ph, &pl);  // both exact in fp32
+                add_source_mass<SPARSE>(st, e.seg, ph, pl);
+            }
+            e = e1, cc = cc1;
+        }
+    }
+}
+
 // Per-worker tables in global memory: node table and per-source arrays.
 struct GlobalPool {
     uint32_t workers, slots;
@@ -1329,12 +1405,13 @@ struct QueryArgs {
     // boxes that several workgroups share: their parts, and per box the sources' sums so far
     uint32_t n_slots;             // boxes there is room for (0: every box is one workgroup's)
     uint4 *split;                 // [2 n_slots] parts (box, part, parts, slot) of a planned call
-    uint4 *split_over;            // [2 n_slots] parts in list 1 (entry: kPartFlag | index here)
+    uint4 *split_over;            // [4 n_slots] parts in list 1 (entry: kPartFlag | index here)
     uint32_t *slot_done;          // [n_slots] parts finished
     uint32_t *slot_cnt;           // [n_slots][S] exact integer counts
     float *slot_hi, *slot_lo;     // [n_slots][S] mass and its compensation
     uint32_t *stats;              // optional [n][2]: cubes, table entries (graph nodes) touched
-    const uint64_t *lut_ptr;      // mixture lookup table rows: expand instead of push (nullptr: push)
+    uint32_t counts;              // nodes collect counts, expanded by rows; 0: mass, pushed rank by rank
+    const uint64_t *lut_ptr;      // mixture lookup table rows (nullptr: the graph's own rows, or push)
     const uint32_t *lut_seg;
     const float *lut_val;
     const float *lut_err;         // propagated uncertainty of each row entry (uncertainty queries)
@@ -1354,7 +1431,8 @@ enum : uint32_t {
     kCountExit = 9,     // workgroups of the last launch that are done
     kCountSplit = 10,   // parts in `split`
     kCountSlot = 11,    // slots taken
-    kCountSplitOver = 12,  // parts in `split_over`
+    kCountSplitOver = 12,  // parts in the first half of `split_over`
+    kCountRedo = 13,    // parts in its second half: boxes cut up after they overflowed
     kCountTotal = 14,   // cubes of all boxes (64 bits)
 };
 constexpr uint32_t kPartFlag = 0x80000000u;
@@ -1374,7 +1452,8 @@ __device__ inline void expand_lut(const QueryArgs &A, const QueryState &st)
         const uint32_t slot = ld(&st.used[i]);
         const uint32_t key = ld(&st.keys[slot]);
         if (key < A.gv.r1_end) continue;  // a source (sparse mode); rank-1 nodes never enter the table
-        const float mh = ld(&st.hi[slot]), ml = ld(&st.lo[slot]);
+        const uint32_t c = ld(&st.cnt[slot]);
+        const float mh = float(c & 0xFFFFFF00u), ml = float(c & 0xFFu);  // both exact in fp32
         const uint64_t e = A.lut_ptr[key + 1];
         for (uint64_t j = A.lut_ptr[key] + g; j < e; j += kLanes) {
             float ph, pl;
@@ -1391,19 +1470,19 @@ __device__ inline void expand_lut(const QueryArgs &A, const QueryState &st)
 // LDS bytes of the query kernels' dynamic shared memory.
 // Dynamic LDS of the query kernels: per-source arrays (dense mode) and the table,
 // then the slab list (6 per level) at a 16-byte aligned offset.
-__host__ __device__ inline uint32_t lds_state_bytes(uint32_t nseg, uint32_t cap, bool sparse)
+__host__ __device__ inline uint32_t lds_state_bytes(uint32_t nseg, uint32_t cap, bool sparse, bool counts)
 {
-    return ((sparse ? cap * 20u : nseg * 12u + cap * 16u) + 15u) & ~15u;
+    return ((sparse ? cap * 20u : nseg * 12u + cap * (counts ? 12u : 16u)) + 15u) & ~15u;
 }
 // The slab list and its two prefix arrays.
 __host__ __device__ inline uint32_t lds_slab_bytes(uint32_t n_levels)
 {
     return 6u * n_levels * uint32_t(sizeof(Slab)) + 2u * (6u * n_levels + 1u) * 4u;
 }
-__host__ __device__ inline uint32_t lds_bytes(uint32_t nseg, uint32_t cap, bool sparse, uint32_t n_levels,
-                                              bool err = false)
+__host__ __device__ inline uint32_t lds_bytes(uint32_t nseg, uint32_t cap, bool sparse, bool counts,
+                                              uint32_t n_levels, bool err)
 {
-    return lds_state_bytes(nseg, cap, sparse) + lds_slab_bytes(n_levels) + (err ? 4u * nseg : 0u);
+    return lds_state_bytes(nseg, cap, sparse, counts) + lds_slab_bytes(n_levels) + (err ? 4u * nseg : 0u);
 }
 
 struct QueryShared {
@@ -1526,6 +1605,48 @@ __device__ inline void write_failure(const QueryArgs &A, uint32_t q)
     }
 }
 
+// Cubes of a box's footprint, level by level in closed form (below 2^31, the volume's voxels).
+__device__ inline uint32_t box_cubes(const LevelTable &lt, const uint32_t *box)
+{
+    uint32_t lo[3], hi[3], cubes = 0;
+    if (!clip_box(box, lt, lo, hi)) return 0;
+    for (uint32_t l = 0; l < lt.n_levels; ++l) {
+        uint32_t outer = 1, inner = 1;
+        for (int d = 0; d < 3; ++d) {
+            const uint32_t one = 1u << l;  // extents are at most 2^15: no sum leaves 32 bits
+            const uint32_t a = (lo[d] + one - 1) >> l, b = hi[d] >> l;
+            const uint32_t pa = (lo[d] + 2 * one - 1) >> (l + 1), pb = hi[d] >> (l + 1);
+            outer *= b > a ? b - a : 0u;
+            inner *= pb > pa ? 2 * (pb - pa) : 0u;
+        }
+        if (outer == 0) break;  // nothing at coarser levels either
+        cubes += outer - inner;
+    }
+    return cubes;
+}
+
+// Cubes above which a box is split, and the parts it is split into (about that many cubes
+// each): the share of one of `ways` workgroups in all boxes' cubes, so that no workgroup
+// works much longer than the others, but at least `least`. At most `ways` boxes exceed their
+// share, in at most 2 `ways` parts.
+__device__ inline uint32_t part_cubes(uint64_t total, uint32_t ways, uint32_t least)
+{
+    if (ways == 0) return 0xFFFFFFFFu;
+    return uint32_t(max(uint64_t(least), min(total / ways + 1, uint64_t(0xFFFFFFFFu))));
+}
+__device__ inline uint32_t parts_of(uint32_t cubes, uint32_t target)
+{
+    return cubes > target ? (cubes + target - 1) / target : 1u;
+}
+
+// Zeroes what an entry of the table collects.
+template <bool SPARSE>
+__device__ inline void clear_entry(const QueryState &st, uint32_t slot)
+{
+    if (SPARSE || st.counts) st.cnt[slot] = 0;
+    if (SPARSE || !st.counts) st.hi[slot] = 0.f, st.lo[slot] = 0.f;
+}
+
 // One box (parts == 1) or one part of a box that several workgroups share.
 struct Item {
     uint32_t q, part, parts, slot;
@@ -1600,6 +1721,8 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     __syncthreads();
     if (ERR || A.lut_ptr)
         expand_lut<BLOCK, SPARSE, ERR>(A, st);
+    else if (A.counts)
+        expand_rows<BLOCK, SPARSE>(st, A.gv);
     else
         push_mass<BLOCK, SPARSE>(st, A.gv, sh.rank_ptr, A.depth);
     __syncthreads();
@@ -1633,9 +1756,7 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     for (uint32_t i = threadIdx.x; i < nu; i += BLOCK) {
         const uint32_t slot = ld(&st.used[i]);
         st.keys[slot] = kEmpty;
-        st.hi[slot] = 0.f;
-        st.lo[slot] = 0.f;
-        if (SPARSE) st.cnt[slot] = 0;
+        clear_entry<SPARSE>(st, slot);
     }
     if (!SPARSE)
         for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK) {
@@ -1648,23 +1769,42 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     return overflow;
 }
 
-// Hands an item whose table overflowed to the retry launch (list 1). Any thread, once.
-__device__ inline void report_overflow(const QueryArgs &A, const Item &it)
+// Hands an item whose table overflowed to the retry launch (list 1). Any thread, once. A whole
+// box of a planned call is cut into parts there and then (`cubes` of it, while slots last), so
+// that the retry launch does not end with one workgroup redoing a large box on its own.
+__device__ inline void report_overflow(const QueryArgs &A, const Item &it, uint32_t cubes)
 {
-    uint32_t e = it.q;
     if (it.parts > 1) {
         const uint32_t k = atomicAdd(&A.counters[kCountSplitOver], 1u);
         A.split_over[k] = make_uint4(it.q, it.part, it.parts, it.slot);
-        e = kPartFlag | k;
+        A.overflow[atomicAdd(&A.counters[kCountOver], 1u)] = kPartFlag | k;
+        return;
     }
-    A.overflow[atomicAdd(&A.counters[kCountOver], 1u)] = e;
+    const uint32_t parts = cubes ? parts_of(cubes, kMinPartRedo) : 1u;
+    if (parts > 1 && A.n_slots) {
+        // (both counters may pass their limits: then the box stays whole)
+        const uint32_t k = atomicAdd(&A.counters[kCountRedo], parts);
+        if (k < 2 * A.n_slots && parts <= 2 * A.n_slots - k) {
+            const uint32_t slot = atomicAdd(&A.counters[kCountSlot], 1u);
+            if (slot < A.n_slots) {
+                const uint32_t at = atomicAdd(&A.counters[kCountOver], parts), first = 2 * A.n_slots + k;
+                for (uint32_t p = 0; p < parts; ++p) {
+                    A.split_over[first + p] = make_uint4(it.q, p, parts, slot);
+                    A.overflow[at + p] = kPartFlag | (first + p);
+                }
+                return;
+            }
+        }
+    }
+    A.overflow[atomicAdd(&A.counters[kCountOver], 1u)] = it.q;
 }
 
 template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
 __device__ __attribute__((always_inline)) inline void answer(const QueryArgs &A, QueryShared &sh,
-                                                             const QueryState &st, const Item it)
+                                                             const QueryState &st, const Item it, bool planned)
 {
-    if (run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it, false, 0u) && threadIdx.x == 0) report_overflow(A, it);
+    if (run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it, false, 0u) && threadIdx.x == 0)
+        report_overflow(A, it, planned ? box_cubes(A.lt, A.boxes + 6 * uint64_t(it.q)) : 0u);
 }
 
 // The graph's tables every query reads, copied to LDS. The loads are issued together and ahead
@@ -1701,28 +1841,32 @@ __device__ inline void place_slabs(QueryState &st, char *p, uint32_t n_levels)
 
 template <bool SPARSE>
 __device__ inline QueryState lds_state(char *dyn, QueryShared &sh, uint32_t nseg, uint32_t cap, uint32_t n_levels,
-                                      bool err)
+                                      bool counts, bool err)
 {
     QueryState st;
-    place_slabs(st, dyn + lds_state_bytes(nseg, cap, SPARSE), n_levels);
-    st.seg_var = err ? reinterpret_cast<float *>(dyn + lds_state_bytes(nseg, cap, SPARSE) + lds_slab_bytes(n_levels))
-                     : nullptr;
+    char *const slabs = dyn + lds_state_bytes(nseg, cap, SPARSE, counts);
+    place_slabs(st, slabs, n_levels);
+    st.seg_var = err ? reinterpret_cast<float *>(slabs + lds_slab_bytes(n_levels)) : nullptr;
+    st.counts = counts;
     uint32_t *t = reinterpret_cast<uint32_t *>(dyn);
     if (SPARSE) {
         st.seg_cnt = nullptr;
         st.seg_hi = st.seg_lo = nullptr;
+        st.hi = reinterpret_cast<float *>(t + cap);
+        st.lo = reinterpret_cast<float *>(t + 2 * cap);
+        st.used = t + 3 * cap;
         st.cnt = t + 4 * cap;
     } else {
         st.seg_cnt = t;
         st.seg_hi = reinterpret_cast<float *>(t + nseg);
         st.seg_lo = reinterpret_cast<float *>(t + 2 * nseg);
         t += 3 * nseg;
-        st.cnt = nullptr;
+        st.used = t + cap;
+        st.cnt = t + 2 * cap;                       // with `counts`, else
+        st.hi = reinterpret_cast<float *>(t + 2 * cap);
+        st.lo = reinterpret_cast<float *>(t + 3 * cap);
     }
     st.keys = t;
-    st.hi = reinterpret_cast<float *>(t + cap);
-    st.lo = reinterpret_cast<float *>(t + 2 * cap);
-    st.used = t + 3 * cap;
     st.cap = cap;
     st.limit = cap / 4 * 3;
     st.n_used = &sh.n_used;
@@ -1736,9 +1880,7 @@ __device__ inline void clear_lds_state(const QueryState &st, uint32_t nseg)
 {
     for (uint32_t i = threadIdx.x; i < st.cap; i += BLOCK) {
         st.keys[i] = kEmpty;
-        st.hi[i] = 0.f;
-        st.lo[i] = 0.f;
-        if (SPARSE) st.cnt[i] = 0;
+        clear_entry<SPARSE>(st, i);
     }
     if (!SPARSE)
         for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK) {
@@ -1755,45 +1897,11 @@ __global__ __launch_bounds__(kBlock) void query_plain_kernel(QueryArgs A)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
-    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, false);
+    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, A.counts != 0, false);
     GraphTables(A).put(A, sh);
     clear_lds_state<kBlock, SPARSE, false>(st, A.gv.nseg);
     __syncthreads();
-    answer<kBlock, kGroup, SPARSE, false>(A, sh, st, whole_box(blockIdx.x));
-}
-
-// Cubes of a box's footprint, level by level in closed form (below 2^31, the volume's voxels).
-__device__ inline uint32_t box_cubes(const LevelTable &lt, const uint32_t *box)
-{
-    uint32_t lo[3], hi[3], cubes = 0;
-    if (!clip_box(box, lt, lo, hi)) return 0;
-    for (uint32_t l = 0; l < lt.n_levels; ++l) {
-        uint32_t outer = 1, inner = 1;
-        for (int d = 0; d < 3; ++d) {
-            const uint32_t one = 1u << l;  // extents are at most 2^15: no sum leaves 32 bits
-            const uint32_t a = (lo[d] + one - 1) >> l, b = hi[d] >> l;
-            const uint32_t pa = (lo[d] + 2 * one - 1) >> (l + 1), pb = hi[d] >> (l + 1);
-            outer *= b > a ? b - a : 0u;
-            inner *= pb > pa ? 2 * (pb - pa) : 0u;
-        }
-        if (outer == 0) break;  // nothing at coarser levels either
-        cubes += outer - inner;
-    }
-    return cubes;
-}
-
-// Cubes above which a box is split, and the parts it is split into (about that many cubes
-// each): the share of one of `ways` workgroups in all boxes' cubes, so that no workgroup
-// works much longer than the others, but at least `least`. At most `ways` boxes exceed their
-// share, in at most 2 `ways` parts.
-__device__ inline uint32_t part_cubes(uint64_t total, uint32_t ways, uint32_t least)
-{
-    if (ways == 0) return 0xFFFFFFFFu;
-    return uint32_t(max(uint64_t(least), min(total / ways + 1, uint64_t(0xFFFFFFFFu))));
-}
-__device__ inline uint32_t parts_of(uint32_t cubes, uint32_t target)
-{
-    return cubes > target ? (cubes + target - 1) / target : 1u;
+    answer<kBlock, kGroup, SPARSE, false>(A, sh, st, whole_box(blockIdx.x), false);
 }
 
 // Calls of at most kDirectMax boxes, in one launch: every workgroup counts the cubes of all
@@ -1848,7 +1956,7 @@ __global__ __launch_bounds__(BLOCK, 6) void query_direct_kernel(QueryArgs A, uin
     __syncthreads();
     const uint32_t items = uni(first[A.n]) & 0xFFFFu;
     if (blockIdx.x >= items) return;
-    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
+    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, A.counts != 0, ERR);
     tables.put(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
     for (uint32_t i = blockIdx.x; i < items; i += gridDim.x) {
@@ -1858,7 +1966,7 @@ __global__ __launch_bounds__(BLOCK, 6) void query_direct_kernel(QueryArgs A, uin
         q = uni(q);
         const uint32_t f = uni(first[q]), e = uni(first[q + 1]);
         answer<BLOCK, GROUP, SPARSE, ERR>(A, sh, st,
-                                          Item{q, i - (f & 0xFFFFu), (e & 0xFFFFu) - (f & 0xFFFFu), f >> 16});
+                                          Item{q, i - (f & 0xFFFFu), (e & 0xFFFFu) - (f & 0xFFFFu), f >> 16}, false);
     }
 }
 
@@ -1872,7 +1980,7 @@ __global__ __launch_bounds__(BLOCK, 6) void query_tier_kernel(QueryArgs A)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
-    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
+    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, A.counts != 0, ERR);
     GraphTables(A).put(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
     const uint32_t big = uni(A.counters[kCountBig]), n_split = BIG ? uni(A.counters[kCountSplit]) : 0u;
@@ -1911,16 +2019,17 @@ __global__ __launch_bounds__(BLOCK, 6) void query_tier_kernel(QueryArgs A)
                 }
                 it = whole_box(q);
             }
-            answer<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it);
+            answer<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it, true);
         }
     }
 }
 
 // State in worker w's tables of a global pool (slab list in LDS at `slabs`).
 __device__ inline QueryState pool_state(const GlobalPool &p, uint32_t w, char *slabs, QueryShared &sh, uint32_t nseg,
-                                        uint32_t n_levels, bool err)
+                                        uint32_t n_levels, bool counts, bool err)
 {
     QueryState st;
+    st.counts = counts;
     const uint64_t at = uint64_t(w) * p.slots, sat = uint64_t(w) * nseg;
     st.keys = p.keys + at;
     st.cnt = p.cnt + at;
@@ -1940,11 +2049,24 @@ __device__ inline QueryState pool_state(const GlobalPool &p, uint32_t w, char *s
     return st;
 }
 
+// The last workgroup of a call's last launch leaves the lists empty for the next call. Every
+// workgroup of that launch must call, past its last use of the counters.
+__device__ inline void clear_lists(const QueryArgs &A)
+{
+    if (threadIdx.x != 0) return;
+    __threadfence();
+    if (atomicAdd(&A.counters[kCountExit], 1u) + 1u != gridDim.x) return;
+    A.counters[kCountOver] = A.counters[kCountOver2] = A.counters[kCountOver3] = 0;
+    A.counters[kCountRetry] = A.counters[kCountNext2] = A.counters[kCountNext3] = 0;
+    A.counters[kCountExit] = A.counters[kCountSplitOver] = A.counters[kCountRedo] = 0;
+}
+
 // What overflowed its LDS table (list 1; usually nothing, and then every workgroup leaves at
 // once) with the largest LDS table of a workgroup; what overflows again goes to list 2. The
 // first workgroup also clears what the launches before this one counted with.
+// last: no launch follows (the table holds any box of this graph), so it clears the lists too.
 template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
-__global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A)
+__global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A, uint32_t last)
 {
     extern __shared__ __align__(16) char dyn[];
     __shared__ QueryShared sh;
@@ -1958,7 +2080,7 @@ __global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A)
     }
     const uint32_t n_list = uni(A.counters[kCountOver]);  // final: the launches before this one counted it
     if (n_list == 0) return;
-    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, ERR);
+    const QueryState st = lds_state<SPARSE>(dyn, sh, A.gv.nseg, A.table_cap, A.lt.n_levels, A.counts != 0, ERR);
     GraphTables(A).put(A, sh);
     clear_lds_state<BLOCK, SPARSE, ERR>(st, A.gv.nseg);
     for (;;) {
@@ -1971,6 +2093,7 @@ __global__ __launch_bounds__(BLOCK) void query_retry_kernel(QueryArgs A)
             threadIdx.x == 0)
             A.overflow2[atomicAdd(&A.counters[kCountOver2], 1u)] = e;
     }
+    if (last) clear_lists(A);
 }
 
 // What overflowed every LDS table (list 2), with per-worker tables and source arrays in global
@@ -1991,7 +2114,7 @@ __global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A, Glo
     const uint32_t n_list = uni(A.counters[list == 2 ? kCountOver2 : kCountOver3]);
     const uint32_t next = list == 2 ? kCountNext2 : kCountNext3;
     if (n_list) {
-        const QueryState st = pool_state(pool, blockIdx.x, dyn, sh, A.gv.nseg, A.lt.n_levels, ERR);
+        const QueryState st = pool_state(pool, blockIdx.x, dyn, sh, A.gv.nseg, A.lt.n_levels, A.counts != 0, ERR);
         GraphTables(A).put(A, sh);
         __syncthreads();
         for (;;) {
@@ -2005,14 +2128,7 @@ __global__ __launch_bounds__(kBlock) void query_fallback_kernel(QueryArgs A, Glo
                 A.overflow3[atomicAdd(&A.counters[kCountOver3], 1u)] = e;
         }
     }
-    if (last && threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&A.counters[kCountExit], 1u) + 1u == gridDim.x) {  // every workgroup is past its counters
-            A.counters[kCountOver] = A.counters[kCountOver2] = A.counters[kCountOver3] = 0;
-            A.counters[kCountRetry] = A.counters[kCountNext2] = A.counters[kCountNext3] = 0;
-            A.counters[kCountExit] = A.counters[kCountSplitOver] = 0;
-        }
-    }
+    if (last) clear_lists(A);
 }
 
 // Per-block histogram of 32 buckets, merged with one global atomic per
@@ -2591,11 +2707,11 @@ struct Workspace {
     uint32_t *buckets;    // 64 u32
     uint32_t *work;       // [max_boxes] cubes of each box
     uint32_t *order;      // [max_boxes]
-    uint32_t *overflow;   // [max_boxes + 2 n_slots] list 1: boxes and parts whose LDS table overflowed
-    uint32_t *overflow2;  // [max_boxes + 2 n_slots] list 2: overflowed the retry table too
-    uint32_t *overflow3;  // [max_boxes + 2 n_slots] list 3: overflowed a mid-size global table too
+    uint32_t *overflow;   // [max_boxes + 4 n_slots] list 1: boxes and parts whose LDS table overflowed
+    uint32_t *overflow2;  // [max_boxes + 4 n_slots] list 2: overflowed the retry table too
+    uint32_t *overflow3;  // [max_boxes + 4 n_slots] list 3: overflowed a mid-size global table too
     uint32_t n_slots;     // boxes that several workgroups may share
-    uint4 *split, *split_over;      // [2 n_slots] each
+    uint4 *split, *split_over;      // [2 n_slots], [4 n_slots]
     uint32_t *slot_done, *slot_cnt; // [n_slots], [n_slots][S]
     float *slot_hi, *slot_lo;       // [n_slots][S]
     GlobalPool fin;       // tables that hold every node of the graph
@@ -2675,12 +2791,12 @@ Workspace carve(const Graph &g, char *base, uint32_t max_boxes, uint32_t fin_wor
     w.slot_hi = reinterpret_cast<float *>(take(ns * g.nseg * 4));
     w.slot_lo = reinterpret_cast<float *>(take(ns * g.nseg * 4));
     w.split = reinterpret_cast<uint4 *>(take(2 * ns * sizeof(uint4)));
-    w.split_over = reinterpret_cast<uint4 *>(take(2 * ns * sizeof(uint4)));
+    w.split_over = reinterpret_cast<uint4 *>(take(4 * ns * sizeof(uint4)));
     w.work = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
     w.order = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
-    w.overflow = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 2 * ns) * 4));
-    w.overflow2 = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 2 * ns) * 4));
-    w.overflow3 = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 2 * ns) * 4));
+    w.overflow = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 4 * ns) * 4));
+    w.overflow2 = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 4 * ns) * 4));
+    w.overflow3 = reinterpret_cast<uint32_t *>(take((uint64_t(max_boxes) + 4 * ns) * 4));
     w.bytes = off;
     w.max_boxes = max_boxes;
     return w;
@@ -3131,7 +3247,7 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
 // Byte offsets of the graph's device arrays inside one buffer (each 256-byte
 // aligned): what mg_device_bytes sizes and mg_bind_device fills.
 struct DeviceLayout {
-    uint64_t nodes, leaf, sched, rank_ptr, mixlen, maps, maps16;
+    uint64_t nodes, leaf, deep_ptr, deep, sched, rank_ptr, mixlen, maps, maps16;
     uint64_t n16, n16t;   // elements of the two 16-bit level-0 copies (0 if none)
     uint64_t run_table;   // RunLevel [2 n_levels]
     std::vector<uint64_t> run_sk, run_rn;  // per level and orientation: skip, runs
@@ -3154,6 +3270,9 @@ DeviceLayout device_layout(const Graph &g)
     const uint64_t nmap = g.lev_off[g.n_levels];
     L.nodes = take(uint64_t(g.n_nodes) * sizeof(NodeTriple));
     L.leaf = take(uint64_t(rank2_end(g) - g.nseg) * sizeof(Leaf));
+    ensure_deep(g);
+    L.deep_ptr = take(g.deep_ptr.size() * 4);
+    L.deep = take(g.deep.size() * sizeof(DeepEntry));
     L.sched = take(uint64_t(g.n_nodes) * sizeof(SchedNode));
     L.rank_ptr = take(g.rank_ptr.size() * 4);
     L.mixlen = take(uint64_t(g.n_nodes) * 4);
@@ -3300,6 +3419,14 @@ int dev_bind(Graph *g, int device, void *base, uint64_t bytes, hipStream_t s, bo
     d.maps_t = d.maps + nmap;
     d.maps16 = L.n16 ? reinterpret_cast<uint16_t *>(b + L.maps16) : nullptr;
     HIP_TRY(hipMemcpyAsync(d.nodes, nodes.data(), nodes.size() * sizeof(NodeTriple), hipMemcpyHostToDevice, s));
+    static_assert(sizeof(DeepEntry) == sizeof(uint64_t), "entries are staged as 64-bit words");
+    if (!g->deep_ptr.empty()) {
+        d.deep_ptr = reinterpret_cast<uint32_t *>(b + L.deep_ptr);
+        d.deep = b + L.deep;
+        HIP_TRY(hipMemcpyAsync(d.deep_ptr, g->deep_ptr.data(), g->deep_ptr.size() * 4, hipMemcpyHostToDevice, s));
+        if (!g->deep.empty())
+            HIP_TRY(hipMemcpyAsync(d.deep, g->deep.data(), g->deep.size() * 8, hipMemcpyHostToDevice, s));
+    }
     if (const uint32_t n_leaf = rank2_end(*g) - g->nseg) {
         hipLaunchKernelGGL(leaf_kernel, dim3((n_leaf + 255) / 256), dim3(256), 0, s, d.nodes, g->nseg, n_leaf,
                            static_cast<Leaf *>(d.leaf));
@@ -3597,7 +3724,10 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     int rc = MG_OK;
     DeviceState &d = g->dev;
     const uint32_t L = g->n_levels;
-    auto bytes = [&](uint32_t cap, bool table) { return lds_bytes(g->nseg, cap, table, L, ERR); };
+    auto bytes = [&](uint32_t cap, bool table) { return lds_bytes(g->nseg, cap, table, A.counts != 0, L, ERR); };
+    // nodes that can become entries of a box's table: with counts only those its cubes are on
+    const uint32_t n_entries = g->n_nodes - A.gv.r2_end;
+    auto holds_all = [&](uint32_t cap, bool table) { return !table && A.counts && n_entries <= cap / 4 * 3; };
     // SPARSE (sparse output, or many sources): small boxes keep their few sources as table entries.
     // Large ones would fill any table with them, mostly after much of their work (20,000 boxes of
     // a 307x480x300 volume of 3,980 fibres: 90 ms, nearly all of it boxes done once in a table of
@@ -3617,7 +3747,12 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     const bool batched = variant == kQueryBatched || variant == kQueryLut;
     if (batched && n <= kDirectMax) {
         // few boxes: no planning launches
-        A.table_cap = d.cfg.table_big ? d.cfg.table_big : ERR ? kHashBig : kHashDirect;
+        // the default table holds every node that can enter it where a small one does: then no
+        // box can overflow, and no launch has to follow
+        A.table_cap = kHashDirect;
+        while (A.table_cap < kHashDirectMax && !holds_all(A.table_cap, false)) A.table_cap *= 2;
+        if (!holds_all(A.table_cap, false)) A.table_cap = kHashBig;
+        if (d.cfg.table_big) A.table_cap = d.cfg.table_big;
         const bool table = by_table(A.table_cap);
         if (table && !d.cfg.table_big) A.table_cap = kHashBigSparse;
         const auto kdirect = table ? query_direct_kernel<kBlockDirect, 4, SPARSE, ERR>
@@ -3633,25 +3768,43 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         if ((rc = timing_begin(g, s, err))) return rc;
         hipLaunchKernelGGL(kdirect, dim3(std::min(grid, n + 2 * ways)), dim3(kBlockDirect), dyn, s, A, ways, kMinPart);
         HIP_TRY(hipGetLastError());
+        if (holds_all(A.table_cap, table)) return timing_end(g, s, err);
     } else if (batched) {
-        const int bbig = d.cfg.block_big == 256 ? 256 : kBlockBig;    // threads per big-tier box
-        uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : SPARSE ? kHashDirect : kHashBig;
+        // Default table: half the size where the graph has few nodes that can enter it (the largest
+        // boxes hold up to about an eighth of them). 353 segments, 2,624 such nodes, 100,000 boxes:
+        // 1.21 ms with 1,024 slots, 1.48 with 2,048; 591 segments, 9,958 nodes, 20,000 boxes: 755 us
+        // with 1,024 (some boxes overflow), 613 with 2,048.
+        const bool few = A.counts && !ERR && n_entries / 8 <= kHashDirect / 4 * 3;
+        uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : few ? kHashDirect : kHashBig;
         const bool table = by_table(cap_big);
         if (table && !d.cfg.table_big) cap_big = kHashBigSparse;
-        const QueryKernel kbig =
-            table ? (bbig == 256 ? tier_kernel<256, true, SPARSE, ERR>(d.cfg.unroll_big)
-                                 : tier_kernel<kBlockBig, true, SPARSE, ERR>(d.cfg.unroll_big))
-                  : (bbig == 256 ? tier_kernel<256, true, false, ERR>(d.cfg.unroll_big)
-                                 : tier_kernel<kBlockBig, true, false, ERR>(d.cfg.unroll_big));
+        const uint32_t dyn_big = bytes(cap_big, table);
+        auto big = [&](int block) {
+            return table ? (block == 256 ? tier_kernel<256, true, SPARSE, ERR>(d.cfg.unroll_big)
+                                         : tier_kernel<kBlockBig, true, SPARSE, ERR>(d.cfg.unroll_big))
+                         : (block == 256 ? tier_kernel<256, true, false, ERR>(d.cfg.unroll_big)
+                                         : tier_kernel<kBlockBig, true, false, ERR>(d.cfg.unroll_big));
+        };
+        // Threads per big-tier box: the choice that keeps more waves resident beside the per-box
+        // LDS, and of two equal ones the smaller workgroup (100,000 boxes of 512^3, 353 segments, 24
+        // waves per CU both: 1.21 ms with 256 threads, 1.40 with 512; 20,000 boxes of 591 segments,
+        // 16 and 24 waves: 729 and 613 us). Batches of few boxes per workgroup take the larger one,
+        // whose boxes end sooner (5,000 boxes of 199x181x163: 142 us with 256, 116 with 512).
+        uint32_t wbig = 0, w512 = 0;
+        int bbig = d.cfg.block_big ? int(d.cfg.block_big) : 256;
+        if ((rc = resident(reinterpret_cast<const void *>(big(bbig)), bbig, dyn_big, &wbig))) return rc;
+        if (!d.cfg.block_big && uint64_t(dyn_big) + kStaticLds <= uint64_t(d.lds_max)) {
+            if ((rc = resident(reinterpret_cast<const void *>(big(kBlockBig)), kBlockBig, dyn_big, &w512))) return rc;
+            if (2 * w512 > wbig || n < 8 * wbig) bbig = kBlockBig, wbig = w512;
+        }
+        const QueryKernel kbig = big(bbig);
         const int bsmall = d.cfg.block_small == 256 ? kBlock : 128;  // threads per small-tier box
         const QueryKernel ksmall = bsmall == 128 ? tier_kernel<128, false, SPARSE, ERR>(d.cfg.unroll_small)
                                                  : tier_kernel<kBlock, false, SPARSE, ERR>(d.cfg.unroll_small);
         const uint32_t cap_small = d.cfg.table_small ? d.cfg.table_small : (SPARSE ? kHashSmallSparse : kHashSmall);
-        const uint32_t dyn_big = bytes(cap_big, table), dyn_small = bytes(cap_small, SPARSE);
-        uint32_t wbig = 0, wsmall = 0;
-        if ((rc = resident(reinterpret_cast<const void *>(kbig), bbig, dyn_big, &wbig)) ||
-            (rc = resident(reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &wsmall)))
-            return rc;
+        const uint32_t dyn_small = bytes(cap_small, SPARSE);
+        uint32_t wsmall = 0;
+        if ((rc = resident(reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &wsmall))) return rc;
         const uint32_t blocks = (n + 255) / 256;
         hipLaunchKernelGGL(query_size_kernel, dim3(blocks), dim3(256), 0, s, lt, A.boxes, n, w.work, w.buckets,
                            w.counters, A.sp_total);
@@ -3685,7 +3838,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         while (cap_retry > kHashBig && uint64_t(bytes(cap_retry, false)) + kStaticLds > uint64_t(d.lds_max)) cap_retry /= 2;
     const bool retry_table = by_table(cap_retry);
     if (retry_table && !d.cfg.table_retry) cap_retry = kHashBigSparse;
-    const QueryKernel kretry = retry_table ? query_retry_kernel<kBlockBig, 4, SPARSE, ERR>
+    const auto kretry = retry_table ? query_retry_kernel<kBlockBig, 4, SPARSE, ERR>
                                            : query_retry_kernel<kBlockBig, 4, false, ERR>;
     const uint32_t dyn_retry = bytes(cap_retry, retry_table);
     uint32_t wretry = 0;
@@ -3693,8 +3846,11 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     A.table_cap = cap_retry;
     level0(retry_table);
     // no more workgroups than there can be entries for (a box, or its parts)
-    hipLaunchKernelGGL(kretry, dim3(std::min(wretry, n + 2 * A.n_slots)), dim3(kBlockBig), dyn_retry, s, A);
+    const bool last = holds_all(cap_retry, retry_table);
+    hipLaunchKernelGGL(kretry, dim3(std::min(wretry, n + 4 * A.n_slots)), dim3(kBlockBig), dyn_retry, s, A,
+                       last ? 1u : 0u);
     HIP_TRY(hipGetLastError());
+    if (last) return timing_end(g, s, err);
     const auto kfallback = query_fallback_kernel<ERR>;
     const uint32_t dyn_fb = lds_slab_bytes(L);
     level0(false);  // per-source arrays
@@ -3774,6 +3930,8 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     A.gv.nseg = g->nseg;
     A.gv.leaf = reinterpret_cast<const Leaf *>(g->dev.leaf);
     A.gv.runs = g->dev.runs;
+    A.gv.deep_ptr = g->dev.deep_ptr;
+    A.gv.deep = static_cast<const DeepEntry *>(g->dev.deep);
     A.gv.r1_end = rank1_end(*g);
     A.gv.r2_end = rank2_end(*g);
     A.rank_ptr = g->dev.rank_ptr;
@@ -3820,6 +3978,10 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
         A.gv.r1_end = A.gv.r2_end = g->nseg;
         variant = kQueryLut;
     }
+    // Nodes of rank >= 3 are expanded by the graph's rows of them, or those of the lookup table;
+    // without rows, and where the nodes a box reaches are reported, mass is pushed instead.
+    if (A.lut_ptr && A.gv.deep_ptr && !A.out_err) A.lut_ptr = nullptr;  // the same mixtures, only the ones needed
+    A.counts = A.lut_ptr || (A.gv.deep_ptr && !stats) ? 1u : 0u;
     // sources in LDS arrays while they fit, else as table entries (sparse mode)
     const bool sparse = sp != nullptr || g->nseg > kSegLdsMax;
     // row runs where the graph has them, for slabs whose rows are long enough

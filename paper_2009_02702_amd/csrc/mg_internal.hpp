@@ -33,6 +33,8 @@ struct DeviceState {
     bool owned = false;            // base was allocated by mg_upload (else bound by the caller)
     NodeTriple *nodes = nullptr;   // [n_nodes]
     void *leaf = nullptr;          // records of the nodes of rank 1 and 2 (Leaf)
+    uint32_t *deep_ptr = nullptr;  // mixture rows of the nodes of rank >= 3 (null: none are kept)
+    void *deep = nullptr;          // their entries (DeepEntry)
     uint32_t *mixlen = nullptr;    // [n_nodes] bound on the sources in each node's mixture
     uint32_t *rank_ptr = nullptr;  // [depth + 2]
     SchedNode *sched = nullptr;    // [n_nodes] in step order
@@ -108,12 +110,20 @@ struct Graph {
     // the host maps on first use (ensure_runs), a cache of the graph's own data
     mutable std::vector<LevelRuns> runs;
     mutable bool runs_ready = false;
+    // mixtures of the nodes of rank >= 3 by their sources: entries deep_ptr[k] .. deep_ptr[k + 1]
+    // of the k-th such node, fp32 fraction << 32 | source; derived on first use (ensure_deep),
+    // empty where they would be too many
+    mutable std::vector<uint32_t> deep_ptr;
+    mutable std::vector<uint64_t> deep;
+    mutable bool deep_ready = false;
     DeviceState dev;
 };
 
 // Fills g.runs from the host maps once (no runs for graphs whose maps are only on
 // the device). Not safe against a concurrent first call on the same graph.
 void ensure_runs(const Graph &g);
+// Fills g.deep_ptr and g.deep from the DAG once (builder.cpp). The same restriction.
+void ensure_deep(const Graph &g);
 
 // A DAG in creation order (children before parents; sources 0 .. nseg-1 have
 // a = b = n): what finalize_dag turns into a Graph's node arrays.
