@@ -630,9 +630,9 @@ void weight_fraction(float c, uint64_t *num, uint64_t *den)
 {
     int e = 0;
     const float fr = std::frexp(c, &e);  // c = fr 2^e, fr in [1/2, 1)
-    uint64_t n = uint64_t(std::ldexp(double(fr), 24)), d = uint64_t(1) << (24 - e);
-    while (n % 2 == 0 && d > 1) n /= 2, d /= 2;
-    *num = n, *den = d;
+    const uint64_t n = uint64_t(std::ldexp(double(fr), 24));
+    const int bits = 24 - e, twos = std::min(bits, n ? int(__builtin_ctzll(n)) : bits);  // common factors
+    *num = n >> twos, *den = uint64_t(1) << (bits - twos);
 }
 
 // Scalar quantization of the interpolation weights (Sec. "Compression": the

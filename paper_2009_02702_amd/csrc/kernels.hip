@@ -3331,16 +3331,16 @@ int decode_stream_maps(Graph *g, const StreamSrc &src, hipStream_t s, std::strin
     // every field lies in the staged words; one zero word past the last field
     const uint64_t words = (lead + bits + 31) / 32 + 1;
     const uint64_t avail = src.size > first_byte ? std::min<uint64_t>(src.size - first_byte, words * 4) : 0;
-    void *stage = nullptr, *perm = nullptr, *bad = nullptr;
-    const uint64_t perm_bytes = std::max<uint64_t>(sm.perm.size(), 1) * 4;
-    if (hipMalloc(&stage, words * 4) != hipSuccess || hipMalloc(&perm, perm_bytes) != hipSuccess ||
-        hipMalloc(&bad, 4) != hipSuccess) {
+    // one allocation for the staged words, the renumbering and the error flag
+    void *block = nullptr;
+    const uint64_t perm_at = align256(words * 4), bad_at = perm_at + align256(sm.perm.size() * 4);
+    if (hipMalloc(&block, bad_at + 4) != hipSuccess) {
         (void)hipGetLastError();
-        if (stage) (void)hipFree(stage);
-        if (perm) (void)hipFree(perm);
         *err = "device allocation for decoding the graph stream failed";
         return MG_ENOMEM;
     }
+    void *const stage = block, *const perm = static_cast<char *>(block) + perm_at,
+                *const bad = static_cast<char *>(block) + bad_at;
     int rc = MG_OK;
     uint32_t flag = 0;
     auto run = [&]() -> int {
@@ -3368,9 +3368,7 @@ int decode_stream_maps(Graph *g, const StreamSrc &src, hipStream_t s, std::strin
         return MG_OK;
     };
     rc = run();
-    (void)hipFree(stage);
-    (void)hipFree(perm);
-    (void)hipFree(bad);
+    (void)hipFree(block);
     if (rc) return rc;
     if (flag) {
         *err = "graph stream: voxel node ID out of range";

@@ -64,7 +64,15 @@ class BitReader {
     bool get(uint32_t bits, uint64_t *v)
     {
         if (bits > nbits_ - std::min(pos_, nbits_)) return false;
+        const uint64_t at = pos_ >> 3;
+        const uint32_t shift = uint32_t(pos_ & 7);
         uint64_t r = 0;
+        if (bits <= 56 && at + 8 <= nbits_ / 8) {  // one little-endian word holds the field
+            std::memcpy(&r, p_ + at, 8);
+            *v = (r >> shift) & ((uint64_t(1) << bits) - 1);
+            pos_ += bits;
+            return true;
+        }
         for (uint32_t i = 0; i < bits;) {
             const uint32_t bit = uint32_t(pos_ & 7), take = std::min(8 - bit, bits - i);
             r |= uint64_t((p_[pos_ >> 3] >> bit) & ((1u << take) - 1)) << i;
@@ -266,15 +274,24 @@ int unpack_graph(const uint8_t *buf, uint64_t size, uint32_t threads, Graph *g, 
         d.a.push_back(s), d.b.push_back(s), d.wn.push_back(0), d.wd.push_back(1), d.mix.push_back(1);
         d.alpha.push_back(0.f), d.sigma.push_back(0.f), d.code.push_back(0);
     }
+    // weights of the codewords, stored with w <= 1/2 (exact in fp32)
+    std::vector<float> wc(B);
+    std::vector<uint64_t> wnum(B, 0), wden(B, 1);
+    for (uint32_t k = 0; k < B; ++k) {
+        wc[k] = cw[k] > 0.5f ? 1.0f - cw[k] : cw[k];
+        weight_fraction(wc[k], &wnum[k], &wden[k]);
+    }
+    for (auto *p : {&d.a, &d.b, &d.mix, &d.code}) p->resize(N);
+    for (auto *p : {&d.wn, &d.wd}) p->resize(N);
+    for (auto *p : {&d.alpha, &d.sigma}) p->resize(N);
     for (uint64_t j = 0; j < n_int; ++j) {
-        uint32_t x = first[j], y = second[j];
-        float c = cw[code[j]];
-        if (c > 0.5f) std::swap(x, y), c = 1.0f - c;  // stored with w <= 1/2 (exact in fp32)
-        uint64_t num = 0, den = 1;
-        weight_fraction(c, &num, &den);
-        d.a.push_back(x), d.b.push_back(y), d.wn.push_back(num), d.wd.push_back(den);
-        d.mix.push_back(d.mix[x] + d.mix[y]);
-        d.alpha.push_back(c), d.sigma.push_back(sg[code[j]]), d.code.push_back(code[j]);
+        const uint64_t n = S + j;
+        const uint32_t k = code[j];
+        const bool swap = cw[k] > 0.5f;
+        d.a[n] = swap ? second[j] : first[j], d.b[n] = swap ? first[j] : second[j];
+        d.wn[n] = wnum[k], d.wd[n] = wden[k];
+        d.mix[n] = d.mix[first[j]] + d.mix[second[j]];
+        d.alpha[n] = wc[k], d.sigma[n] = sg[k], d.code[n] = k;
     }
     g->nseg = S;
     if (int rc = finalize_dag(d, true, 0, resolve_threads(threads), g, err, dev ? &dev->perm : nullptr)) return rc;
