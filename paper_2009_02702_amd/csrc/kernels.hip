@@ -44,6 +44,11 @@ constexpr int kMaxSlabs = 6 * kMaxLevelsDev;
 constexpr uint32_t kHashPlain = 2048;         // per-box hash slots in LDS, plain kernel
 constexpr uint32_t kHashSmall = 256;          // small-box tier (per-source arrays in LDS)
 constexpr uint32_t kHashBig = 2048;           // big-box tier (per-source arrays in LDS)
+// Uncertainty queries: nodes of every rank are entries. 10,000 boxes of 256^3 (353 segments, 7.9
+// thousand nodes): 638 us with tables of 256 and 2,048 slots (a tenth of the boxes done twice),
+// 603 with 512 and 2,048, 472 with 512 and 4,096, 516 with 1,024 and 4,096, 490 with 512 and 8,192.
+constexpr uint32_t kHashSmallErr = 512;
+constexpr uint32_t kHashBigErr = 4096;
 constexpr uint32_t kHashSmallSparse = 2048;   // small-box tier, sources as table entries
 constexpr uint32_t kHashBigSparse = 4096;     // big-box tier, sources as table entries
 constexpr uint32_t kHashRetry = 8192;         // boxes that overflowed a tier table
@@ -73,6 +78,11 @@ constexpr uint32_t kMinSlots = 16;            // (but hold at least this many bo
 constexpr uint32_t kMinPart = 4096;
 constexpr uint32_t kMinPartBatch = 1u << 16;
 constexpr uint32_t kMinPartRedo = 1u << 14;   // the same for boxes that overflowed: the others are done
+// Uncertainty queries: classes of the nodes of a large box that overflowed its table, each taken
+// by a workgroup that reads all its cubes (10,000 boxes of 256^3: 0.47 ms; with such boxes redone
+// whole, mostly in tables in global memory in the end: 1.03). Boxes of the small tier fit the
+// larger LDS table whole.
+constexpr uint32_t kClassesRedo = 4;
 constexpr uint32_t kDirectMax = 1024;         // boxes of a call answered without a planning launch
 constexpr uint32_t kNoallocSlots = 256;        // the same on the library's static scratch
 constexpr int kBlockDirect = 256;             // workgroup size of that path
@@ -371,6 +381,7 @@ struct QueryState {
     Slab *slabs;        // [6 * levels] the box's slabs (LDS)
     uint32_t *tile0, *item0;  // [6 * levels + 1] tiles and run items before each slab (LDS)
     float *seg_var;     // [S] accumulated variance per source (uncertainty queries), or null
+    uint32_t cls, n_cls;  // only nodes of class cls of n_cls (a power of two) count; 1: every node
 };
 
 // A node of rank 1 or 2 by its sources: (1 - w) of it goes to the a side, w to the b side;
@@ -421,6 +432,10 @@ __device__ inline uint32_t hash_node(uint32_t k)
     k ^= k >> 16;
     return k;
 }
+
+// Class of a node where a box's nodes are dealt to several workgroups (by bits of the hash
+// that the table's slots do not use).
+__device__ inline uint32_t node_class(uint32_t key, uint32_t n_cls) { return (hash_node(key) >> 24) & (n_cls - 1); }
 
 // Slot of node `key`, inserting it if absent. Returns kEmpty on overflow.
 __device__ inline uint32_t table_slot(const QueryState &st, uint32_t key)
@@ -538,6 +553,7 @@ __device__ inline void scatter_count(const QueryState &st, const GraphView &gv, 
         add_source_count<SPARSE>(st, node, c);
         return;
     }
+    if (st.n_cls > 1 && node_class(node, st.n_cls) != st.cls) return;
     const float h = float(c & 0xFFFFFF00u), l = float(c & 0xFFu);  // both exact in fp32
     if (node < gv.r2_end) {
         push_leaf<SPARSE>(st, gv.leaf[node - gv.nseg], h, l);
@@ -1307,14 +1323,53 @@ __device__ inline void push_mass(const QueryState &st, const GraphView &gv, cons
     }
 }
 
-// Expansion of the table's nodes of rank >= 3: every node adds its voxel count times its
+// Mixture rows of the table's nodes: the graph's own of its nodes of rank >= 3 ...
+struct DeepRows {
+    typedef uint32_t Pos;
+    typedef DeepEntry Entry;
+    const uint32_t *__restrict__ ptr;
+    const DeepEntry *__restrict__ row;
+    uint32_t first;  // the first node that has one
+    __device__ DeepRows(const GraphView &gv) : ptr(gv.deep_ptr), row(gv.deep), first(gv.r2_end) {}
+    __device__ Pos begin(uint32_t node) const { return ptr[node - first]; }
+    __device__ Entry entry(Pos j) const { return row[j]; }
+};
+// ... or the mixture lookup table's, of every node, with the uncertainties of a quantized graph.
+template <bool ERR>
+struct LutRows {
+    typedef uint64_t Pos;
+    struct Entry {
+        uint32_t seg;
+        float val, err;
+    };
+    const uint64_t *__restrict__ ptr;
+    const uint32_t *__restrict__ seg;
+    const float *__restrict__ val, *__restrict__ dev;
+    uint32_t first;  // (with ERR r1_end is nseg: nodes of every rank enter the table)
+    __device__ LutRows(const uint64_t *p, const uint32_t *s, const float *v, const float *e, const GraphView &gv)
+        : ptr(p), seg(s), val(v), dev(e), first(gv.r1_end)
+    {
+    }
+    __device__ Pos begin(uint32_t node) const { return ptr[node]; }
+    __device__ Entry entry(Pos j) const { return Entry{seg[j], val[j], ERR ? dev[j] : 0.f}; }
+};
+__device__ inline uint32_t row_bpermute(uint32_t v, uint32_t src)
+{
+    return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
+}
+__device__ inline uint64_t row_bpermute(uint64_t v, uint32_t src)
+{
+    return row_bpermute(uint32_t(v), src) | uint64_t(row_bpermute(uint32_t(v >> 32), src)) << 32;
+}
+
+// Expansion of the table's nodes: every node adds its voxel count times its
 // mixture row to the sources. The nodes are dealt to the waves; a wave takes the entries of up
 // to 64 nodes' rows as one sequence, one per lane and step (as sum_runs does with runs). One
 // pass of independent additions instead of a pass per rank of the push, each with a table
 // insertion or two per node: the part of a 205,000-cube box that held 147 such nodes pushed for
 // 20,000 cycles. All threads of the block must call.
-template <int BLOCK, bool SPARSE>
-__device__ inline void expand_rows(const QueryState &st, const GraphView &gv)
+template <int BLOCK, bool SPARSE, bool ERR, class ROWS>
+__device__ inline void expand_rows(const QueryState &st, const ROWS &rows)
 {
     constexpr uint32_t kWaves = BLOCK / 64;
     const uint32_t nu = uni(ld(st.n_used));
@@ -1322,12 +1377,13 @@ __device__ inline void expand_rows(const QueryState &st, const GraphView &gv)
     const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
     const uint32_t per = max(8u, (nu + kWaves - 1) / kWaves), n0 = min(nu, wave * per), n1 = min(nu, n0 + per);
     for (uint32_t b0 = n0; b0 < n1; b0 += 64) {
-        uint32_t c = 0, j0 = 0, len = 0;
+        uint32_t c = 0, len = 0;
+        typename ROWS::Pos j0 = 0;
         if (b0 + lane < n1) {
             const uint32_t slot = ld(&st.used[b0 + lane]), key = ld(&st.keys[slot]);
-            if (key >= gv.r2_end) {  // (sparse mode: sources are entries too)
-                j0 = gv.deep_ptr[key - gv.r2_end];
-                len = gv.deep_ptr[key - gv.r2_end + 1] - j0;
+            if (key >= rows.first) {  // (sparse mode: sources are entries too)
+                j0 = rows.begin(key);
+                len = uint32_t(rows.begin(key + 1) - j0);
                 c = ld(&st.cnt[slot]);
             }
         }
@@ -1340,28 +1396,30 @@ __device__ inline void expand_rows(const QueryState &st, const GraphView &gv)
         if (total == 0) continue;
         pos -= len;
         j0 -= pos;
-        auto from = [](uint32_t v, uint32_t src) {
-            return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
-        };
-        auto fetch = [&](uint32_t s, DeepEntry *e, uint32_t *cc) {
+        auto fetch = [&](uint32_t s, typename ROWS::Entry *e, uint32_t *cc) {
             const uint32_t x = min(s + lane, total - 1);
             uint32_t i = 0;
 #pragma unroll
             for (uint32_t step = 32; step > 0; step >>= 1)
-                if (from(pos, i + step) <= x) i += step;
-            *e = gv.deep[from(j0, i) + x];
-            const uint32_t v = from(c, i);
+                if (row_bpermute(pos, i + step) <= x) i += step;
+            *e = rows.entry(row_bpermute(j0, i) + x);
+            const uint32_t v = row_bpermute(c, i);
             *cc = s + lane < total ? v : 0u;
         };
-        DeepEntry e, e1;
+        typename ROWS::Entry e, e1;
         uint32_t cc, cc1;
         fetch(0, &e, &cc);
         for (uint32_t s = 0; s < total; s += 64) {
             fetch(s + 64, &e1, &cc1);  // past the end: the last entry again, not added
             if (cc) {
+                const float mh = float(cc & 0xFFFFFF00u), ml = float(cc & 0xFFu);  // both exact in fp32
                 float ph, pl;
-                scale_pair(e.val, float(cc & 0xFFFFFF00u), float(cc & 0xFFu), &ph, &pl);  // both exact in fp32
+                scale_pair(e.val, mh, ml, &ph, &pl);
                 add_source_mass<SPARSE>(st, e.seg, ph, pl);
+                if constexpr (ERR) {
+                    const float d = (mh + ml) * e.err;
+                    atomicAdd(&st.seg_var[e.seg], d * d);
+                }
             }
             e = e1, cc = cc1;
         }
@@ -1409,6 +1467,7 @@ struct QueryArgs {
     uint32_t *slot_done;          // [n_slots] parts finished
     uint32_t *slot_cnt;           // [n_slots][S] exact integer counts
     float *slot_hi, *slot_lo;     // [n_slots][S] mass and its compensation
+    float *slot_var;              // [n_slots][S] variance (uncertainty queries)
     uint32_t *stats;              // optional [n][2]: cubes, table entries (graph nodes) touched
     uint32_t counts;              // nodes collect counts, expanded by rows; 0: mass, pushed rank by rank
     const uint64_t *lut_ptr;      // mixture lookup table rows (nullptr: the graph's own rows, or push)
@@ -1436,36 +1495,6 @@ enum : uint32_t {
     kCountTotal = 14,   // cubes of all boxes (64 bits)
 };
 constexpr uint32_t kPartFlag = 0x80000000u;
-
-// Mixture lookup expansion (the paper's query through per-node mixtures):
-// every graph node in the table adds its mass times its mixture row to the
-// sources. Groups of 8 lanes take one node each, lanes over the row's entries.
-// Replaces the rank-by-rank push; all threads of the block must call.
-template <int BLOCK, bool SPARSE, bool ERR>
-__device__ inline void expand_lut(const QueryArgs &A, const QueryState &st)
-{
-    constexpr uint32_t kLanes = 8;
-    const uint32_t nu = ld(st.n_used);
-    if (nu == 0 || (ld(st.flags) & 1u)) return;  // uniform
-    const uint32_t g = threadIdx.x & (kLanes - 1);
-    for (uint32_t i = threadIdx.x / kLanes; i < nu; i += BLOCK / kLanes) {
-        const uint32_t slot = ld(&st.used[i]);
-        const uint32_t key = ld(&st.keys[slot]);
-        if (key < A.gv.r1_end) continue;  // a source (sparse mode); rank-1 nodes never enter the table
-        const uint32_t c = ld(&st.cnt[slot]);
-        const float mh = float(c & 0xFFFFFF00u), ml = float(c & 0xFFu);  // both exact in fp32
-        const uint64_t e = A.lut_ptr[key + 1];
-        for (uint64_t j = A.lut_ptr[key] + g; j < e; j += kLanes) {
-            float ph, pl;
-            scale_pair(A.lut_val[j], mh, ml, &ph, &pl);
-            add_source_mass<SPARSE>(st, A.lut_seg[j], ph, pl);
-            if (ERR) {  // uncertainty: the node's count times its row's, added in quadrature
-                const float d = (mh + ml) * A.lut_err[j];
-                atomicAdd(&st.seg_var[A.lut_seg[j]], d * d);
-            }
-        }
-    }
-}
 
 // LDS bytes of the query kernels' dynamic shared memory.
 // Dynamic LDS of the query kernels: per-source arrays (dense mode) and the table,
@@ -1664,7 +1693,7 @@ __device__ inline Item listed_item(const QueryArgs &A, uint32_t e)
 
 // Adds the sources of this workgroup's part to its box's sums. Returns true in the workgroup
 // that finished the box's last part: its sums are then complete. Every thread must call.
-template <int BLOCK, bool SPARSE>
+template <int BLOCK, bool SPARSE, bool ERR>
 __device__ inline bool merge_part(const QueryArgs &A, QueryShared &sh, const QueryState &st, const Item &it)
 {
     const uint64_t at = uint64_t(it.slot) * A.gv.nseg;
@@ -1679,8 +1708,14 @@ __device__ inline bool merge_part(const QueryArgs &A, QueryShared &sh, const Que
             if (key < A.gv.nseg) add(key, ld(&st.cnt[slot]), ld(&st.hi[slot]), ld(&st.lo[slot]));
         }
     } else {
-        for (uint32_t s = threadIdx.x; s < A.gv.nseg; s += BLOCK)
-            add(s, ld(&st.seg_cnt[s]), ld(&st.seg_hi[s]), ld(&st.seg_lo[s]));
+        for (uint32_t s = threadIdx.x; s < A.gv.nseg; s += BLOCK) {
+            // (with ERR every part counted the cubes on sources)
+            add(s, ERR && it.part ? 0u : ld(&st.seg_cnt[s]), ld(&st.seg_hi[s]), ld(&st.seg_lo[s]));
+            if (ERR) {
+                const float v = ld(&st.seg_var[s]);
+                if (v != 0.0f) atomicAdd(&A.slot_var[at + s], v);
+            }
+        }
     }
     __threadfence();
     __syncthreads();
@@ -1696,11 +1731,15 @@ __device__ inline bool merge_part(const QueryArgs &A, QueryShared &sh, const Que
 // tag: OR-ed into the box's stats (which launch answered it). Returns true where the table
 // overflowed: nothing was written then, or, with `fail`, the box is marked as failed.
 // (always inlined: each query kernel is one function, whatever the inliner's size limit)
+// Parts of a box: ranges of its cubes; with ERR, where every node's count has to meet its row
+// whole (uncertainties add in quadrature), classes of its nodes, each part reading all cubes.
 template <int BLOCK, int GROUP, bool SPARSE, bool ERR>
 __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs &A, QueryShared &sh,
-                                                                const QueryState &st, const Item it, bool fail,
+                                                                const QueryState &state, const Item it, bool fail,
                                                                 uint32_t tag)
 {
+    QueryState st = state;
+    if (ERR) st.cls = uni(it.part), st.n_cls = uni(it.parts);
     const uint32_t q = uni(it.q);
     uint32_t lo[3], hi[3];
     const bool nonempty = clip_box(A.boxes + 6 * uint64_t(q), A.lt, lo, hi);
@@ -1717,12 +1756,12 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     if (n_slabs)
         scatter_box<BLOCK, GROUP, SPARSE>(reinterpret_cast<const char *>(A.maps),
                                           reinterpret_cast<const char *>(A.maps16), sh.runs, sh.rows, st, A.gv,
-                                          n_slabs, uni(it.part), uni(it.parts), &sh.flags);
+                                          n_slabs, ERR ? 0u : uni(it.part), ERR ? 1u : uni(it.parts), &sh.flags);
     __syncthreads();
     if (ERR || A.lut_ptr)
-        expand_lut<BLOCK, SPARSE, ERR>(A, st);
+        expand_rows<BLOCK, SPARSE, ERR>(st, LutRows<ERR>(A.lut_ptr, A.lut_seg, A.lut_val, A.lut_err, A.gv));
     else if (A.counts)
-        expand_rows<BLOCK, SPARSE>(st, A.gv);
+        expand_rows<BLOCK, SPARSE, false>(st, DeepRows(A.gv));
     else
         push_mass<BLOCK, SPARSE>(st, A.gv, sh.rank_ptr, A.depth);
     __syncthreads();
@@ -1740,14 +1779,17 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
         if (fail) write_failure<BLOCK>(A, q);  // even a table for the whole graph overflowed
     } else if (uni(it.parts) == 1) {
         write_result<BLOCK, SPARSE, ERR>(A, sh, st, q, nonempty, vol);
-    } else if (!ERR && merge_part<BLOCK, SPARSE>(A, sh, st, it)) {
+    } else if (merge_part<BLOCK, SPARSE, ERR>(A, sh, st, it)) {
         QueryState all = st;  // the box's sums, and zeros for the next call
         const uint64_t at = uint64_t(it.slot) * nseg;
         all.seg_cnt = A.slot_cnt + at, all.seg_hi = A.slot_hi + at, all.seg_lo = A.slot_lo + at;
-        write_result<BLOCK, false, false>(A, sh, all, q, nonempty, vol);
+        if (ERR) all.seg_var = A.slot_var + at;
+        write_result<BLOCK, false, ERR>(A, sh, all, q, nonempty, vol);
         __syncthreads();
-        for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK)
+        for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK) {
             all.seg_cnt[s] = 0, all.seg_hi[s] = 0.f, all.seg_lo[s] = 0.f;
+            if (ERR) all.seg_var[s] = 0.f;
+        }
         if (threadIdx.x == 0) A.slot_done[it.slot] = 0;
     }
     __syncthreads();
@@ -1772,6 +1814,7 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
 // Hands an item whose table overflowed to the retry launch (list 1). Any thread, once. A whole
 // box of a planned call is cut into parts there and then (`cubes` of it, while slots last), so
 // that the retry launch does not end with one workgroup redoing a large box on its own.
+template <bool ERR>
 __device__ inline void report_overflow(const QueryArgs &A, const Item &it, uint32_t cubes)
 {
     if (it.parts > 1) {
@@ -1780,7 +1823,7 @@ __device__ inline void report_overflow(const QueryArgs &A, const Item &it, uint3
         A.overflow[atomicAdd(&A.counters[kCountOver], 1u)] = kPartFlag | k;
         return;
     }
-    const uint32_t parts = cubes ? parts_of(cubes, kMinPartRedo) : 1u;
+    const uint32_t parts = ERR ? (cubes >> kBigLog2 ? kClassesRedo : 1u) : cubes ? parts_of(cubes, kMinPartRedo) : 1u;
     if (parts > 1 && A.n_slots) {
         // (both counters may pass their limits: then the box stays whole)
         const uint32_t k = atomicAdd(&A.counters[kCountRedo], parts);
@@ -1804,7 +1847,7 @@ __device__ __attribute__((always_inline)) inline void answer(const QueryArgs &A,
                                                              const QueryState &st, const Item it, bool planned)
 {
     if (run_query<BLOCK, GROUP, SPARSE, ERR>(A, sh, st, it, false, 0u) && threadIdx.x == 0)
-        report_overflow(A, it, planned ? box_cubes(A.lt, A.boxes + 6 * uint64_t(it.q)) : 0u);
+        report_overflow<ERR>(A, it, planned || ERR ? box_cubes(A.lt, A.boxes + 6 * uint64_t(it.q)) : 0u);
 }
 
 // The graph's tables every query reads, copied to LDS. The loads are issued together and ahead
@@ -1848,6 +1891,7 @@ __device__ inline QueryState lds_state(char *dyn, QueryShared &sh, uint32_t nseg
     place_slabs(st, slabs, n_levels);
     st.seg_var = err ? reinterpret_cast<float *>(slabs + lds_slab_bytes(n_levels)) : nullptr;
     st.counts = counts;
+    st.cls = 0, st.n_cls = 1;
     uint32_t *t = reinterpret_cast<uint32_t *>(dyn);
     if (SPARSE) {
         st.seg_cnt = nullptr;
@@ -2030,6 +2074,7 @@ __device__ inline QueryState pool_state(const GlobalPool &p, uint32_t w, char *s
 {
     QueryState st;
     st.counts = counts;
+    st.cls = 0, st.n_cls = 1;
     const uint64_t at = uint64_t(w) * p.slots, sat = uint64_t(w) * nseg;
     st.keys = p.keys + at;
     st.cnt = p.cnt + at;
@@ -2714,6 +2759,7 @@ struct Workspace {
     uint4 *split, *split_over;      // [2 n_slots], [4 n_slots]
     uint32_t *slot_done, *slot_cnt; // [n_slots], [n_slots][S]
     float *slot_hi, *slot_lo;       // [n_slots][S]
+    float *slot_var;                // [n_slots][S]
     GlobalPool fin;       // tables that hold every node of the graph
     GlobalPool mid;       // many workers with mid-size tables (workers 0: none)
     uint64_t bytes;
@@ -2748,7 +2794,7 @@ inline uint32_t mid_workers(const Graph &g) { return fallback_slots(g) > kHashGl
 inline uint32_t split_slots(const Graph &g)
 {
     if (uint64_t(g.n_nodes) * 4 / 3 + 2 > (uint64_t(1) << 26)) return 0;
-    return uint32_t(std::min<uint64_t>(kMaxSlots, std::max<uint64_t>(kMinSlots, kSlotBytes / (12ull * g.nseg))));
+    return uint32_t(std::min<uint64_t>(kMaxSlots, std::max<uint64_t>(kMinSlots, kSlotBytes / (16ull * g.nseg))));
 }
 
 // Carves the workspace for `fin_workers` workers of the final tables (0:
@@ -2790,6 +2836,7 @@ Workspace carve(const Graph &g, char *base, uint32_t max_boxes, uint32_t fin_wor
     w.slot_cnt = reinterpret_cast<uint32_t *>(take(ns * g.nseg * 4));
     w.slot_hi = reinterpret_cast<float *>(take(ns * g.nseg * 4));
     w.slot_lo = reinterpret_cast<float *>(take(ns * g.nseg * 4));
+    w.slot_var = reinterpret_cast<float *>(take(ns * g.nseg * 4));
     w.split = reinterpret_cast<uint4 *>(take(2 * ns * sizeof(uint4)));
     w.split_over = reinterpret_cast<uint4 *>(take(4 * ns * sizeof(uint4)));
     w.work = reinterpret_cast<uint32_t *>(take(uint64_t(max_boxes) * 4));
@@ -3697,6 +3744,7 @@ void clear_workspace(const Graph &g, const Workspace &w, hipStream_t s)
     zero(w.slot_cnt, ns * g.nseg);
     zero(w.slot_hi, ns * g.nseg);
     zero(w.slot_lo, ns * g.nseg);
+    zero(w.slot_var, ns * g.nseg);
 }
 
 int dev_workspace_init(Graph *g, void *work, uint64_t bytes, void *stream, std::string *err)
@@ -3749,7 +3797,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         // box can overflow, and no launch has to follow
         A.table_cap = kHashDirect;
         while (A.table_cap < kHashDirectMax && !holds_all(A.table_cap, false)) A.table_cap *= 2;
-        if (!holds_all(A.table_cap, false)) A.table_cap = kHashBig;
+        if (!holds_all(A.table_cap, false)) A.table_cap = ERR ? kHashBigErr : kHashBig;
         if (d.cfg.table_big) A.table_cap = d.cfg.table_big;
         const bool table = by_table(A.table_cap);
         if (table && !d.cfg.table_big) A.table_cap = kHashBigSparse;
@@ -3762,7 +3810,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
         // about one part per CU: with four, 256 boxes of a 589x563x395 volume took 122 us instead
         // of 63 (every part adds its sources to its box's sums with global atomics)
-        const uint32_t ways = std::min({grid, uint32_t(d.ncu), A.n_slots});
+        const uint32_t ways = ERR ? 0u : std::min({grid, uint32_t(d.ncu), A.n_slots});
         if ((rc = timing_begin(g, s, err))) return rc;
         hipLaunchKernelGGL(kdirect, dim3(std::min(grid, n + 2 * ways)), dim3(kBlockDirect), dyn, s, A, ways, kMinPart);
         HIP_TRY(hipGetLastError());
@@ -3773,7 +3821,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         // 1.21 ms with 1,024 slots, 1.48 with 2,048; 591 segments, 9,958 nodes, 20,000 boxes: 755 us
         // with 1,024 (some boxes overflow), 613 with 2,048.
         const bool few = A.counts && !ERR && n_entries / 8 <= kHashDirect / 4 * 3;
-        uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : few ? kHashDirect : kHashBig;
+        uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : ERR ? kHashBigErr : few ? kHashDirect : kHashBig;
         const bool table = by_table(cap_big);
         if (table && !d.cfg.table_big) cap_big = kHashBigSparse;
         const uint32_t dyn_big = bytes(cap_big, table);
@@ -3799,7 +3847,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         const int bsmall = d.cfg.block_small == 256 ? kBlock : 128;  // threads per small-tier box
         const QueryKernel ksmall = bsmall == 128 ? tier_kernel<128, false, SPARSE, ERR>(d.cfg.unroll_small)
                                                  : tier_kernel<kBlock, false, SPARSE, ERR>(d.cfg.unroll_small);
-        const uint32_t cap_small = d.cfg.table_small ? d.cfg.table_small : (SPARSE ? kHashSmallSparse : kHashSmall);
+        const uint32_t cap_small = d.cfg.table_small ? d.cfg.table_small : (SPARSE ? kHashSmallSparse : ERR ? kHashSmallErr : kHashSmall);
         const uint32_t dyn_small = bytes(cap_small, SPARSE);
         uint32_t wsmall = 0;
         if ((rc = resident(reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &wsmall))) return rc;
@@ -3807,7 +3855,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         hipLaunchKernelGGL(query_size_kernel, dim3(blocks), dim3(256), 0, s, lt, A.boxes, n, w.work, w.buckets,
                            w.counters, A.sp_total);
         hipLaunchKernelGGL(query_order_kernel, dim3(blocks), dim3(256), 0, s, w.work, n, w.buckets, w.order,
-                           w.counters, w.split, A.n_slots, kMinPartBatch, SPARSE ? kBigLog2Sparse : kBigLog2);
+                           w.counters, w.split, ERR ? 0u : A.n_slots, kMinPartBatch, SPARSE ? kBigLog2Sparse : kBigLog2);
         A.order = w.order;
         if ((rc = timing_begin(g, s, err))) return rc;
         A.table_cap = cap_big;
@@ -3942,15 +3990,16 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     A.overflow2 = w.overflow2;
     A.overflow3 = w.overflow3;
     A.stats = stats;
-    // Shared boxes: not where a box's table entries are reported, nor where they all have to be
-    // in one table (uncertainties); list entries hold box numbers below kPartFlag.
-    A.n_slots = stats || variant == kQueryLutErr || variant == kQueryPlain || n >= kPartFlag ? 0u : w.n_slots;
+    // Shared boxes: not where a box's table entries are reported; list entries hold box numbers
+    // below kPartFlag.
+    A.n_slots = stats || variant == kQueryPlain || n >= kPartFlag ? 0u : w.n_slots;
     A.split = w.split;
     A.split_over = w.split_over;
     A.slot_done = w.slot_done;
     A.slot_cnt = w.slot_cnt;
     A.slot_hi = w.slot_hi;
     A.slot_lo = w.slot_lo;
+    A.slot_var = w.slot_var;
     if (variant == kQueryLut || variant == kQueryLutErr) {
         if (!g->dev.lut_ptr) {
             *err = "the mixture lookup table is not on the device (mg_lut_build)";

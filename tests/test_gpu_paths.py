@@ -1,0 +1,117 @@
+"""GPU parity of the query launches where a call takes one path or another: boxes shared by several
+workgroups (calls with and without a planning launch), boxes whose node tables overflow and are
+redone in parts or in classes of nodes, against the CPU oracle.
+
+Bounds as in test_gpu.py (fractions: relative error below 1e-5, exact zeros) and test_gpu_quant.py
+(uncertainties: 2e-4 relative, plus 1e-6 of the largest). A shared box adds one fp32 addition with
+its compensation per part and source, the terms of one more node: inside the same bounds.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import footprint as ofp
+from oracle import quant, scan
+from paper_2009_02702_amd import Graph, synth
+
+from test_gpu import _compare, _dev, _graph
+from test_gpu_quant import _compare as _compare_quant
+from test_gpu_quant import _compare_err
+
+pytestmark = pytest.mark.gpu
+
+DIMS = (160, 150, 140)
+
+
+def _boxes(n, large):
+    """n boxes: `large` ones of most of the volume (odd corners: up to 150,000 cubes), then an empty
+    one, one outside, then small ones of odd sizes."""
+    rng = np.random.default_rng(n)
+    b = np.concatenate([rng.integers(0, 130, size=(n, 3)), rng.integers(1, 24, size=(n, 3))], axis=1)
+    k = min(n, large)
+    b[:k, :3] = rng.integers(0, 3, size=(k, 3)) * 2 + 1
+    b[:k, 3:] = np.asarray(DIMS) - rng.integers(6, 13, size=(k, 3))
+    if n > k + 2:
+        b[k] = [5, 5, 5, 0, 4, 4]
+        b[k + 1] = [DIMS[0], 0, 0, 3, 3, 3]
+    return b[rng.permutation(n)].astype(np.uint32)
+
+
+@pytest.mark.parametrize("n,large", [(1, 1), (3, 2), (255, 5), (1024, 3), (1025, 3), (1500, 40)])
+def test_boxes_shared_by_several_workgroups(n, large):
+    """Calls of up to 1,024 boxes (one launch) and of more (planned): large boxes are shared by
+    several workgroups, the others are not; with tiny tables parts overflow and are redone, in LDS
+    or in global memory. Twice each: the call leaves its workspace as it found it."""
+    w = synth.workload(2, dims=DIMS, segments=300, n_boxes=1)
+    vol = synth.make_volume(w)
+    g = _graph("paths", vol)
+    boxes = _boxes(n, large)
+    ids, vol_c = scan.compact(vol)
+    _, ref = scan.box_counts(vol_c, len(ids), boxes)
+    db = _dev(boxes)
+    ws = g.workspace(n)
+    try:
+        for tables in ((0, 0, 0), (64, 64, 1024), (64, 64, 64)):
+            g.set_launch_config(table_big=tables[0], table_small=tables[1], table_retry=tables[2])
+            for again in range(2):
+                got = g.query(db, workspace=ws).cpu().numpy()
+                _compare(got, ref, None, "%d boxes, tables %s, call %d" % (n, tables, again))
+    finally:
+        g.set_launch_config(table_big=0, table_small=0, table_retry=0)
+
+
+_QUANT = []
+
+
+def _quantized():
+    """A quantized graph, boxes of 1 to 27,000 cubes, and the oracle's fractions and uncertainties."""
+    if not _QUANT:
+        dims = (72, 70, 66)
+        g = Graph.build(synth.make_volume(synth.workload(2, dims=dims, segments=150, n_boxes=1)))
+        S = g.info()["nseg"]
+        d = g.export_dag()
+        rep, nodes, _, _ = quant.quantize_dag(S, d["child_a"][S:], d["child_b"][S:],
+                                              d["wnum"][S:] / d["wden"][S:], 9)
+        mu, dmu = quant.propagate(S, nodes)
+        maps = [g.export_map(l) for l in range(g.info()["n_levels"])]
+        boxes = np.array([[1, 1, 1, 70, 67, 64], [1, 3, 1, 68, 63, 64], [3, 1, 1, 66, 69, 62], [0, 0, 0, 72, 70, 66],
+                          [5, 9, 7, 20, 31, 6], [7, 7, 7, 1, 1, 1], [9, 9, 9, 4, 0, 4]], dtype=np.uint32)
+        f, u = np.zeros((len(boxes), S)), np.zeros((len(boxes), S))
+        cubes, l0 = np.zeros(len(boxes), dtype=np.int64), np.zeros(len(boxes), dtype=bool)
+        for i, bx in enumerate(boxes.astype(np.int64)):
+            counts, levels = {}, set()
+            for lev, c in ofp.assembly(bx[:3], bx[3:], dims):
+                node = rep[int(maps[lev][c[2], c[1], c[0]])]
+                counts[node] = counts.get(node, 0) + 8 ** lev
+                levels.add(lev)
+                cubes[i] += 1
+            if counts:
+                f[i], u[i] = quant.box_histogram(counts, mu, dmu, float(np.prod(bx[3:])))
+                l0[i] = levels == {0}
+        q = g.quantize(9).upload(0)
+        q.lut_build()
+        _QUANT.append((q, boxes, f, u, l0, cubes))
+    return _QUANT[0]
+
+
+@pytest.mark.parametrize("n", [7, 1024, 1025])
+def test_uncertainty_boxes_redone_by_classes_of_nodes(n):
+    """Large boxes (from 2^14 cubes) of an uncertainty query whose table overflows are redone by
+    workgroups that each take one class of the nodes: every node's count still meets its row whole.
+    More such boxes than can be shared in one call are redone whole."""
+    q, boxes, f, u, l0, cubes = _quantized()
+    assert (cubes[:3] >= 1 << 14).all()
+    pick = np.arange(n) % len(boxes)
+    db = _dev(boxes[pick])
+    ws = q.workspace(n)
+    try:
+        for tables in ((0, 0, 0), (64, 64, 1024), (64, 64, 64)):
+            q.set_launch_config(table_big=tables[0], table_small=tables[1], table_retry=tables[2])
+            for again in range(2):
+                out, err = q.query_err(db, workspace=ws)
+                tag = "%d boxes, tables %s, call %d" % (n, tables, again)
+                _compare_quant(out.cpu().numpy(), f[pick], l0[pick], tag)
+                _compare_err(err.cpu().numpy(), u[pick], tag)
+    finally:
+        q.set_launch_config(table_big=0, table_small=0, table_retry=0)
