@@ -142,6 +142,9 @@ struct RunLevel {
 // cube is at an odd position starts one element early, `odd`); or, kind 2, each
 // row segment summed from the row runs of its level and orientation (base, s1b,
 // s2b, units unused).
+// (kind 2, in the same words: base: the first row's index in the level's runs, above it the
+// reciprocal of e1 (run_item); s1b, s2b: row indices between rows / slices; units: the first
+// cube's cell along its row; odd: log2 of the segments per row)
 struct Slab {
     uint64_t base;         // byte offset of the first unit in its buffer (maps or maps16)
     uint32_t e0, e1, e2;   // cubes along the fast, mid and slow axes
@@ -193,6 +196,14 @@ __host__ __device__ inline LevelRow level_row(const LevelTable &lt, uint32_t lev
     return LevelRow{lt.dims[lev][0], lt.dims[lev][1], lt.dims[lev][2], 0u, lt.off[lev]};
 }
 
+// Segments per row of a kind-2 slab, as log2 of the power of two >= ceil(e0 / kRunSeg).
+__host__ __device__ inline uint32_t run_lseg(uint32_t e0)
+{
+    uint32_t lseg = 0;
+    while ((kRunSeg << lseg) < e0) ++lseg;
+    return lseg;
+}
+
 // The slab of level `lev` covering cells [x0, x1) x [y0, y1) x [z0, z1) (not empty): the
 // fast axis is x (rows from maps) unless the block is thinner in x than in y
 // (rows along y from maps_t); of the other two, the thinner is the slow axis.
@@ -219,7 +230,11 @@ __host__ __device__ inline Slab make_slab(const LevelTable &lt, const LevelRow &
     // rows from the runs (while the slab's (row, segment) items fit 32 bits)
     if (ef >= lt.run_min && ((lt.runs_mask >> (2 * lev + f)) & 1u) &&
         uint64_t(em) * ew * ((ef + kRunSeg - 1) / kRunSeg) < (1ull << 30)) {
-        s.kind = 2, s.odd = 0, s.base = 0, s.s1b = s.s2b = 0, s.units = ef;
+        const uint32_t pitch = f ? lr.Z : lr.Y;  // rows of a slice: z (f: y fast) or y
+        const bool in_slice = f ? m == 2 : m == 1;
+        s.kind = 2, s.odd = uint8_t(run_lseg(ef)), s.units = f ? y0 : x0;
+        s.s1b = in_slice ? 1u : pitch, s.s2b = in_slice ? pitch : 1u;
+        s.base = (f ? z0 + pitch * x0 : y0 + pitch * z0) | uint64_t(0xFFFFFFFFu / em + 1) << 32;
         return s;
     }
     // element strides of the mid and slow axes in the chosen copy, and the first element
@@ -302,18 +317,29 @@ __host__ __device__ inline uint32_t slab_tiles(const Slab &sl)
     return ((sl.units + (1u << ltx) - 1) >> ltx) * ((sl.e1 + ty - 1) / ty) * sl.e2;
 }
 
-// Segments per row of a kind-2 slab, as log2 of the power of two >= ceil(e0 / kRunSeg).
-__host__ __device__ inline uint32_t run_lseg(uint32_t e0)
-{
-    uint32_t lseg = 0;
-    while ((kRunSeg << lseg) < e0) ++lseg;
-    return lseg;
-}
-
 // (row, segment) items of a slab summed from row runs.
 __host__ __device__ inline uint32_t slab_items(const Slab &sl)
 {
-    return sl.kind == 2 ? (sl.e1 * sl.e2) << run_lseg(sl.e0) : 0u;
+    return sl.kind == 2 ? (sl.e1 * sl.e2) << sl.odd : 0u;
+}
+
+// Lane src's value of v (all lanes active).
+__device__ inline uint32_t lane_value(uint32_t v, uint32_t src)
+{
+    return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
+}
+
+// Inclusive sums over the lanes of a wave (all active), by DPP shifts inside rows of 16 lanes and
+// two broadcasts across them.
+__device__ inline uint32_t wave_sums(uint32_t v)
+{
+    v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x111, 0xF, 0xF, true));
+    v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x112, 0xF, 0xF, true));
+    v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x114, 0xF, 0xF, true));
+    v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x118, 0xF, 0xF, true));
+    v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x142, 0xA, 0xF, false));
+    v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x143, 0xC, 0xF, false));
+    return v;
 }
 
 // Wave 0 fills the slab table of one box in LDS, lane (level, face) one slab (two rounds
@@ -334,12 +360,8 @@ __device__ inline void build_slabs(const LevelTable &lt, const LevelRow *rows, c
         const uint64_t mask = __builtin_amdgcn_ballot_w64(have);
         const uint32_t at = n + __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32),
                                                           __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u));
-        uint32_t t = have ? slab_tiles(sl) : 0u, k = have ? slab_items(sl) : 0u;
-        const uint32_t t1 = t, k1 = k;
-        for (int off = 1; off < 64; off <<= 1) {  // inclusive sums over the lanes
-            const uint32_t vt = uint32_t(__shfl_up(int(t), off, 64)), vk = uint32_t(__shfl_up(int(k), off, 64));
-            if (lane >= uint32_t(off)) t += vt, k += vk;
-        }
+        const uint32_t t1 = have ? slab_tiles(sl) : 0u, k1 = have ? slab_items(sl) : 0u;
+        const uint32_t t = wave_sums(t1), k = wave_sums(k1);
         if (have) {
             slabs[at] = sl;
             if (tile0) tile0[at] = tiles + t - t1, item0[at] = items + k - k1;
@@ -450,7 +472,7 @@ __device__ inline uint32_t table_slot(const QueryState &st, uint32_t key)
             if (old == kEmpty) {
                 const uint32_t idx = atomicAdd(st.n_used, 1u);
                 st.used[idx] = slot;
-                atomicMax(st.max_key, key);
+                if (!st.counts) atomicMax(st.max_key, key);  // (only the push needs it)
                 if (idx >= st.limit) atomicOr(st.flags, 1u);
                 return slot;
             }
@@ -861,31 +883,30 @@ __device__ inline T load_global(const T *p)
     return *(const __attribute__((address_space(1))) T *)(p);
 }
 
-// The skip entries that bound the runs of cells [p0, p1) of row r: the chunk of p0, and the one
-// after p1's, which past the row's last chunk is the next row's first. True if that lies past
-// the last row (the level's runs end there: no entry).
+// The skip entries that bound the runs of cells [p0, p1) of row r: c0, that of p0's chunk, and the
+// one after p1's chunk, *n entries on, which past the row's last chunk (*row_end) is the next
+// row's first. True if that lies past the last row (the level's runs end there: no entry).
 __host__ __device__ inline bool run_skips(uint32_t rows, uint32_t chunks, uint32_t r, uint32_t p0, uint32_t p1,
-                                          uint64_t *c0, uint64_t *c1)
+                                          uint64_t *c0, uint32_t *n, bool *row_end)
 {
-    *c0 = uint64_t(r) * chunks + p0 / kRunSkipCells;
-    *c1 = uint64_t(r) * chunks + (p1 - 1) / kRunSkipCells + 1;
-    return *c1 == uint64_t(rows) * chunks;
+    const uint32_t k0 = p0 / kRunSkipCells, k1 = (p1 - 1) / kRunSkipCells + 1;
+    *c0 = uint64_t(r) * chunks + k0;
+    *n = k1 - k0;
+    *row_end = k1 == chunks;
+    return *row_end && r + 1 == rows;
 }
 
-// Item `it` of a kind-2 slab: its row index r in the level's runs of orientation
-// f (the level is Y cells deep in y and Z in z) and its cells [p0, p1) along the row;
-// false for a padding item past the row.
-__host__ __device__ inline bool run_item(const Slab &sp, uint32_t Y, uint32_t Z, uint32_t f, uint32_t lseg,
-                                         uint32_t it, uint32_t *r, uint32_t *p0, uint32_t *p1)
+// Item `it` of a kind-2 slab: its row index r in the level's runs and its cells [p0, p1) along
+// the row; false for a padding item past the row. (row / e1 by the slab's reciprocal, rounded up:
+// for the fewer than 2^30 rows of a slab the product is at most one too large.)
+__host__ __device__ inline bool run_item(const Slab &sp, uint32_t it, uint32_t *r, uint32_t *p0, uint32_t *p1)
 {
-    const uint32_t c = it & ((1u << lseg) - 1), row = it >> lseg;
-    const uint32_t i2 = sp.e2 == 1 ? 0u : row / sp.e1, i1 = row - i2 * sp.e1;
-    uint32_t x, y, z;
-    slab_coords(sp, 0, i1, i2, &x, &y, &z);
-    const uint32_t fa = f == 0 ? x : y;
-    *p0 = fa + c * kRunSeg;
-    *p1 = min(*p0 + kRunSeg, fa + sp.e0);
-    *r = f == 0 ? y + Y * z : z + Z * x;
+    const uint32_t lseg = sp.odd, c = it & ((1u << lseg) - 1), row = it >> lseg;
+    uint32_t i2 = uint32_t((uint64_t(row) * uint32_t(sp.base >> 32)) >> 32);
+    if (i2 * sp.e1 > row) --i2;
+    *r = uint32_t(sp.base) + (row - i2 * sp.e1) * sp.s1b + i2 * sp.s2b;
+    *p0 = sp.units + c * kRunSeg;
+    *p1 = min(*p0 + kRunSeg, sp.units + sp.e0);
     return *p0 < *p1;
 }
 
@@ -990,7 +1011,7 @@ __device__ inline void ring_put(DeferRing &q, const QueryState &st, const GraphV
 // wave so meets few slabs instead of a share of every one: a box of 25,000 cubes has
 // ~30 slabs, most of them a tile or two, and walking all of them with every wave
 // cost one exposed load latency per slab and wave. What bounds it is the issue of
-// vector instructions (about 75 per tile, 70 per 64 runs), so rows go to runs from
+// vector instructions (about 75 per tile, 45 per 64 runs), so rows go to runs from
 // kRunMinRow cubes on. 100,000 boxes of a 512^3 volume, default launch: 2.82 ms with
 // the waves of a box dealt the blocks of every slab in turn and one lane per row
 // segment, 1.54 ms so.
@@ -1051,13 +1072,14 @@ __host__ __device__ inline uint32_t tile_lane(uint32_t pack, uint32_t s1b, uint3
     return ok ? off : 0u;
 }
 
-// The slab that holds tile (or item) `t`: the last one with first[i] <= t.
+// The slab that holds tile (or item) `t`, below the total in first[n_slabs]: the last one with
+// first[i] <= t. (No branch in a step: one cost as much again in execution masks.)
 __device__ inline uint32_t find_slab(const uint32_t *first, uint32_t n_slabs, uint32_t t)
 {
-    uint32_t i = 0;
+    uint32_t i = n_slabs > 64 && first[64] <= t ? 64u : 0u;
 #pragma unroll
-    for (uint32_t step = 64; step > 0; step >>= 1)
-        if (i + step < n_slabs && first[i + step] <= t) i += step;
+    for (uint32_t step = 32; step > 0; step >>= 1)
+        if (first[min(i + step, n_slabs)] <= t) i += step;
     return i;
 }
 
@@ -1175,75 +1197,83 @@ __device__ __attribute__((always_inline)) inline void stream_tiles(const char *m
 // a load latency on every four runs of the longest of 64 segments.) A run starts where the one
 // before it ends: the lane below's, the step before's for lane 0; of an item's first run every
 // cell from p0 on counts.
+// Which item a run of the step at s belongs to: the items that start in the 64 positions from s
+// mark theirs in LDS (with a number of the step's own, so that no mark is ever cleared), and a lane
+// counts the marks up to its own. (Six steps of a binary search through the lanes before: 40 of the
+// 75 vector instructions of a step; 100,000 boxes of 512^3: 1.22 ms, 1.14 so,
+// with find_slab, run_item and the prefix sums shortened as well.)
 template <bool SPARSE>
-__device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *runs, const LevelRow *rows,
-                                                               const QueryState &st, const GraphView &gv,
-                                                               uint32_t n_slabs, uint32_t a, uint32_t b,
-                                                               DeferRing &dq, const uint32_t *flags_lds)
+__device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *runs, const QueryState &st,
+                                                               const GraphView &gv, uint32_t n_slabs, uint32_t a,
+                                                               uint32_t b, DeferRing &dq, uint32_t *marks,
+                                                               const uint32_t *flags_lds)
 {
     const uint32_t lane = threadIdx.x & 63;
+    uint32_t tag = 0;
+    marks[lane] = 0;
     for (uint32_t b0 = a; b0 < b; b0 += 64) {
         if (uni(*flags_lds) & 1u) return;
         const uint32_t it = b0 + lane;
-        uint32_t span = 0, lev = 0, j0 = 0, cnt = 0;  // span: p0 | p1 << 16 (rows hold at most 2^15 cells)
+        // span: p0 (rows hold at most 2^15 cells), p1 - p0 << 16 (<= kRunSeg), level << 25
+        uint32_t span = 0, j0 = 0, cnt = 0;
         if (it < b) {
             const uint32_t i = find_slab(st.item0, n_slabs, it);
             const Slab &sp = st.slabs[i];
-            lev = sp.level;
-            const uint32_t f = sp.axes & 3u;
-            const RunLevel &rl = runs[2 * lev + f];
+            const uint32_t lev = sp.level;
+            const RunLevel &rl = runs[2 * lev + (sp.axes & 3u)];
             uint32_t r, p0, p1;
-            if (run_item(sp, rows[lev].Y, rows[lev].Z, f, run_lseg(sp.e0), it - st.item0[i], &r, &p0, &p1)) {
-                span = p0 | (p1 << 16);
-                uint64_t c0, c1;
-                const bool last = run_skips(rl.rows, rl.chunks, r, p0, p1, &c0, &c1);
-                const uint32_t lo = load_global(rl.skip + c0);
-                uint32_t hi = last ? rl.n_runs : load_global(rl.skip + c1);  // a row's first run or one inside it
-                if ((p1 - 1) / kRunSkipCells + 1 == rl.chunks) --hi;         // the run before the next row's first
+            cnt = 1;  // a padding item: one place in the sequence, no cells
+            if (run_item(sp, it - st.item0[i], &r, &p0, &p1)) {
+                span = p0 | (p1 - p0) << 16 | lev << 25;
+                uint64_t c0;
+                uint32_t n;
+                bool row_end;
+                const bool last = run_skips(rl.rows, rl.chunks, r, p0, p1, &c0, &n, &row_end);
+                const uint32_t *const skip = rl.skip + c0;
+                const uint32_t lo = load_global(skip);
+                uint32_t hi = last ? rl.n_runs : load_global(skip + n);  // a row's first run or one inside it
+                if (row_end) --hi;                                       // the run before the next row's first
                 hi = min(hi, rl.n_runs - 1);
                 j0 = rl.first + lo;
-                cnt = hi >= lo ? hi - lo + 1 : 0u;
+                cnt = hi >= lo ? hi - lo + 1 : 1u;
             }
         }
         // position of each item's first run in the sequence
-        uint32_t pos = cnt;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t v = uint32_t(__shfl_up(int(pos), off, 64));
-            if (lane >= uint32_t(off)) pos += v;
-        }
+        uint32_t pos = wave_sums(cnt);
         const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(pos), 63));
-        if (total == 0) continue;
         pos -= cnt;
         j0 -= pos;  // run index less position
-        auto from = [](uint32_t v, uint32_t src) {
-            return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
-        };
-        // this lane's run of the step at s: the last item that starts at or before it
-        auto fetch = [&](uint32_t s, uint64_t *v, uint32_t *cells, uint32_t *lv, bool *first) {
-            const uint32_t x = min(s + lane, total - 1);
-            uint32_t i = 0, at = 0;
-#pragma unroll
-            for (uint32_t step = 32; step > 0; step >>= 1) {
-                const uint32_t p = from(pos, i + step);
-                if (p <= x) i += step, at = p;
-            }
-            *v = load_global(gv.runs + (from(j0, i) + x));
-            const uint32_t sc = from(span, i);
-            *cells = s + lane < total ? sc : 0u;  // no cells past the end
-            *lv = from(lev, i);
-            *first = x == at;
+        if (cnt == 0) pos = kEmpty;  // past the wave's items: starts nowhere
+        uint32_t begun = 0;          // items that start before the step's positions
+        auto fetch = [&](uint32_t s, uint64_t *v, uint32_t *sp, bool *first) {
+            ++tag;
+            const uint32_t d = pos - s;
+            if (d < 64) marks[d] = tag;
+            __builtin_amdgcn_wave_barrier();
+            *first = marks[lane] == tag;
+            __builtin_amdgcn_wave_barrier();
+            const uint64_t m = __builtin_amdgcn_ballot_w64(*first);
+            // marks at the positions up to this lane's own, as those below it of m shifted by one
+            const uint32_t i = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 33),
+                                                         __builtin_amdgcn_mbcnt_lo(uint32_t(m >> 1),
+                                                                                   begun - 1 + (uint32_t(m) & 1u)));
+            begun += uint32_t(__builtin_popcountll(m));
+            *v = load_global(gv.runs + (lane_value(j0, i) + min(s + lane, total - 1)));
+            const uint32_t sc = lane_value(span, i);
+            *sp = s + lane < total ? sc : 0u;  // no cells past the end
         };
         uint64_t v, w;
-        uint32_t cells, lv, cells1, lv1, carry = 0;
+        uint32_t sp, sp1, carry = 0;
         bool first, first1;
-        fetch(0, &v, &cells, &lv, &first);
+        fetch(0, &v, &sp, &first);
         for (uint32_t s = 0; s < total; s += 64) {
-            fetch(s + 64, &w, &cells1, &lv1, &first1);  // past the end: the last run again, not counted
-            const uint32_t end = uint32_t(v >> 32), node = uint32_t(v);
+            // (at or past the end: nothing starts, the last run again, not counted)
+            fetch(s + 64, &w, &sp1, &first1);
+            const uint32_t end = uint32_t(v >> 32), node = uint32_t(v), lv = sp >> 25;
             uint32_t begin = uint32_t(__builtin_amdgcn_update_dpp(int(carry), int(end), 0x138, 0xF, 0xF, false));
             carry = uint32_t(__builtin_amdgcn_readlane(int(end), 63));
-            begin = max(first ? 0u : begin, cells & 0xFFFFu);
-            const uint32_t to = min(end, cells >> 16);
+            begin = max(first ? 0u : begin, sp & 0xFFFFu);
+            const uint32_t to = min(end, (sp & 0xFFFFu) + ((sp >> 16) & 0x1FFu));
             const bool act = to > begin;
             const uint32_t len = to - begin;
             if (SPARSE) {
@@ -1252,7 +1282,7 @@ __device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *r
                 if (act && node < gv.nseg) atomicAdd(&st.seg_cnt[node], len << (3 * lv));
                 ring_put<SPARSE>(dq, st, gv, act && node >= gv.nseg, node, len, lv);
             }
-            v = w, cells = cells1, lv = lv1, first = first1;
+            v = w, sp = sp1, first = first1;
         }
     }
 }
@@ -1262,14 +1292,14 @@ __device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *r
 // or are scattered at once (sparse state).
 template <int BLOCK, int GROUP, bool SPARSE>
 __device__ __attribute__((always_inline)) inline void scatter_box(const char *maps, const char *maps16,
-                                                                  const RunLevel *runs, const LevelRow *rows,
-                                                                  const QueryState &st, const GraphView &gv,
-                                                                  uint32_t n_slabs, uint32_t part, uint32_t parts,
+                                                                  const RunLevel *runs, const QueryState &st,
+                                                                  const GraphView &gv, uint32_t n_slabs, uint32_t part, uint32_t parts,
                                                                   const uint32_t *flags_lds)
 {
     constexpr uint32_t kWaves = BLOCK / 64;
     __shared__ uint32_t dq_node[kWaves * (SPARSE ? 1u : kDeferSlots)];
     __shared__ uint16_t dq_code[kWaves * (SPARSE ? 1u : kDeferSlots)];
+    __shared__ uint32_t marks[kWaves * 64];
     const uint32_t wave = uni(threadIdx.x >> 6);
     DeferRing dq{dq_node, dq_code, wave * kDeferSlots, 0u, 0u};
     // The part's range first, then the wave's range of it: a part is the same work whatever
@@ -1287,7 +1317,7 @@ __device__ __attribute__((always_inline)) inline void scatter_box(const char *ma
     range(t1 - t0, 1, wave, kWaves, &a, &b);
     if (a < b) stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, t0 + a, t0 + b, dq, flags_lds);
     range(i1 - i0, kLeastItems, kWaves - 1 - wave, kWaves, &a, &b);
-    if (a < b) sum_runs<SPARSE>(runs, rows, st, gv, n_slabs, i0 + a, i0 + b, dq, flags_lds);
+    if (a < b) sum_runs<SPARSE>(runs, st, gv, n_slabs, i0 + a, i0 + b, dq, marks + 64 * wave, flags_lds);
     if (!SPARSE && dq.tail != dq.head) ring_resolve<SPARSE>(dq, st, gv, dq.tail - dq.head);
 }
 
@@ -1353,13 +1383,9 @@ struct LutRows {
     __device__ Pos begin(uint32_t node) const { return ptr[node]; }
     __device__ Entry entry(Pos j) const { return Entry{seg[j], val[j], ERR ? dev[j] : 0.f}; }
 };
-__device__ inline uint32_t row_bpermute(uint32_t v, uint32_t src)
+__device__ inline uint64_t lane_value(uint64_t v, uint32_t src)
 {
-    return uint32_t(__builtin_amdgcn_ds_bpermute(int(4 * src), int(v)));
-}
-__device__ inline uint64_t row_bpermute(uint64_t v, uint32_t src)
-{
-    return row_bpermute(uint32_t(v), src) | uint64_t(row_bpermute(uint32_t(v >> 32), src)) << 32;
+    return lane_value(uint32_t(v), src) | uint64_t(lane_value(uint32_t(v >> 32), src)) << 32;
 }
 
 // Expansion of the table's nodes: every node adds its voxel count times its
@@ -1387,11 +1413,7 @@ __device__ inline void expand_rows(const QueryState &st, const ROWS &rows)
                 c = ld(&st.cnt[slot]);
             }
         }
-        uint32_t pos = len;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t v = uint32_t(__shfl_up(int(pos), off, 64));
-            if (lane >= uint32_t(off)) pos += v;
-        }
+        uint32_t pos = wave_sums(len);
         const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(pos), 63));
         if (total == 0) continue;
         pos -= len;
@@ -1401,9 +1423,9 @@ __device__ inline void expand_rows(const QueryState &st, const ROWS &rows)
             uint32_t i = 0;
 #pragma unroll
             for (uint32_t step = 32; step > 0; step >>= 1)
-                if (row_bpermute(pos, i + step) <= x) i += step;
-            *e = rows.entry(row_bpermute(j0, i) + x);
-            const uint32_t v = row_bpermute(c, i);
+                if (lane_value(pos, i + step) <= x) i += step;
+            *e = rows.entry(lane_value(j0, i) + x);
+            const uint32_t v = lane_value(c, i);
             *cc = s + lane < total ? v : 0u;
         };
         typename ROWS::Entry e, e1;
@@ -1755,7 +1777,7 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     const uint32_t n_slabs = uni(uint32_t(sh.n_slabs));
     if (n_slabs)
         scatter_box<BLOCK, GROUP, SPARSE>(reinterpret_cast<const char *>(A.maps),
-                                          reinterpret_cast<const char *>(A.maps16), sh.runs, sh.rows, st, A.gv,
+                                          reinterpret_cast<const char *>(A.maps16), sh.runs, st, A.gv,
                                           n_slabs, ERR ? 0u : uni(it.part), ERR ? 1u : uni(it.parts), &sh.flags);
     __syncthreads();
     if (ERR || A.lut_ptr)
@@ -3178,11 +3200,15 @@ int check_load_addresses(const uint32_t dims[3], bool use16, bool naive, bool ru
                 if (f > 1 || items != (uint64_t(sl.e1) * sl.e2) << lseg) where = "run slab orientation or size";
                 for (uint64_t it = 0; where.empty() && it < items; ++it) {
                     uint32_t r, p0, p1;
-                    if (!run_item(sl, lt.dims[L][1], lt.dims[L][2], f, lseg, uint32_t(it), &r, &p0, &p1)) continue;
+                    if (!run_item(sl, uint32_t(it), &r, &p0, &p1)) continue;
                     ++counts[2];
-                    uint64_t c0, c1;
-                    const bool last = run_skips(uint32_t(rows), uint32_t(chunks), r, p0, p1, &c0, &c1);
-                    if (r >= rows || c0 >= rows * chunks || (!last && c1 >= rows * chunks) || p1 > len || p1 >= 65536) {
+                    uint64_t c0;
+                    uint32_t n;
+                    bool row_end;
+                    const bool last = run_skips(uint32_t(rows), uint32_t(chunks), r, p0, p1, &c0, &n, &row_end);
+                    const uint64_t c1 = c0 + n;
+                    if (r >= rows || c0 >= rows * chunks || last != (c1 == rows * chunks) ||
+                        row_end != (c1 == (uint64_t(r) + 1) * chunks) || (!last && c1 >= rows * chunks) || p1 > len || p1 >= 65536) {
                         where = "run row or skip entry out of range";
                         break;
                     }
