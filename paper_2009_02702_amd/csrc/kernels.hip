@@ -60,6 +60,8 @@ constexpr uint32_t kStaticLds = 9216;         // LDS set aside for the query ker
 constexpr uint32_t kHashGlobal = 1u << 16;    // fewest per-worker hash slots in the fallback tables
 constexpr uint32_t kSegLdsMax = 2048;         // sources kept in LDS
 constexpr uint32_t kFallbackWorkers = 128;    // workers of the final global-table launch (budget)
+constexpr uint32_t kLeastTiles = 16;            // tiles and row segments (64 are described at once) worth a
+constexpr uint32_t kLeastRunItems = 32;         // piece of their own where waves share them
 constexpr uint32_t kLeastItems = 8;            // row segments worth a wave's while
 constexpr uint32_t kRunSeg = 256;             // cells of a row one thread sums from the runs
 constexpr uint32_t kRunMinRow = 16;           // rows shorter than this stream cube by cube (default)
@@ -196,12 +198,13 @@ __host__ __device__ inline LevelRow level_row(const LevelTable &lt, uint32_t lev
     return LevelRow{lt.dims[lev][0], lt.dims[lev][1], lt.dims[lev][2], 0u, lt.off[lev]};
 }
 
+// Least k with 2^k >= v (v >= 1, at most 2^31).
+__host__ __device__ inline uint32_t ceil_log2(uint32_t v) { return v > 1 ? 32u - uint32_t(__builtin_clz(v - 1)) : 0u; }
+
 // Segments per row of a kind-2 slab, as log2 of the power of two >= ceil(e0 / kRunSeg).
 __host__ __device__ inline uint32_t run_lseg(uint32_t e0)
 {
-    uint32_t lseg = 0;
-    while ((kRunSeg << lseg) < e0) ++lseg;
-    return lseg;
+    return ceil_log2((e0 + kRunSeg - 1) / kRunSeg);
 }
 
 // The slab of level `lev` covering cells [x0, x1) x [y0, y1) x [z0, z1) (not empty): the
@@ -305,16 +308,15 @@ __host__ __device__ inline bool face_slab(const LevelTable &lt, const LevelRow &
 // product below 2^32.
 __host__ __device__ inline uint32_t tile_ltx(const Slab &sl)
 {
-    uint32_t ltx = 0;
-    while (ltx < 6 && (1u << ltx) < sl.units) ++ltx;
+    const uint32_t ltx = sl.units > 32 ? 6u : ceil_log2(sl.units);
     return sl.s1b >= (1u << 24) ? 6u : ltx;
 }
 
 __host__ __device__ inline uint32_t slab_tiles(const Slab &sl)
 {
     if (sl.kind == 2) return 0;
-    const uint32_t ltx = tile_ltx(sl), ty = 64u >> ltx;
-    return ((sl.units + (1u << ltx) - 1) >> ltx) * ((sl.e1 + ty - 1) / ty) * sl.e2;
+    const uint32_t ltx = tile_ltx(sl), lty = 6u - ltx;
+    return ((sl.units + (1u << ltx) - 1) >> ltx) * ((sl.e1 + (1u << lty) - 1) >> lty) * sl.e2;
 }
 
 // (row, segment) items of a slab summed from row runs.
@@ -1206,11 +1208,10 @@ template <bool SPARSE>
 __device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *runs, const QueryState &st,
                                                                const GraphView &gv, uint32_t n_slabs, uint32_t a,
                                                                uint32_t b, DeferRing &dq, uint32_t *marks,
-                                                               const uint32_t *flags_lds)
+                                                               uint32_t *tags, const uint32_t *flags_lds)
 {
     const uint32_t lane = threadIdx.x & 63;
-    uint32_t tag = 0;
-    marks[lane] = 0;
+    uint32_t &tag = *tags;
     for (uint32_t b0 = a; b0 < b; b0 += 64) {
         if (uni(*flags_lds) & 1u) return;
         const uint32_t it = b0 + lane;
@@ -1287,6 +1288,51 @@ __device__ __attribute__((always_inline)) inline void sum_runs(const RunLevel *r
     }
 }
 
+// The waves of a workgroup share [0, n) of a box's tiles or items: each has one piece to begin with
+// and takes the next from a counter in LDS when it is done with its last. WAVES pieces of half of what is left between
+// them, then WAVES of half of the rest, and so on, and equal shares once those are below twice
+// `least`: an item of a long row holds
+// forty runs, one of a coarse level's three, and with one equal range per wave the waves of a box
+// waited 27,000 of its 92,000 cycles for the last one (boxes of 2^14 cubes and more of a 512^3
+// volume, 353 segments; anisotropic, 591 segments: 43,000 of 98,000).
+template <uint32_t WAVES>
+struct Pieces {
+    uint32_t n, least, mult;            // pieces above `mult` are multiples of it
+    uint32_t at = 0, first = 0, per;    // of the current round: first unit, first piece, units per piece
+    uint32_t k;                         // the wave's first piece; then the last it took
+    bool began = false;
+    __device__ Pieces(uint32_t n_, uint32_t least_, uint32_t mult_, uint32_t k_) : n(n_), least(least_), mult(mult_), k(k_)
+    {
+        size();
+    }
+    __device__ void size()
+    {
+        const uint32_t left = n - at;
+        per = left > 2 * WAVES * least ? left / (2 * WAVES) : (left + WAVES - 1) / WAVES;
+        if (per > mult && left > 2 * WAVES * least) per -= per % mult;
+    }
+    // The wave's next piece [*a, *b); false when there is none.
+    __device__ bool next(uint32_t *taken, uint32_t *a, uint32_t *b)
+    {
+        if (began) {
+            if (n <= 2 * WAVES * least) return false;  // one share each
+            uint32_t v = 0;
+            if ((threadIdx.x & 63) == 0) v = atomicAdd(taken, 1u);
+            k = WAVES + uni(v);
+        }
+        began = true;
+        while (k - first >= WAVES) {
+            at += WAVES * per, first += WAVES;
+            if (at >= n) return false;
+            size();
+        }
+        *a = at + (k - first) * per;
+        if (*a >= n) return false;
+        *b = min(n, *a + per);
+        return true;
+    }
+};
+
 // Part `part` of `parts` of a box's scatter, by one workgroup. Runs on sources add to an
 // integer counter; runs on internal nodes go through the wave's deferral ring (dense state)
 // or are scattered at once (sparse state).
@@ -1294,7 +1340,7 @@ template <int BLOCK, int GROUP, bool SPARSE>
 __device__ __attribute__((always_inline)) inline void scatter_box(const char *maps, const char *maps16,
                                                                   const RunLevel *runs, const QueryState &st,
                                                                   const GraphView &gv, uint32_t n_slabs, uint32_t part, uint32_t parts,
-                                                                  const uint32_t *flags_lds)
+                                                                  uint32_t *taken, const uint32_t *flags_lds)
 {
     constexpr uint32_t kWaves = BLOCK / 64;
     __shared__ uint32_t dq_node[kWaves * (SPARSE ? 1u : kDeferSlots)];
@@ -1314,10 +1360,21 @@ __device__ __attribute__((always_inline)) inline void scatter_box(const char *ma
         range(tiles, 1, part, parts, &t0, &t1);
         range(items, kLeastItems, parts - 1 - part, parts, &i0, &i1);  // from the end that got the fewer tiles
     }
-    range(t1 - t0, 1, wave, kWaves, &a, &b);
-    if (a < b) stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, t0 + a, t0 + b, dq, flags_lds);
-    range(i1 - i0, kLeastItems, kWaves - 1 - wave, kWaves, &a, &b);
-    if (a < b) sum_runs<SPARSE>(runs, st, gv, n_slabs, i0 + a, i0 + b, dq, marks + 64 * wave, flags_lds);
+    uint32_t tag = 0;
+    marks[threadIdx.x] = 0;
+    if constexpr (kWaves > 2) {
+        Pieces<kWaves> tp(t1 - t0, kLeastTiles, GROUP, wave), ip(i1 - i0, kLeastRunItems, 64, kWaves - 1 - wave);
+        while (tp.next(&taken[0], &a, &b))
+            stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, t0 + a, t0 + b, dq, flags_lds);
+        while (ip.next(&taken[1], &a, &b))
+            sum_runs<SPARSE>(runs, st, gv, n_slabs, i0 + a, i0 + b, dq, marks + 64 * wave, &tag, flags_lds);
+    } else {  // two waves, small boxes: one range each, from opposite ends
+        range(t1 - t0, 1, wave, kWaves, &a, &b);
+        if (a < b) stream_tiles<GROUP, SPARSE>(maps, maps16, st, gv, n_slabs, t0 + a, t0 + b, dq, flags_lds);
+        range(i1 - i0, kLeastItems, kWaves - 1 - wave, kWaves, &a, &b);
+        if (a < b)
+            sum_runs<SPARSE>(runs, st, gv, n_slabs, i0 + a, i0 + b, dq, marks + 64 * wave, &tag, flags_lds);
+    }
     if (!SPARSE && dq.tail != dq.head) ring_resolve<SPARSE>(dq, st, gv, dq.tail - dq.head);
 }
 
@@ -1544,6 +1601,7 @@ struct QueryShared {
     uint32_t n_used;
     uint32_t flags;
     uint32_t max_key;
+    uint32_t taken[2];  // pieces of the box's tiles and run items taken beyond the waves' first
     uint32_t q;
     uint32_t last;   // this workgroup finished its box's last part
     uint32_t nnz;    // sparse output: entries of this box
@@ -1769,6 +1827,7 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
         sh.n_used = 0;
         sh.flags = 0;
         sh.max_key = 0;
+        sh.taken[0] = sh.taken[1] = 0;
         sh.n_slabs = 0;
     }
     __syncthreads();
@@ -1778,7 +1837,7 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     if (n_slabs)
         scatter_box<BLOCK, GROUP, SPARSE>(reinterpret_cast<const char *>(A.maps),
                                           reinterpret_cast<const char *>(A.maps16), sh.runs, st, A.gv,
-                                          n_slabs, ERR ? 0u : uni(it.part), ERR ? 1u : uni(it.parts), &sh.flags);
+                                          n_slabs, ERR ? 0u : uni(it.part), ERR ? 1u : uni(it.parts), sh.taken, &sh.flags);
     __syncthreads();
     if (ERR || A.lut_ptr)
         expand_rows<BLOCK, SPARSE, ERR>(st, LutRows<ERR>(A.lut_ptr, A.lut_seg, A.lut_val, A.lut_err, A.gv));
