@@ -447,6 +447,13 @@ __device__ inline T ld(const T *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The stores that go with them.
+template <class T>
+__device__ inline void st_atomic(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ inline uint32_t hash_node(uint32_t k)
 {
     k ^= k >> 16;
@@ -1772,7 +1779,15 @@ __device__ inline Item listed_item(const QueryArgs &A, uint32_t e)
 }
 
 // Adds the sources of this workgroup's part to its box's sums. Returns true in the workgroup
-// that finished the box's last part: its sums are then complete. Every thread must call.
+// that finished the box's last part: its sums are then complete, in its own per-source arrays
+// (dense state; the slot is left zero) or in the slot. Every thread must call.
+//
+// Nothing but atomics touches a slot, and the dense state takes the sums out of it with atomics
+// too, so it needs no fence between workgroups, only that a part's additions are done when it is
+// counted: every wave waits for its own, then the barrier. (A device-scope fence writes back and
+// invalidates caches: 32,000 of 140,000 cycles of a part were spent here with two of them;
+// 256 boxes of a 589x563x395 volume: 57 us with them, 40 without; 20,000 anisotropic boxes, 591
+// segments: 441 and 351.)
 template <int BLOCK, bool SPARSE, bool ERR>
 __device__ inline bool merge_part(const QueryArgs &A, QueryShared &sh, const QueryState &st, const Item &it)
 {
@@ -1797,12 +1812,24 @@ __device__ inline bool merge_part(const QueryArgs &A, QueryShared &sh, const Que
             }
         }
     }
-    __threadfence();
+    if (SPARSE) __threadfence();
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
     if (threadIdx.x == 0) sh.last = atomicAdd(&A.slot_done[it.slot], 1u) + 1u == it.parts;
     __syncthreads();
     if (!uni(sh.last)) return false;
-    __threadfence();
+    if (SPARSE) {
+        __threadfence();
+        return true;
+    }
+    for (uint32_t s = threadIdx.x; s < A.gv.nseg; s += BLOCK) {
+        st_atomic(&st.seg_cnt[s], atomicExch(&A.slot_cnt[at + s], 0u));
+        st_atomic(&st.seg_hi[s], atomicExch(&A.slot_hi[at + s], 0.f));
+        st_atomic(&st.seg_lo[s], atomicExch(&A.slot_lo[at + s], 0.f));
+        if (ERR) st_atomic(&st.seg_var[s], atomicExch(&A.slot_var[at + s], 0.f));
+    }
+    if (threadIdx.x == 0) A.slot_done[it.slot] = 0;
+    __syncthreads();
     return true;
 }
 
@@ -1861,17 +1888,18 @@ __device__ __attribute__((always_inline)) inline bool run_query(const QueryArgs 
     } else if (uni(it.parts) == 1) {
         write_result<BLOCK, SPARSE, ERR>(A, sh, st, q, nonempty, vol);
     } else if (merge_part<BLOCK, SPARSE, ERR>(A, sh, st, it)) {
-        QueryState all = st;  // the box's sums, and zeros for the next call
-        const uint64_t at = uint64_t(it.slot) * nseg;
-        all.seg_cnt = A.slot_cnt + at, all.seg_hi = A.slot_hi + at, all.seg_lo = A.slot_lo + at;
-        if (ERR) all.seg_var = A.slot_var + at;
-        write_result<BLOCK, false, ERR>(A, sh, all, q, nonempty, vol);
-        __syncthreads();
-        for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK) {
-            all.seg_cnt[s] = 0, all.seg_hi[s] = 0.f, all.seg_lo[s] = 0.f;
-            if (ERR) all.seg_var[s] = 0.f;
+        if (SPARSE) {
+            QueryState all = st;  // the box's sums, and zeros for the next call
+            const uint64_t at = uint64_t(it.slot) * nseg;
+            all.seg_cnt = A.slot_cnt + at, all.seg_hi = A.slot_hi + at, all.seg_lo = A.slot_lo + at;
+            write_result<BLOCK, false, false>(A, sh, all, q, nonempty, vol);
+            __syncthreads();
+            for (uint32_t s = threadIdx.x; s < nseg; s += BLOCK)
+                all.seg_cnt[s] = 0, all.seg_hi[s] = 0.f, all.seg_lo[s] = 0.f;
+            if (threadIdx.x == 0) A.slot_done[it.slot] = 0;
+        } else {
+            write_result<BLOCK, false, ERR>(A, sh, st, q, nonempty, vol);
         }
-        if (threadIdx.x == 0) A.slot_done[it.slot] = 0;
     }
     __syncthreads();
     // restore a clean state for the next query
