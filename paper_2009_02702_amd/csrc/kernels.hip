@@ -76,9 +76,9 @@ constexpr uint32_t kMinSlots = 16;            // (but hold at least this many bo
 // Fewest cubes worth a workgroup of their own: when others idle (one box of 205,000 cubes of a
 // 400x375x263 volume in parts of 2,048 / 4,096 / 8,192 / 16,384 / 32,768: 36 / 36 / 40 / 46 / 55 us,
 // whole: 105), and in a large batch (5,000 boxes of 199x181x163, parts of 16,384 / 32,768 /
-// 65,536 / 131,072: 254 / 174 / 126 / 135 us, whole: 160).
+// 65,536: 105 / 102 / 106 us, whole: 111).
 constexpr uint32_t kMinPart = 4096;
-constexpr uint32_t kMinPartBatch = 1u << 16;
+constexpr uint32_t kMinPartBatch = 1u << 15;
 constexpr uint32_t kMinPartRedo = 1u << 14;   // the same for boxes that overflowed: the others are done
 // Uncertainty queries: classes of the nodes of a large box that overflowed its table, each taken
 // by a workgroup that reads all its cubes (10,000 boxes of 256^3: 0.47 ms; with such boxes redone
@@ -3921,9 +3921,8 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         uint32_t grid = 0;
         if ((rc = resident(reinterpret_cast<const void *>(kdirect), kBlockDirect, dyn, &grid))) return rc;
         if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
-        // about one part per CU: with four, 256 boxes of a 589x563x395 volume took 122 us instead
-        // of 63 (every part adds its sources to its box's sums with global atomics)
-        const uint32_t ways = ERR ? 0u : std::min({grid, uint32_t(d.ncu), A.n_slots});
+        // about two parts per CU: 256 boxes of a 589x563x395 volume take 34 us so, 40 with one
+        const uint32_t ways = ERR ? 0u : std::min({grid, 2u * uint32_t(d.ncu), A.n_slots});
         if ((rc = timing_begin(g, s, err))) return rc;
         hipLaunchKernelGGL(kdirect, dim3(std::min(grid, n + 2 * ways)), dim3(kBlockDirect), dyn, s, A, ways, kMinPart);
         HIP_TRY(hipGetLastError());
