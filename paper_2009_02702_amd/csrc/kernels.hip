@@ -18,11 +18,15 @@
 //
 // Each cube contributes its 8^l voxels to the node its mip voxel holds
 // ("denormalized" samples). Cubes whose node is a source add straight to the
-// segment's integer count; other nodes collect integer counts in a per-query
-// hash table, then their mass is pushed down the DAG step by step in reverse
-// order (node n = (1 - w_n) a_n + w_n b_n gives a the share 1 - w_n and b the
-// share w_n). Mass is fp32 with a two-sum compensation term per entry; the
-// final per-segment count is summed in fp64 and divided by the box volume.
+// segment's integer count, those on nodes of rank 1 and 2 through the node's
+// record of its two to four sources; nodes of rank >= 3 collect integer counts in
+// a per-query hash table, then each adds its count times its mixture row. Graphs
+// too large for rows, and calls that report the nodes a box reaches, push mass
+// down the DAG instead, rank by rank in reverse order (node n = (1 - w_n) a_n +
+// w_n b_n gives a the share 1 - w_n and b the share w_n). Mass is fp32 with a
+// two-sum compensation term per entry; the final per-segment count is summed in
+// fp64 and divided by the box volume. A box is answered by one workgroup, or in
+// parts by several whose sums meet in the workspace.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
