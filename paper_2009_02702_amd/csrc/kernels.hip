@@ -60,7 +60,7 @@ constexpr uint32_t kBigLog2 = 14;             // boxes of >= 2^14 cubes go to th
 // The same where small boxes keep sources in the table: 20,000 boxes of a 307x480x300 volume of
 // 3,980 fibres with 2^8 / 2^10 / 2^12 / 2^14: 4.70 / 4.76 / 4.88 / 5.41 ms.
 constexpr uint32_t kBigLog2Sparse = 10;
-constexpr uint32_t kStaticLds = 9216;         // LDS set aside for the query kernels' fixed arrays
+constexpr uint32_t kStaticLds = 10240;        // LDS set aside for the query kernels' fixed arrays (9,952 at most)
 constexpr uint32_t kHashGlobal = 1u << 16;    // fewest per-worker hash slots in the fallback tables
 constexpr uint32_t kSegLdsMax = 2048;         // sources kept in LDS
 constexpr uint32_t kFallbackWorkers = 128;    // workers of the final global-table launch (budget)
@@ -68,7 +68,9 @@ constexpr uint32_t kLeastTiles = 16;            // tiles and row segments (64 ar
 constexpr uint32_t kLeastRunItems = 32;         // piece of their own where waves share them
 constexpr uint32_t kLeastItems = 8;            // row segments worth a wave's while
 constexpr uint32_t kRunSeg = 256;             // cells of a row one thread sums from the runs
-constexpr uint32_t kRunMinRow = 16;           // rows shorter than this stream cube by cube (default)
+// Rows shorter than this stream cube by cube (default). 100,000 boxes of 512^3 with 8 / 16 / 32 / 128:
+// 1.126 / 1.112 / 1.146 / 1.728 ms; 5,000 of 199x181x163: 101 / 100 / 112 / 157 us.
+constexpr uint32_t kRunMinRow = 16;
 constexpr uint32_t kTfPlanes = 4;             // transfer functions per thread of a propagation step
 constexpr uint32_t kTfTailPairs = 4096;        // steps of at most this many node x TF pairs may share a launch
 constexpr uint32_t kTfTailSteps = 16;          // at most this many of them
@@ -3934,8 +3936,8 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     } else if (batched) {
         // Default table: half the size where the graph has few nodes that can enter it (the largest
         // boxes hold up to about an eighth of them). 353 segments, 2,624 such nodes, 100,000 boxes:
-        // 1.21 ms with 1,024 slots, 1.48 with 2,048; 591 segments, 9,958 nodes, 20,000 boxes: 755 us
-        // with 1,024 (some boxes overflow), 613 with 2,048.
+        // 1.11 ms with 1,024 slots, 1.20 with 2,048; 591 segments, 9,958 nodes, 20,000 boxes: 444 us
+        // with 1,024 (some boxes overflow), 352 with 2,048.
         const bool few = A.counts && !ERR && n_entries / 8 <= kHashDirect / 4 * 3;
         uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : ERR ? kHashBigErr : few ? kHashDirect : kHashBig;
         const bool table = by_table(cap_big);
@@ -3949,9 +3951,9 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         };
         // Threads per big-tier box: the choice that keeps more waves resident beside the per-box
         // LDS, and of two equal ones the smaller workgroup (100,000 boxes of 512^3, 353 segments, 24
-        // waves per CU both: 1.21 ms with 256 threads, 1.40 with 512; 20,000 boxes of 591 segments,
-        // 16 and 24 waves: 729 and 613 us). Batches of few boxes per workgroup take the larger one,
-        // whose boxes end sooner (5,000 boxes of 199x181x163: 142 us with 256, 116 with 512).
+        // waves per CU both: 1.11 ms with 256 threads, 1.20 with 512; 20,000 boxes of 591 segments,
+        // 16 and 24 waves: 410 and 351 us). Batches of few boxes per workgroup take the larger one,
+        // whose boxes end sooner (5,000 boxes of 199x181x163: 113 us with 256, 100 with 512).
         uint32_t wbig = 0, w512 = 0;
         int bbig = d.cfg.block_big ? int(d.cfg.block_big) : 256;
         if ((rc = resident(reinterpret_cast<const void *>(big(bbig)), bbig, dyn_big, &wbig))) return rc;
