@@ -1472,8 +1472,11 @@ template <int BLOCK, bool SPARSE, bool ERR, class ROWS>
 __device__ inline void expand_rows(const QueryState &st, const ROWS &rows)
 {
     constexpr uint32_t kWaves = BLOCK / 64;
-    const uint32_t nu = uni(ld(st.n_used));
-    if (nu == 0 || (uni(ld(st.flags)) & 1u)) return;
+    const uint32_t nu = uni(ld(st.n_used)), over = uni(ld(st.flags)) & 1u;
+    // (sparse state: the additions below insert sources, so n_used grows) every wave has read the
+    // count that its range follows from, and of entries all of which are written, before any of them
+    if (SPARSE) __syncthreads();
+    if (nu == 0 || over) return;
     const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
     const uint32_t per = max(8u, (nu + kWaves - 1) / kWaves), n0 = min(nu, wave * per), n1 = min(nu, n0 + per);
     for (uint32_t b0 = n0; b0 < n1; b0 += 64) {

@@ -15,7 +15,7 @@ from oracle import footprint as ofp
 from oracle import quant, scan
 from paper_2009_02702_amd import Graph, synth
 
-from test_gpu import _compare, _dev, _graph
+from test_gpu import _compare, _dev, _graph, _sparse_to_dense
 from test_gpu_quant import _compare as _compare_quant
 from test_gpu_quant import _compare_err
 
@@ -115,3 +115,41 @@ def test_uncertainty_boxes_redone_by_classes_of_nodes(n):
                 _compare_err(err.cpu().numpy(), u[pick], tag)
     finally:
         q.set_launch_config(table_big=0, table_small=0, table_retry=0)
+
+
+_SMALL_CELLS = []
+
+
+def _small_cells():
+    """A graph of more sources than the per-source LDS arrays hold, cells of about 50 voxels: most
+    cubes above level 0 are on nodes of rank >= 3, whose expansion meets new sources. 1,500 boxes of
+    a few to 8,000 voxels, and the oracle's fractions."""
+    if not _SMALL_CELLS:
+        dims = (62, 59, 61)
+        vol = synth.make_volume(synth.workload(2, dims=dims, segments=4000, n_boxes=1))
+        g = Graph.build(vol).upload(0)
+        rng = np.random.default_rng(5)
+        b = np.concatenate([rng.integers(0, 50, size=(1500, 3)), rng.integers(1, 21, size=(1500, 3))], axis=1)
+        b[:3] = [[4, 4, 4, 16, 16, 16], [7, 7, 7, 0, 3, 3], [61, 58, 60, 9, 9, 9]]
+        ids, vol_c = scan.compact(vol)
+        _, ref = scan.box_counts(vol_c, len(ids), b.astype(np.uint32))
+        assert g.info()["nseg"] == len(ids) > 2048
+        _SMALL_CELLS.append((g, b.astype(np.uint32), ref))
+    return _SMALL_CELLS[0]
+
+
+@pytest.mark.parametrize("variant", ["batched", "plain", "sparse"])
+def test_expansion_that_inserts_sources_into_the_node_table(variant):
+    """Sources as entries of the node table, inserted while its nodes are expanded: every node's
+    count meets its row exactly once, in each of several calls."""
+    g, boxes, ref = _small_cells()
+    db = _dev(boxes)
+    nnz = int((ref > 0).sum())
+    for call in range(4):
+        if variant == "sparse":
+            index, seg, val, total = g.query_sparse(db, capacity=nnz)
+            assert int(total.item()) == nnz
+            got = _sparse_to_dense(index.cpu().numpy(), seg.cpu().numpy(), val.cpu().numpy(), *ref.shape)
+        else:
+            got = g.query(db, variant=variant).cpu().numpy()
+        _compare(got, ref, None, "%s, call %d" % (variant, call))
