@@ -182,7 +182,8 @@ int mg_upload(mg_graph *g, int device);
 int mg_workspace_bytes(const mg_graph *g, uint32_t max_boxes, uint64_t *bytes);
 
 /* Prepare a workspace once after allocating it (enqueued on `stream`): clears the counters,
- * queues and tables that every query expects clean and leaves clean. */
+ * queues and tables that every query expects clean and leaves clean, also where it
+ * returns an error. */
 int mg_workspace_init(mg_graph *g, void *d_work, uint64_t work_bytes, void *stream);
 
 /* Box histograms, the batched path (Sec. "Fast Sub-Volume Queries"; the

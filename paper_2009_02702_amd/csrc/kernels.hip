@@ -3889,9 +3889,12 @@ int dev_workspace_init(Graph *g, void *work, uint64_t bytes, void *stream, std::
     return MG_OK;
 }
 
+// Every kernel, table size and launch size of a call is settled before its first launch, so that a
+// call refused for its limits has enqueued nothing; *began tells a caller whose call failed that
+// launches before the failure may have left the workspace's counters and slots in use.
 template <bool SPARSE, bool ERR>
 int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &w, uint32_t n, hipStream_t s,
-                 int variant, std::string *err)
+                 int variant, bool *began, std::string *err)
 {
     int rc = MG_OK;
     DeviceState &d = g->dev;
@@ -3916,6 +3919,17 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         *out = uint32_t(d.ncu) * uint32_t(occ);
         return MG_OK;
     };
+    // what overflows its table: once more with a larger LDS table, then in global memory
+    uint32_t cap_retry = d.cfg.table_retry ? d.cfg.table_retry : kHashRetry;
+    if (!d.cfg.table_retry)  // the largest table up to kHashRetry that fits the LDS of a workgroup
+        while (cap_retry > kHashBig && uint64_t(bytes(cap_retry, false)) + kStaticLds > uint64_t(d.lds_max)) cap_retry /= 2;
+    const bool retry_table = by_table(cap_retry);
+    if (retry_table && !d.cfg.table_retry) cap_retry = kHashBigSparse;
+    const auto kretry = retry_table ? query_retry_kernel<kBlockBig, 4, SPARSE, ERR>
+                                    : query_retry_kernel<kBlockBig, 4, false, ERR>;
+    const uint32_t dyn_retry = bytes(cap_retry, retry_table);
+    uint32_t wretry = 0;
+    auto resident_retry = [&]() { return resident(reinterpret_cast<const void *>(kretry), kBlockBig, dyn_retry, &wretry); };
     const bool batched = variant == kQueryBatched || variant == kQueryLut;
     if (batched && n <= kDirectMax) {
         // few boxes: no planning launches
@@ -3932,14 +3946,17 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         const uint32_t dyn = bytes(A.table_cap, table);
         level0(table);
         uint32_t grid = 0;
+        const bool alone = holds_all(A.table_cap, table);
         if ((rc = resident(reinterpret_cast<const void *>(kdirect), kBlockDirect, dyn, &grid))) return rc;
+        if (!alone && (rc = resident_retry())) return rc;
+        *began = true;
         if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
         // about two parts per CU: 256 boxes of a 589x563x395 volume take 34 us so, 40 with one
         const uint32_t ways = ERR ? 0u : std::min({grid, 2u * uint32_t(d.ncu), A.n_slots});
         if ((rc = timing_begin(g, s, err))) return rc;
         hipLaunchKernelGGL(kdirect, dim3(std::min(grid, n + 2 * ways)), dim3(kBlockDirect), dyn, s, A, ways, kMinPart);
         HIP_TRY(hipGetLastError());
-        if (holds_all(A.table_cap, table)) return timing_end(g, s, err);
+        if (alone) return timing_end(g, s, err);
     } else if (batched) {
         // Default table: half the size where the graph has few nodes that can enter it (the largest
         // boxes hold up to about an eighth of them). 353 segments, 2,624 such nodes, 100,000 boxes:
@@ -3976,6 +3993,8 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         const uint32_t dyn_small = bytes(cap_small, SPARSE);
         uint32_t wsmall = 0;
         if ((rc = resident(reinterpret_cast<const void *>(ksmall), bsmall, dyn_small, &wsmall))) return rc;
+        if ((rc = resident_retry())) return rc;
+        *began = true;
         const uint32_t blocks = (n + 255) / 256;
         hipLaunchKernelGGL(query_size_kernel, dim3(blocks), dim3(256), 0, s, lt, A.boxes, n, w.work, w.buckets,
                            w.counters, A.sp_total);
@@ -3997,23 +4016,14 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         A.table_cap = kHashPlain;
         uint32_t all = 0;
         if ((rc = resident(reinterpret_cast<const void *>(kplain), kBlock, bytes(kHashPlain, SPARSE), &all))) return rc;
+        if ((rc = resident_retry())) return rc;
+        *began = true;
         if (A.sp_total) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, A.sp_total, uint64_t(1), 0u);
         if ((rc = timing_begin(g, s, err))) return rc;
         level0(SPARSE);
         hipLaunchKernelGGL(kplain, dim3(n), dim3(kBlock), bytes(kHashPlain, SPARSE), s, A);
         HIP_TRY(hipGetLastError());
     }
-    // what overflowed its table: once more with a larger LDS table, then in global memory
-    uint32_t cap_retry = d.cfg.table_retry ? d.cfg.table_retry : kHashRetry;
-    if (!d.cfg.table_retry)  // the largest table up to kHashRetry that fits the LDS of a workgroup
-        while (cap_retry > kHashBig && uint64_t(bytes(cap_retry, false)) + kStaticLds > uint64_t(d.lds_max)) cap_retry /= 2;
-    const bool retry_table = by_table(cap_retry);
-    if (retry_table && !d.cfg.table_retry) cap_retry = kHashBigSparse;
-    const auto kretry = retry_table ? query_retry_kernel<kBlockBig, 4, SPARSE, ERR>
-                                           : query_retry_kernel<kBlockBig, 4, false, ERR>;
-    const uint32_t dyn_retry = bytes(cap_retry, retry_table);
-    uint32_t wretry = 0;
-    if ((rc = resident(reinterpret_cast<const void *>(kretry), kBlockBig, dyn_retry, &wretry))) return rc;
     A.table_cap = cap_retry;
     level0(retry_table);
     // no more workgroups than there can be entries for (a box, or its parts)
@@ -4161,9 +4171,13 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     A.lt.runs_mask = run_min == 0xFFFFFFFFu ? 0u : g->dev.runs_mask;
     A.lt.run_min = run_min;
     A.runs = static_cast<const RunLevel *>(g->dev.run_table);
-    if (A.out_err) return launch_query<false, true>(g, A, lt, w, n, s, variant, err);
-    return sparse ? launch_query<true, false>(g, A, lt, w, n, s, variant, err)
-                  : launch_query<false, false>(g, A, lt, w, n, s, variant, err);
+    bool began = false;
+    if (A.out_err) rc = launch_query<false, true>(g, A, lt, w, n, s, variant, &began, err);
+    else rc = sparse ? launch_query<true, false>(g, A, lt, w, n, s, variant, &began, err)
+                     : launch_query<false, false>(g, A, lt, w, n, s, variant, &began, err);
+    // a call that ends early does not reach the launches that leave the workspace clean
+    if (rc && began) clear_workspace(*g, w, s);
+    return rc;
 }
 
 }  // namespace
@@ -4222,6 +4236,7 @@ int dev_query_noalloc(Graph *g, const uint32_t *boxes, uint32_t n, float *out, v
     g->dev.timing = false;  // no events are created on this path
     rc = query_in(g, boxes, n, out, nullptr, w, s, kQueryBatched, nullptr, err, nullptr);
     g->dev.timing = timing;
+    if (rc) std::memset(sl->layout, 0, sizeof(sl->layout));  // cleared again by the next call
     return rc;
 }
 

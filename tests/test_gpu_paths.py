@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 
 from oracle import footprint as ofp
 from oracle import quant, scan
-from paper_2009_02702_amd import Graph, synth
+from paper_2009_02702_amd import Graph, MGError, _lib, synth
 
 from test_gpu import _compare, _dev, _graph, _sparse_to_dense
 from test_gpu_quant import _compare as _compare_quant
@@ -153,3 +153,44 @@ def test_expansion_that_inserts_sources_into_the_node_table(variant):
         else:
             got = g.query(db, variant=variant).cpu().numpy()
         _compare(got, ref, None, "%s, call %d" % (variant, call))
+
+
+def test_a_failed_call_leaves_its_workspace_clean():
+    """A retry table that no workgroup's LDS holds refuses a call with MG_ELIMIT, and a call that
+    finds an earlier error of its thread fails after its launches: the next call on the same
+    workspace (or on the library's scratch) answers every box."""
+    vol = synth.make_volume(synth.workload(2, dims=(62, 59, 61), segments=5000, n_boxes=1))
+    g = Graph.build(vol).upload(0)
+    rng = np.random.default_rng(6)
+    boxes = np.concatenate([rng.integers(0, 40, size=(1300, 3)), rng.integers(1, 33, size=(1300, 3))],
+                           axis=1).astype(np.uint32)
+    boxes[:2] = [[0, 0, 0, 62, 59, 61], [1, 3, 1, 60, 55, 57]]
+    ids, vol_c = scan.compact(vol)
+    _, ref = scan.box_counts(vol_c, len(ids), boxes)
+    assert len(ids) > 4500
+    ws = g.workspace(len(boxes))
+    db = _dev(boxes)
+    out = torch.empty(ref.shape, dtype=torch.float32, device="cuda")
+    index = torch.empty((len(boxes), 2), dtype=torch.int32, device="cuda")
+    one = [torch.empty(1, dtype=t, device="cuda") for t in (torch.int32, torch.float32, torch.int32)]
+    calls = {"sparse": lambda k: g.query_sparse(db[:k], capacity=1, workspace=ws, bufs=(index[:k], *one)),
+             "batched": lambda k: g.query(db[:k], out=out[:k], workspace=ws),
+             "plain": lambda k: g.query(db[:k], out=out[:k], variant="plain", workspace=ws),
+             "noalloc": lambda k: g.query_noalloc(db[:k], out=out[:k])}
+    for n in (1300, 900):  # with and without planning launches
+        for name, call in calls.items():
+            g.set_launch_config(table_retry=8192)
+            with pytest.raises(MGError) as e:
+                call(n)
+            assert e.value.code == -8
+            g.set_launch_config(table_retry=0)
+            try:
+                _lib.load().hipSetDevice(1 << 20)  # an error that may wait for the next hipGetLastError
+                call(n)
+            except MGError as e:
+                assert e.code != -8
+            for again in range(2):
+                tag = "%s, %d boxes, call %d" % (name, n, again)
+                _compare(g.query(db[:n], workspace=ws).cpu().numpy(), ref[:n], None, tag)
+                _compare(g.query_noalloc(db[:n]).cpu().numpy(), ref[:n], None, tag + ", noalloc")
+    g.close()
