@@ -241,7 +241,10 @@ int mg_query_boxes_stats(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float
  * of up to about 1.5 M nodes.
  * Every call on one GPU shares that GPU's array, which keeps the last call's
  * contents: calls that overlap in time on one GPU (other streams, other
- * threads, other graphs) race; order them on one stream or synchronise. */
+ * threads, other graphs) race; order them on one stream or synchronise. Calls
+ * captured into HIP graphs may be replayed in any order with other calls and
+ * replays; from the first captured call on, every call starts with a launch
+ * that looks on the device whether another layout used the array last. */
 #define MG_NOALLOC_SCRATCH_BYTES (64u << 20)
 int mg_query_boxes_noalloc(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float *d_out, void *stream);
 

@@ -1592,6 +1592,7 @@ enum : uint32_t {
     kCountSplitOver = 12,  // parts in the first half of `split_over`
     kCountRedo = 13,    // parts in its second half: boxes cut up after they overflowed
     kCountTotal = 14,   // cubes of all boxes (64 bits)
+    kCountLayout = 32,  // the library's scratch: the layout it was last cleared for (ScratchLayout)
 };
 constexpr uint32_t kPartFlag = 0x80000000u;
 
@@ -2839,6 +2840,41 @@ __global__ void fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v)
     for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
+// Arrays of a workspace with the word each holds when clean.
+constexpr uint32_t kMaxRanges = 24;
+struct ClearRanges {
+    uint32_t n;
+    struct {
+        uint32_t *p;
+        uint64_t words;
+        uint32_t value;
+    } r[kMaxRanges];
+};
+
+// (sources, table slots, workers, shared boxes + 1) that the library's scratch is carved for
+struct ScratchLayout {
+    uint64_t v[4];
+};
+
+// Clears a workspace; with `have`, only where the layout it was last cleared for is not `want`
+// (the same words for every workgroup: they are written by a launch of their own).
+__global__ void clear_kernel(ClearRanges c, const uint64_t *have, ScratchLayout want)
+{
+    if (have) {
+        bool same = true;
+        for (int k = 0; k < 4; ++k) same = same && have[k] == want.v[k];
+        if (same) return;
+    }
+    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x, first = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    for (uint32_t k = 0; k < c.n; ++k)
+        for (uint64_t i = first; i < c.r[k].words; i += stride) c.r[k].p[i] = c.r[k].value;
+}
+
+__global__ void stamp_kernel(uint64_t *have, ScratchLayout want)
+{
+    if (threadIdx.x < 4) have[threadIdx.x] = want.v[threadIdx.x];
+}
+
 // Levels, offsets and the 16-bit copy's pitches of a volume (the graph's own
 // level table for its dims; the host-side address check builds one from dims).
 LevelTable level_table_dims(const uint32_t dims[3])
@@ -3091,8 +3127,9 @@ constexpr uint64_t kScratchBytes = uint64_t(MG_NOALLOC_SCRATCH_BYTES);
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 struct ScratchSlot {
-    char *ptr = nullptr;                // device address of `scratch` on this device
-    uint64_t layout[4] = {0, 0, 0, 0};  // (sources, table slots, workers, shared boxes + 1) last cleared; 0: never
+    char *ptr = nullptr;         // device address of `scratch` on this device
+    ScratchLayout layout = {};   // last cleared (zeros: never), while no call was captured
+    bool captured = false;       // a call was captured: its replays change the layout unseen
 };
 std::mutex g_scratch_mu;
 std::vector<ScratchSlot> g_scratch;      // per device ordinal
@@ -3832,45 +3869,42 @@ uint64_t dev_workspace_bytes(const Graph &g, uint32_t max_boxes)
     return carve(g, nullptr, std::max<uint32_t>(max_boxes, 1)).bytes;
 }
 
-// The global fallback tables of a workspace in their clean state (empty keys,
-// zero counts and mass), by fill kernels on `s` (no memset: callers may
-// capture the stream into a graph).
-void clear_pool(const Graph &g, const GlobalPool &p, hipStream_t s)
+// Everything a query expects clean and leaves clean: the fixed part of a workspace.
+ClearRanges clean_state(const Graph &g, const Workspace &w)
 {
-    const uint64_t hs = uint64_t(p.workers) * p.slots;
-    if (hs) {
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, s, p.keys, hs, kEmpty);
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, s, p.cnt, hs, 0u);
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, s, reinterpret_cast<uint32_t *>(p.hi), hs, 0u);
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, s, reinterpret_cast<uint32_t *>(p.lo), hs, 0u);
+    ClearRanges c;
+    c.n = 0;
+    auto add = [&](void *p, uint64_t words, uint32_t value) {
+        if (!words) return;
+        c.r[c.n].p = static_cast<uint32_t *>(p), c.r[c.n].words = words, c.r[c.n].value = value;
+        ++c.n;
+    };
+    for (const GlobalPool *p : {&w.fin, &w.mid}) {
+        const uint64_t hs = uint64_t(p->workers) * p->slots, ss = uint64_t(p->workers) * g.nseg;
+        add(p->keys, hs, kEmpty);
+        for (void *a : {static_cast<void *>(p->cnt), static_cast<void *>(p->hi), static_cast<void *>(p->lo)})
+            add(a, hs, 0);
+        for (void *a : {static_cast<void *>(p->seg_cnt), static_cast<void *>(p->seg_hi), static_cast<void *>(p->seg_lo),
+                        static_cast<void *>(p->seg_var)})
+            add(a, ss, 0);
     }
-    const uint64_t ss = uint64_t(p.workers) * g.nseg;
-    if (!ss) return;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, p.seg_cnt, ss, 0u);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, reinterpret_cast<uint32_t *>(p.seg_hi), ss, 0u);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, reinterpret_cast<uint32_t *>(p.seg_lo), ss, 0u);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(256), dim3(256), 0, s, reinterpret_cast<uint32_t *>(p.seg_var), ss, 0u);
+    const uint64_t ns = w.n_slots;
+    add(w.counters, 64, 0);
+    add(w.buckets, 64, 0);
+    add(w.queues, uint64_t(kQueues) * kQueueStride, 0);
+    add(w.slot_done, ns, 0);
+    for (void *a : {static_cast<void *>(w.slot_cnt), static_cast<void *>(w.slot_hi), static_cast<void *>(w.slot_lo),
+                    static_cast<void *>(w.slot_var)})
+        add(a, ns * g.nseg, 0);
+    static_assert(2 * 8 + 3 + 5 <= kMaxRanges, "one entry per array");
+    return c;
 }
 
-// Everything a query expects clean and leaves clean: the fixed part of a workspace.
+// By a kernel on `s` (no memset: callers may capture the stream into a graph).
 void clear_workspace(const Graph &g, const Workspace &w, hipStream_t s)
 {
-    clear_pool(g, w.fin, s);
-    clear_pool(g, w.mid, s);
-    auto zero = [&](void *p, uint64_t n) {
-        if (n)
-            hipLaunchKernelGGL(fill_u32_kernel, dim3(uint32_t(std::min<uint64_t>((n + 255) / 256, 1024))), dim3(256), 0,
-                               s, static_cast<uint32_t *>(p), n, 0u);
-    };
-    zero(w.counters, 64);
-    zero(w.buckets, 64);
-    zero(w.queues, uint64_t(kQueues) * kQueueStride);
-    const uint64_t ns = w.n_slots;
-    zero(w.slot_done, ns);
-    zero(w.slot_cnt, ns * g.nseg);
-    zero(w.slot_hi, ns * g.nseg);
-    zero(w.slot_lo, ns * g.nseg);
-    zero(w.slot_var, ns * g.nseg);
+    hipLaunchKernelGGL(clear_kernel, dim3(1024), dim3(256), 0, s, clean_state(g, w),
+                       static_cast<const uint64_t *>(nullptr), ScratchLayout{});
 }
 
 int dev_workspace_init(Graph *g, void *work, uint64_t bytes, void *stream, std::string *err)
@@ -4224,19 +4258,27 @@ int dev_query_noalloc(Graph *g, const uint32_t *boxes, uint32_t n, float *out, v
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Workspace w = carve(*g, sl->ptr, n, workers, 0, slots);
-    // the scratch keeps the last call's contents; every query leaves the fallback
-    // tables clean, so they are cleared only when their layout changes
-    const uint64_t layout[4] = {g->nseg, fallback_slots(*g), workers, slots + 1ull};
-    if (std::memcmp(layout, sl->layout, sizeof(layout)) != 0) {
-        clear_workspace(*g, w, s);
+    // The scratch keeps the last call's contents, and every query leaves its part of it clean, so
+    // it is cleared only where its layout changes. The layout it has is noted on the device as well:
+    // once a call was captured, a graph's replay may be the last to have used it, which only the
+    // device knows, and every call, replayed or not, looks there.
+    const ScratchLayout layout = {{g->nseg, fallback_slots(*g), workers, slots + 1ull}};
+    uint64_t *const have = reinterpret_cast<uint64_t *>(w.counters + kCountLayout);
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+    sl->captured = sl->captured || status != hipStreamCaptureStatusNone;
+    if (sl->captured || std::memcmp(&layout, &sl->layout, sizeof(layout)) != 0) {
+        hipLaunchKernelGGL(clear_kernel, dim3(1024), dim3(256), 0, s, clean_state(*g, w), have, layout);
         HIP_TRY(hipGetLastError());
-        std::memcpy(sl->layout, layout, sizeof(layout));
+        hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(64), 0, s, have, layout);
+        HIP_TRY(hipGetLastError());
+        sl->layout = layout;
     }
     const bool timing = g->dev.timing;
     g->dev.timing = false;  // no events are created on this path
     rc = query_in(g, boxes, n, out, nullptr, w, s, kQueryBatched, nullptr, err, nullptr);
     g->dev.timing = timing;
-    if (rc) std::memset(sl->layout, 0, sizeof(sl->layout));  // cleared again by the next call
+    if (rc) sl->layout = ScratchLayout{};  // looked at again by the next call
     return rc;
 }
 

@@ -194,3 +194,43 @@ def test_a_failed_call_leaves_its_workspace_clean():
                 _compare(g.query(db[:n], workspace=ws).cpu().numpy(), ref[:n], None, tag)
                 _compare(g.query_noalloc(db[:n]).cpu().numpy(), ref[:n], None, tag + ", noalloc")
     g.close()
+
+
+def test_captured_noalloc_calls_replayed_among_other_graphs_calls():
+    """Captured calls on the library's scratch, replayed after calls of a graph with another layout
+    of it (which the capture could not know of), with shared boxes and with boxes that overflow
+    into the scratch's global tables: every replay and every call between them answers every box."""
+    cases = []
+    for dims, segments in (((160, 150, 140), 300), ((96, 80, 72), 900)):
+        vol = synth.make_volume(synth.workload(2, dims=dims, segments=segments, n_boxes=1))
+        g = Graph.build(vol).upload(0)
+        b = np.minimum(_boxes(40, 4), np.asarray(dims + dims)).astype(np.uint32)
+        ids, vol_c = scan.compact(vol)
+        _, ref = scan.box_counts(vol_c, len(ids), b)
+        out = torch.empty(ref.shape, dtype=torch.float32, device="cuda")
+        cases.append((g, _dev(b), ref, out))
+    try:
+        for tables in ((0, 0, 0), (64, 64, 64)):
+            graphs = []
+            for g, db, ref, out in cases:
+                g.set_launch_config(table_big=tables[0], table_small=tables[1], table_retry=tables[2])
+                _compare(g.query_noalloc(db, out=out).cpu().numpy(), ref, None, "before capture")
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph):
+                    g.query_noalloc(db, out=out)
+                graphs.append(graph)
+            # (replay or call, graph): each graph's after the other's, in both forms
+            for step, (replay, k) in enumerate([(1, 0), (0, 1), (1, 0), (1, 1), (1, 0), (0, 0), (1, 1), (0, 1), (0, 0),
+                                                (1, 1), (1, 1), (0, 1)]):
+                g, db, ref, out = cases[k]
+                out.fill_(-1.0)
+                if replay:
+                    graphs[k].replay()
+                else:
+                    g.query_noalloc(db, out=out)
+                torch.cuda.synchronize()
+                _compare(out.cpu().numpy(), ref, None, "tables %s, step %d" % (tables, step))
+            del graphs
+    finally:
+        for g, _, _, _ in cases:
+            g.close()
