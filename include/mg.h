@@ -355,8 +355,10 @@ int mg_export_lut(const mg_graph *g, uint64_t *ptr, uint32_t *seg, float *val, f
 /* Box histograms answered from the mixture lookup table (the paper's own
  * query, Sec. "Range queries"): the same footprint and scatter as
  * mg_query_boxes, then every scattered graph node adds count * mixture row
- * to the segments, instead of the rank-by-rank push. Same arguments and
- * output as mg_query_boxes; MG_ESTATE unless mg_lut_build ran. */
+ * to the segments. (mg_query_boxes expands nodes by rows the graph keeps of its
+ * nodes of rank >= 3, the same mixtures; on graphs whose rows would hold more than
+ * 2^25 entries it pushes their mass down the DAG rank by rank.) Same arguments
+ * and output as mg_query_boxes; MG_ESTATE unless mg_lut_build ran. */
 int mg_query_boxes_lut(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float *d_out,
                        void *d_work, uint64_t work_bytes, void *stream);
 
