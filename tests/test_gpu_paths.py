@@ -239,8 +239,8 @@ def test_captured_noalloc_calls_replayed_among_other_graphs_calls():
 def test_graph_too_large_for_mixture_rows():
     """Noise of 2,000 sources, whose nodes of rank >= 3 would need more than 2^25 row entries: the
     batched calls push mass rank by rank, in the tiers and in the global tables their overflows end
-    in; the lookup table is read where it is named, large boxes shared by several workgroups among
-    them. All against the oracle."""
+    in, and the lookup table is read where it is named; large boxes shared by several workgroups
+    among them. All against the oracle."""
     dims = (149, 151, 147)
     vol = np.random.default_rng(3).integers(1, 2001, size=dims[::-1]).astype(np.uint32)
     g = Graph.build(vol).upload(0)
@@ -257,7 +257,8 @@ def test_graph_too_large_for_mixture_rows():
     _, ref = scan.box_counts(vol_c, len(ids), boxes)
     db = _dev(boxes)
     ws = g.workspace(len(boxes))
-    for variant, lo, hi in (("batched", 0, 300), ("batched", 0, 1100), ("plain", 0, 300), ("lut", 0, 1106),
+    for variant, lo, hi in (("batched", 0, 300), ("batched", 0, 1106), ("batched", 1000, 1106),
+                            ("batched", 1100, 1101), ("plain", 0, 300), ("lut", 0, 1106),
                             ("lut", 1000, 1106), ("lut", 1100, 1101)):
         for tables in ((0, 0, 0), (64, 64, 64)):
             g.set_launch_config(table_big=tables[0], table_small=tables[1], table_retry=tables[2])
