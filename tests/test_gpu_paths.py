@@ -266,3 +266,33 @@ def test_graph_too_large_for_mixture_rows():
                 got = g.query(db[lo:hi], variant=variant, workspace=ws).cpu().numpy()
                 _compare(got, ref[lo:hi], None, "%s, boxes %d..%d, tables %s, call %d" % (variant, lo, hi, tables, again))
     g.close()
+
+
+@pytest.mark.parametrize("segments", [1500, 12000])
+def test_shared_boxes_with_sparse_output_and_sources_as_entries(segments):
+    """Boxes shared by several workgroups whose sums are read out as sparse entries: from per-source
+    arrays (1,500 sources), and where sources are entries of every table (12,000), which the box's
+    last part reads from the shared sums. With and without planning launches; with tiny tables the
+    parts overflow and are redone."""
+    vol = synth.make_volume(synth.workload(2, dims=DIMS, segments=segments, n_boxes=1))
+    g = Graph.build(vol).upload(0)
+    boxes = _boxes(1100, 12)
+    boxes[0] = [1, 3, 1, DIMS[0] - 7, DIMS[1] - 9, DIMS[2] - 11]
+    ids, vol_c = scan.compact(vol)
+    _, ref = scan.box_counts(vol_c, len(ids), boxes)
+    nnz = (ref > 0).sum(axis=1)
+    db = _dev(boxes)
+    ws = g.workspace(len(boxes))
+    for n in (1, 400, 1100):
+        cap = int(nnz[:n].sum())
+        for tables in ((0, 0, 0), (64, 64, 1024), (64, 64, 64)):
+            g.set_launch_config(table_big=tables[0], table_small=tables[1], table_retry=tables[2])
+            for again in range(2):
+                tag = "%d sources, %d boxes, tables %s, call %d" % (len(ids), n, tables, again)
+                index, seg, val, total = g.query_sparse(db[:n], capacity=cap, workspace=ws)
+                assert int(total.item()) == cap, tag
+                assert np.array_equal(index[:, 1].cpu().numpy(), nnz[:n]), tag
+                got = _sparse_to_dense(index.cpu().numpy(), seg.cpu().numpy(), val.cpu().numpy(), n, len(ids))
+                _compare(got, ref[:n], None, tag)
+                _compare(g.query(db[:n], workspace=ws).cpu().numpy(), ref[:n], None, tag + ", dense rows")
+    g.close()
