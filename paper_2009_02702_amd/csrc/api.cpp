@@ -15,6 +15,18 @@ namespace {
 
 thread_local std::string g_err;
 
+// f(), or MG_ENOMEM where the host has no memory for it.
+template <class F>
+int guarded(std::string *err, F f)
+{
+    try {
+        return f();
+    } catch (const std::bad_alloc &) {
+        *err = "out of host memory";
+        return MG_ENOMEM;
+    }
+}
+
 int fail(int code, const std::string &msg)
 {
     g_err = msg;
@@ -208,21 +220,27 @@ int mg_upload(mg_graph *h, int device)
     if (!h) return fail(MG_EINVAL, "mg_upload: null graph");
     if (device < 0) return fail(MG_EINVAL, "mg_upload: negative device");
     std::string err;
-    return done(mg::dev_upload(&h->g, device, &err), err);
+    const int rc = guarded(&err, [&]() { return mg::dev_upload(&h->g, device, &err); });
+    return done(rc, err);
 }
 
 int mg_device_bytes(const mg_graph *h, uint64_t *bytes)
 {
     if (!h || !bytes) return fail(MG_EINVAL, "mg_device_bytes: null argument");
-    *bytes = mg::dev_device_bytes(h->g);
-    return MG_OK;
+    std::string err;
+    const int rc = guarded(&err, [&]() {
+        *bytes = mg::dev_device_bytes(h->g);
+        return int(MG_OK);
+    });
+    return done(rc, "mg_device_bytes: " + err);
 }
 
 int mg_bind_device(mg_graph *h, int device, void *d_buf, uint64_t bytes, void *stream)
 {
     if (!h || !d_buf) return fail(MG_EINVAL, "mg_bind_device: null argument");
     std::string err;
-    return done(mg::dev_bind_device(&h->g, device, d_buf, bytes, stream, &err), "mg_bind_device: " + err);
+    const int rc = guarded(&err, [&]() { return mg::dev_bind_device(&h->g, device, d_buf, bytes, stream, &err); });
+    return done(rc, "mg_bind_device: " + err);
 }
 
 int mg_query_nnz_bound(mg_graph *h, const uint32_t *d_boxes, uint32_t n, uint32_t *d_bound, void *stream)

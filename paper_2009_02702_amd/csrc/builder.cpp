@@ -33,8 +33,11 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <exception>
 #include <functional>
+#include <new>
 #include <numeric>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
 #include <cmath>
@@ -50,6 +53,30 @@ unsigned resolve_threads(uint32_t t)
     return t == 0 ? hw : std::min<unsigned>(t, 4 * hw);
 }
 
+void run_workers(unsigned k, const std::function<void(unsigned)> &fn)
+{
+    std::vector<std::exception_ptr> thrown(k);
+    std::vector<std::thread> th;
+    th.reserve(k);
+    auto work = [&](unsigned t) {
+        try {
+            fn(t);
+        } catch (...) {
+            thrown[t] = std::current_exception();
+        }
+    };
+    for (unsigned t = 0; t < k; ++t) {
+        try {
+            th.emplace_back(work, t);
+        } catch (const std::system_error &) {
+            work(t);
+        }
+    }
+    for (auto &x : th) x.join();
+    for (const auto &e : thrown)
+        if (e) std::rethrow_exception(e);
+}
+
 namespace {
 
 constexpr uint32_t kMixed = 0xFFFFFFFFu;
@@ -62,14 +89,9 @@ void parallel_chunks(uint64_t n, unsigned nt, const std::function<void(uint64_t,
         fn(0, n, 0);
         return;
     }
-    std::vector<std::thread> th;
     const uint64_t chunk = (n + nt - 1) / nt;
-    for (unsigned t = 0; t < nt; ++t) {
-        const uint64_t b = t * chunk, e = std::min<uint64_t>(n, b + chunk);
-        if (b >= e) break;
-        th.emplace_back(fn, b, e, t);
-    }
-    for (auto &x : th) x.join();
+    run_workers(unsigned((n + chunk - 1) / chunk),
+                [&](unsigned t) { fn(t * chunk, std::min<uint64_t>(n, (t + 1) * chunk), t); });
 }
 
 inline uint64_t mix64(uint64_t x)
@@ -919,15 +941,15 @@ struct DeepRows {
 
 }  // namespace
 
-void ensure_deep(const Graph &g)
+namespace {
+
+// The rows of all nodes of rank >= 3; false, and none, where they have too many entries. A worker
+// leaves its rank as soon as the entries so far are too many: one rank can hold many times the limit.
+bool fill_deep(const Graph &g)
 {
-    if (g.deep_ready) return;
-    g.deep_ready = true;
-    g.deep_ptr.clear();
-    g.deep.clear();
     if (g.depth < 3) {  // no such node
         g.deep_ptr.assign(1, 0);
-        return;
+        return true;
     }
     constexpr uint64_t kMaxEntries = uint64_t(1) << 25;  // 256 MiB; beyond, mass is pushed rank by rank
     const unsigned nt = resolve_threads(0);
@@ -939,11 +961,14 @@ void ensure_deep(const Graph &g)
     for (uint32_t r = 3; r <= g.depth; ++r) {
         const uint32_t lo = g.rank_ptr[r], hi = g.rank_ptr[r + 1];
         std::vector<Part> parts(std::max(1u, nt));
+        std::atomic<uint64_t> entries(d.ptr[lo - d.first]);
         parallel_chunks(hi - lo, nt, [&](uint64_t b, uint64_t e, unsigned t) {
             Part &p = parts[t];
             p.len.resize(e - b);
-            uint64_t at = 0;
+            uint64_t at = 0, told = 0;
             for (uint64_t i = b; i < e; ++i) {
+                if (at - told >= 4096) entries.fetch_add(at - told, std::memory_order_relaxed), told = at;
+                if (entries.load(std::memory_order_relaxed) > kMaxEntries) return;
                 const uint32_t n = lo + uint32_t(i), ca = g.child_a[n], cb = g.child_b[n];
                 auto bound = [&](uint32_t c) { return c < d.first ? 4u : d.ptr[c - d.first + 1] - d.ptr[c - d.first]; };
                 const uint64_t room = at + bound(ca) + bound(cb);
@@ -952,12 +977,11 @@ void ensure_deep(const Graph &g)
                 at += p.len[i - b];
             }
             p.seg.resize(at), p.val.resize(at);
+            entries.fetch_add(at - told, std::memory_order_relaxed);
         });
+        if (entries.load() > kMaxEntries) return false;
         uint32_t k = lo - d.first;
-        uint64_t total = d.ptr[k];
         for (const Part &p : parts) {
-            total += p.seg.size();
-            if (total > kMaxEntries) return;
             for (uint32_t len : p.len) d.ptr[k + 1] = d.ptr[k] + len, ++k;
             d.seg.insert(d.seg.end(), p.seg.begin(), p.seg.end());
             d.val.insert(d.val.end(), p.val.begin(), p.val.end());
@@ -971,6 +995,24 @@ void ensure_deep(const Graph &g)
         g.deep[i] = uint64_t(bits) << 32 | d.seg[i];
     }
     g.deep_ptr.swap(d.ptr);
+    return true;
+}
+
+}  // namespace
+
+void ensure_deep(const Graph &g)
+{
+    if (g.deep_ready) return;
+    bool have = false;
+    try {
+        have = fill_deep(g);
+    } catch (const std::bad_alloc &) {
+    }
+    if (!have) {  // too many, or too large for the host: mass is pushed instead
+        std::vector<uint32_t>().swap(g.deep_ptr);
+        std::vector<uint64_t>().swap(g.deep);
+    }
+    g.deep_ready = true;
 }
 
 // Mixture lookup table (Sec. "Decoder", mixture lookup; used by range queries in

@@ -3721,7 +3721,12 @@ int dev_bind_device(Graph *g, int device, void *base, uint64_t bytes, void *stre
         return MG_EINVAL;
     }
     HIP_TRY(hipSetDevice(device));
-    const int rc = dev_bind(g, device, base, bytes, static_cast<hipStream_t>(stream), false, err);
+    int rc = MG_ENOMEM;
+    try {
+        rc = dev_bind(g, device, base, bytes, static_cast<hipStream_t>(stream), false, err);
+    } catch (const std::bad_alloc &) {
+        *err = "out of host memory";
+    }
     if (rc) dev_free(g);
     return rc;
 }
@@ -3744,7 +3749,12 @@ int upload_with(Graph *g, int device, const StreamSrc *src, std::string *err)
         *err = "mg_upload: device allocation of " + std::to_string(bytes) + " bytes failed";
         return MG_ENOMEM;
     }
-    const int rc = dev_bind(g, device, base, bytes, nullptr, true, err, src);
+    int rc = MG_ENOMEM;
+    try {
+        rc = dev_bind(g, device, base, bytes, nullptr, true, err, src);
+    } catch (const std::bad_alloc &) {
+        *err = "out of host memory";
+    }
     if (rc) {
         if (g->dev.base != base) (void)hipFree(base);  // not recorded yet: release it here
         dev_free(g);

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -122,7 +123,8 @@ struct Graph {
 // Fills g.runs from the host maps once (no runs for graphs whose maps are only on
 // the device). Not safe against a concurrent first call on the same graph.
 void ensure_runs(const Graph &g);
-// Fills g.deep_ptr and g.deep from the DAG once (builder.cpp). The same restriction.
+// Fills g.deep_ptr and g.deep from the DAG once (builder.cpp); no rows where the host has no room
+// for them. The same restriction.
 void ensure_deep(const Graph &g);
 
 // A DAG in creation order (children before parents; sources 0 .. nseg-1 have
@@ -168,6 +170,9 @@ int greedy_factorize(uint32_t nseg, std::vector<std::vector<std::pair<uint32_t, 
                      uint32_t tau, RawDag *d, std::vector<uint32_t> *root, std::string *err);
 // Worker threads for a request (0: all hardware threads).
 unsigned resolve_threads(uint32_t t);
+// fn(0) .. fn(k - 1), each on a thread of its own (here where none can be had); the first exception
+// is thrown again once all have ended.
+void run_workers(unsigned k, const std::function<void(unsigned)> &fn);
 // Bit-packed graph stream (Table "bitstream"); quantized graphs only.
 int pack_graph(const Graph &g, std::vector<uint8_t> *out, std::string *err);
 // Where a stream's voxel data (A) lies, for decoding it on the GPU: bit offset

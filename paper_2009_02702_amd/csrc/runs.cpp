@@ -18,7 +18,6 @@
 // runs that cross them: 1.61 ms per 100,000 boxes of a 512^3 volume, 1.53 with 16). Built only where the runs are at
 // most a quarter of the level's cells (long runs).
 #include <algorithm>
-#include <thread>
 #include <vector>
 
 #include "mg_internal.hpp"
@@ -32,10 +31,7 @@ template <class Fn>
 void parallel_for(uint32_t n, unsigned nt, Fn fn)
 {
     const unsigned k = std::max(1u, std::min<unsigned>(nt, n));
-    std::vector<std::thread> th;
-    for (unsigned t = 0; t < k; ++t)
-        th.emplace_back(fn, uint32_t(uint64_t(n) * t / k), uint32_t(uint64_t(n) * (t + 1) / k));
-    for (auto &x : th) x.join();
+    run_workers(k, [&](unsigned t) { fn(uint32_t(uint64_t(n) * t / k), uint32_t(uint64_t(n) * (t + 1) / k)); });
 }
 
 // row_ptr from per-row run counts; false if the runs are too many to pay.
@@ -128,18 +124,19 @@ bool build_y(const uint32_t *m, uint32_t X, uint32_t Y, uint32_t Z, unsigned nt,
 void ensure_runs(const Graph &g)
 {
     if (g.runs_ready) return;
-    g.runs.assign(2 * size_t(g.n_levels), LevelRuns());
-    g.runs_ready = true;
-    if (g.maps.size() != g.lev_off[g.n_levels]) return;  // maps only on the device: no runs
+    std::vector<LevelRuns> runs(2 * size_t(g.n_levels));  // (kept only when complete)
     const unsigned nt = resolve_threads(0);
-    for (uint32_t l = 0; l < g.n_levels; ++l) {
+    const bool host = g.maps.size() == g.lev_off[g.n_levels];  // maps only on the device: no runs
+    for (uint32_t l = 0; host && l < g.n_levels; ++l) {
         const uint32_t X = g.lev_dims[3 * l], Y = g.lev_dims[3 * l + 1], Z = g.lev_dims[3 * l + 2];
         const uint32_t *m = g.maps.data() + g.lev_off[l];
         // rows along x (row y + Y z) and along y (row z + Z x)
-        if (uint64_t(Y) * Z < 0xFFFFFFFFull && !build_x(m, X, Y, Z, nt, &g.runs[2 * l])) g.runs[2 * l] = LevelRuns();
-        if (uint64_t(Z) * X < 0xFFFFFFFFull && !build_y(m, X, Y, Z, nt, &g.runs[2 * l + 1]))
-            g.runs[2 * l + 1] = LevelRuns();
+        if (uint64_t(Y) * Z < 0xFFFFFFFFull && !build_x(m, X, Y, Z, nt, &runs[2 * l])) runs[2 * l] = LevelRuns();
+        if (uint64_t(Z) * X < 0xFFFFFFFFull && !build_y(m, X, Y, Z, nt, &runs[2 * l + 1]))
+            runs[2 * l + 1] = LevelRuns();
     }
+    g.runs.swap(runs);
+    g.runs_ready = true;
 }
 
 }  // namespace mg

@@ -8,6 +8,8 @@ reconstructs the mipmap; with exact weights, without any loss).
 """
 import os
 import re
+import subprocess
+import sys
 from fractions import Fraction
 
 import numpy as np
@@ -379,3 +381,38 @@ def test_server_admission_step():
     assert not q
     take, n_rows, n_tf = srv._admit(q, rows, None)
     assert take == [] and n_rows == 0
+
+
+def _with_little_memory(code, mib):
+    """Runs `code` (with a graph g of noise at hand) in a process that may grow by `mib` MiB from there."""
+    prog = """
+import resource, sys
+sys.path.insert(0, %r)
+import numpy as np
+from paper_2009_02702_amd import Graph, MGError
+g = Graph.build(np.random.default_rng(1).integers(0, 2000, size=(100, 100, 100)).astype(np.uint32))
+with open("/proc/self/status") as f:
+    size = next(int(x.split()[1]) << 10 for x in f if x.startswith("VmSize"))
+resource.setrlimit(resource.RLIMIT_AS, (size + (%d << 20), resource.RLIM_INFINITY))
+%s
+""" % (os.path.dirname(os.path.dirname(os.path.abspath(__file__))), mib, code)
+    return subprocess.run([sys.executable, "-c", prog], capture_output=True, text=True, timeout=300)
+
+
+@pytest.mark.parametrize("mib", [16, 64, 200])
+def test_sizing_a_graph_without_host_memory_for_its_rows(mib):
+    """The mixture rows of the nodes of rank >= 3 (here 14 million entries) are worked out where a graph
+    is sized for a device. Without the memory for them they are left out, or the call reports
+    MG_ENOMEM: no exception leaves a worker thread or the library, and a second call agrees."""
+    r = _with_little_memory("""
+sizes = []
+for call in range(2):
+    try:
+        sizes.append(g.device_bytes())
+    except MGError as e:
+        assert e.code == -2, e
+        sizes.append(None)
+assert sizes[0] is None or sizes[0] == sizes[1], sizes
+print("sizes", sizes)
+""", mib)
+    assert r.returncode == 0 and "sizes" in r.stdout, (r.returncode, r.stdout, r.stderr[-2000:])
