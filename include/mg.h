@@ -414,7 +414,8 @@ int mg_set_launch(mg_graph *g, const mg_launch_cfg *cfg); /* MG_EINVAL for unsup
  * every supported unroll choice, then the table sizes and threads per box of
  * each tier one tier at a time, `reps` timed repetitions each (HIP events on
  * `stream`), keeps the fastest configuration in the graph and returns it in
- * *chosen. Synchronises `stream`; d_out and d_work as for mg_query_boxes. */
+ * *chosen. With at most 1,024 boxes only what such calls read is tried
+ * (table_big, run_min_row, unroll_naive); the rest stays as set. Synchronises `stream`; d_out and d_work as for mg_query_boxes. */
 int mg_autotune(mg_graph *g, const uint32_t *d_boxes, uint32_t n, float *d_out, void *d_work,
                 uint64_t work_bytes, uint32_t reps, void *stream, mg_launch_cfg *chosen);
 

@@ -4451,8 +4451,12 @@ int dev_autotune(Graph *g, const uint32_t *boxes, uint32_t n, float *out, void *
     const uint32_t us[3] = {4, 8, 16};
     mg_launch_cfg best_cfg = saved;
     float best = 1e30f;
+    // calls of few boxes read none of the tiers' settings: what was set for larger ones stays
+    const bool tiers = n > kDirectMax;
+    if (!tiers) rc = time_variant(kQueryBatched, &best);
     for (uint32_t ub : us)
         for (uint32_t usm : us) {
+            if (rc || !tiers) break;
             g->dev.cfg.unroll_big = ub;
             g->dev.cfg.unroll_small = usm;
             float ms = 0;
@@ -4463,17 +4467,17 @@ int dev_autotune(Graph *g, const uint32_t *boxes, uint32_t n, float *out, void *
     const uint32_t tb[3] = {1024, 2048, 4096}, ts[3] = {256, 512, 1024};
     for (uint32_t bbg : {512u, 256u})
         for (uint32_t t : tb) {
-            if (rc) break;
+            if (rc || (!tiers && bbg != 512u)) break;
             g->dev.cfg = best_cfg;
             g->dev.cfg.table_big = t;
-            g->dev.cfg.block_big = bbg;
+            g->dev.cfg.block_big = tiers ? bbg : saved.block_big;
             float ms = 0;
             if ((rc = time_variant(kQueryBatched, &ms))) break;
-            if (ms < best) best = ms, best_cfg.table_big = t, best_cfg.block_big = bbg;
+            if (ms < best) best = ms, best_cfg.table_big = t, best_cfg.block_big = g->dev.cfg.block_big;
         }
     for (uint32_t bsm : {128u, 256u})
         for (uint32_t t : ts) {
-            if (rc) break;
+            if (rc || !tiers) break;
             g->dev.cfg = best_cfg;
             g->dev.cfg.table_small = t;
             g->dev.cfg.block_small = bsm;
@@ -4482,15 +4486,15 @@ int dev_autotune(Graph *g, const uint32_t *boxes, uint32_t n, float *out, void *
             if (ms < best) best = ms, best_cfg.table_small = t, best_cfg.block_small = bsm;
         }
     for (uint32_t c : {0u, 2u, 4u}) {
-        if (rc) break;
+        if (rc || !tiers) break;
         g->dev.cfg = best_cfg;
         g->dev.cfg.chunk_small = c;
         float ms = 0;
         if ((rc = time_variant(kQueryBatched, &ms))) break;
         if (ms < best) best = ms, best_cfg.chunk_small = c;
     }
-    // shortest row summed from runs (where the graph keeps runs)
-    for (uint32_t m : {64u, 256u}) {
+    // shortest row summed from runs (where the graph keeps runs): both sides of the default
+    for (uint32_t m : {8u, 32u, 64u}) {
         if (rc || !g->dev.runs_mask) break;
         g->dev.cfg = best_cfg;
         g->dev.cfg.run_min_row = m;

@@ -296,3 +296,23 @@ def test_shared_boxes_with_sparse_output_and_sources_as_entries(segments):
                 _compare(got, ref[:n], None, tag)
                 _compare(g.query(db[:n], workspace=ws).cpu().numpy(), ref[:n], None, tag + ", dense rows")
     g.close()
+
+
+def test_autotune_on_few_boxes_leaves_what_such_calls_do_not_read():
+    """Calls of at most 1,024 boxes take one launch that reads none of the tiers' settings: tuning on
+    such a call keeps them as they were set for larger ones."""
+    vol = synth.make_volume(synth.workload(2, dims=(64, 64, 64), segments=40, n_boxes=1))
+    g = Graph.build(vol).upload(0)
+    boxes = synth.make_boxes(synth.workload(2, dims=(64, 64, 64), segments=40, n_boxes=1025))
+    kept = dict(unroll_big=4, unroll_small=16, table_small=512, block_small=256, block_big=512, chunk_small=3)
+    for n in (1, 1024):
+        g.set_launch_config(**kept)
+        cfg = g.autotune(_dev(boxes[:n]), reps=1)
+        assert {k: cfg[k] for k in kept} == kept and g.launch_config() == cfg
+        assert cfg["run_min_row"] in (0, 8, 32, 64)
+    cfg = g.autotune(_dev(boxes), reps=1)
+    assert g.launch_config() == cfg
+    ids, vol_c = scan.compact(vol)
+    _, ref = scan.box_counts(vol_c, len(ids), boxes)
+    _compare(g.query(_dev(boxes)).cpu().numpy(), ref, None, "after autotune")
+    g.close()
