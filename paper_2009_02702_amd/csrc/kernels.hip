@@ -61,6 +61,9 @@ constexpr uint32_t kBigLog2 = 14;             // boxes of >= 2^14 cubes go to th
 // 3,980 fibres with 2^8 / 2^10 / 2^12 / 2^14: 4.70 / 4.76 / 4.88 / 5.41 ms.
 constexpr uint32_t kBigLog2Sparse = 10;
 constexpr uint32_t kStaticLds = 10240;        // LDS set aside for the query kernels' fixed arrays (9,952 at most)
+// A table size set by the caller that fits the LDS beside this much is always taken; where only the
+// kernels' larger fixed arrays leave no room for it, half the size is.
+constexpr uint32_t kStaticLdsSet = 6448;
 constexpr uint32_t kHashGlobal = 1u << 16;    // fewest per-worker hash slots in the fallback tables
 constexpr uint32_t kSegLdsMax = 2048;         // sources kept in LDS
 constexpr uint32_t kFallbackWorkers = 128;    // workers of the final global-table launch (budget)
@@ -3961,6 +3964,11 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     auto by_table = [&](uint32_t cap) {
         return SPARSE && uint64_t(bytes(cap, false)) + kStaticLds > uint64_t(d.lds_max);
     };
+    auto set_size = [&](uint32_t cap) {
+        const uint64_t state = lds_state_bytes(g->nseg, cap, false, A.counts != 0) + 6u * L * sizeof(Slab) + (ERR ? 4u * g->nseg : 0u);
+        return !SPARSE && uint64_t(bytes(cap, false)) + kStaticLds > uint64_t(d.lds_max) &&
+                       state + kStaticLdsSet <= uint64_t(d.lds_max) ? cap / 2 : cap;
+    };
     auto level0 = [&](bool table) { A.lt.use16 = (!table && d.maps16) ? 1u : 0u; };  // sources only: 16 bits
     // workgroups of a kernel that are resident together
     auto resident = [&](const void *k, int block, uint32_t dyn, uint32_t *out) -> int {
@@ -3970,7 +3978,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         return MG_OK;
     };
     // what overflows its table: once more with a larger LDS table, then in global memory
-    uint32_t cap_retry = d.cfg.table_retry ? d.cfg.table_retry : kHashRetry;
+    uint32_t cap_retry = d.cfg.table_retry ? set_size(d.cfg.table_retry) : kHashRetry;
     if (!d.cfg.table_retry)  // the largest table up to kHashRetry that fits the LDS of a workgroup
         while (cap_retry > kHashBig && uint64_t(bytes(cap_retry, false)) + kStaticLds > uint64_t(d.lds_max)) cap_retry /= 2;
     const bool retry_table = by_table(cap_retry);
@@ -3988,7 +3996,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         A.table_cap = kHashDirect;
         while (A.table_cap < kHashDirectMax && !holds_all(A.table_cap, false)) A.table_cap *= 2;
         if (!holds_all(A.table_cap, false)) A.table_cap = ERR ? kHashBigErr : kHashBig;
-        if (d.cfg.table_big) A.table_cap = d.cfg.table_big;
+        if (d.cfg.table_big) A.table_cap = set_size(d.cfg.table_big);
         const bool table = by_table(A.table_cap);
         if (table && !d.cfg.table_big) A.table_cap = kHashBigSparse;
         const auto kdirect = table ? query_direct_kernel<kBlockDirect, 4, SPARSE, ERR>
@@ -4013,7 +4021,7 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
         // 1.11 ms with 1,024 slots, 1.20 with 2,048; 591 segments, 9,958 nodes, 20,000 boxes: 444 us
         // with 1,024 (some boxes overflow), 352 with 2,048.
         const bool few = A.counts && !ERR && n_entries / 8 <= kHashDirect / 4 * 3;
-        uint32_t cap_big = d.cfg.table_big ? d.cfg.table_big : ERR ? kHashBigErr : few ? kHashDirect : kHashBig;
+        uint32_t cap_big = d.cfg.table_big ? set_size(d.cfg.table_big) : ERR ? kHashBigErr : few ? kHashDirect : kHashBig;
         const bool table = by_table(cap_big);
         if (table && !d.cfg.table_big) cap_big = kHashBigSparse;
         const uint32_t dyn_big = bytes(cap_big, table);

@@ -316,3 +316,23 @@ def test_autotune_on_few_boxes_leaves_what_such_calls_do_not_read():
     _, ref = scan.box_counts(vol_c, len(ids), boxes)
     _compare(g.query(_dev(boxes)).cpu().numpy(), ref, None, "after autotune")
     g.close()
+
+
+def test_largest_set_tables_of_the_push():
+    """Calls that push (16 bytes per table slot) with tables set to 8,192 slots and 1,800 sources,
+    which fit the LDS but for the kernels' fixed arrays: answered, in calls with and without planning
+    launches (half the size is used)."""
+    vol = synth.make_volume(synth.workload(2, dims=(62, 59, 61), segments=1800, n_boxes=1))
+    g = Graph.build(vol).upload(0)
+    rng = np.random.default_rng(8)
+    boxes = np.concatenate([rng.integers(0, 40, size=(1100, 3)), rng.integers(1, 33, size=(1100, 3))],
+                           axis=1).astype(np.uint32)
+    ids, vol_c = scan.compact(vol)
+    _, ref = scan.box_counts(vol_c, len(ids), boxes)
+    assert 1750 < len(ids) < 1900
+    for n in (1100, 500):
+        for tables in ((8192, 64), (64, 8192), (8192, 8192)):
+            g.set_launch_config(table_big=tables[0], table_retry=tables[1])
+            out, _ = g.query_stats(_dev(boxes[:n]))
+            _compare(out.cpu().numpy(), ref[:n], None, "tables %s, %d boxes" % (tables, n))
+    g.close()
