@@ -3952,7 +3952,10 @@ int launch_query(Graph *g, QueryArgs &A, const LevelTable &lt, const Workspace &
     int rc = MG_OK;
     DeviceState &d = g->dev;
     const uint32_t L = g->n_levels;
-    auto bytes = [&](uint32_t cap, bool table) { return lds_bytes(g->nseg, cap, table, A.counts != 0, L, ERR); };
+    auto bytes = [&](uint32_t cap, bool table) -> uint32_t {
+        if (!table && g->nseg > (1u << 20)) return 1u << 30;  // no LDS holds them (nor 32 bits their bytes)
+        return lds_bytes(g->nseg, cap, table, A.counts != 0, L, ERR);
+    };
     // nodes that can become entries of a box's table: with counts only those its cubes are on
     const uint32_t n_entries = g->n_nodes - A.gv.r2_end;
     auto holds_all = [&](uint32_t cap, bool table) { return !table && A.counts && n_entries <= cap / 4 * 3; };
