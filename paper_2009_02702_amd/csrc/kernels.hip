@@ -82,6 +82,7 @@ constexpr uint32_t kMidWorkers = 256;         // workers of the mid-size global-
 constexpr uint32_t kMaxSlots = 1024;           // boxes of one call that several workgroups may share
 constexpr uint64_t kSlotBytes = 32ull << 20;  // their accumulators take at most this much of a workspace
 constexpr uint32_t kMinSlots = 16;            // (but hold at least this many boxes)
+constexpr uint32_t kNoallocWorkers = 16;      // workers of the static scratch that come before shared boxes
 // Fewest cubes worth a workgroup of their own: when others idle (one box of 205,000 cubes of a
 // 400x375x263 volume in parts of 2,048 / 4,096 / 8,192 / 16,384 / 32,768: 36 / 36 / 40 / 46 / 55 us,
 // whole: 105), and in a large batch (5,000 boxes of 199x181x163, parts of 16,384 / 32,768 /
@@ -390,12 +391,13 @@ __device__ inline void build_slabs(const LevelTable &lt, const LevelRow *rows, c
 // ---------------------------------------------------------------- per-query state
 
 // Per-query accumulators. Internal nodes of rank >= 3 live in an
-// open-addressing table (key, mass, compensation); nodes of rank 1 (both
-// predecessors are sources) and rank 2 (predecessors of rank <= 1) never enter
-// it: their mass goes straight to the sources, in at most two hops. Sources keep an exact integer count (cubes whose node is a
-// source) plus pushed fp32 mass with its compensation term: in dense mode in
-// per-source arrays [S], in sparse mode (many sources) as entries of the same
-// table. Pointers are into LDS or into a global per-worker region; the same
+// open-addressing table (key and voxel count, or, where they are pushed, mass and
+// compensation); nodes of rank 1 (both predecessors are sources) and rank 2
+// (predecessors of rank <= 1) never enter it: their voxels go straight to the
+// sources by the node's record (Leaf). Sources keep an exact integer count (cubes
+// whose node is a source, whole voxels of nodes of rank 1 and 2) plus fp32 mass with
+// its compensation term: in dense mode in per-source arrays [S], in sparse mode
+// (many sources) as entries of the same table. Pointers are into LDS or into a global per-worker region; the same
 // code serves both (the compiler resolves the address space after inlining).
 struct QueryState {
     uint32_t *keys;     // [cap] node ID or kEmpty
@@ -756,16 +758,14 @@ __host__ __device__ inline TileWalk naive_walk(const LevelTable &lt, const uint3
 // Streams a slab of 32-bit node IDs; `use(v)` consumes each of a block's n_u
 // values (every lane calls it, kEmpty outside the slab). The next block's loads
 // are in flight while a block is consumed. Blocks are dealt round-robin to the
-// waves starting at wave `first`. Returns false if `stop()` became true
-// (checked every 8 blocks).
-template <int UNROLL, int WAVES, class Use, class Stop>
-__device__ inline bool stream_slab(const char *__restrict__ p, const TileWalk &tw, uint32_t first, Use use,
-                                   Stop stop)
+// waves.
+template <int UNROLL, int WAVES, class Use>
+__device__ inline void stream_slab(const char *__restrict__ p, const TileWalk &tw, Use use)
 {
     const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);  // the wave index is uniform
     const uint32_t lane_bytes = tile_lane_bytes(tw, lane);
-    uint32_t fb = (wave + WAVES - first) % WAVES;
-    if (fb >= tw.n_blk) return true;
+    uint32_t fb = wave;
+    if (fb >= tw.n_blk) return;
     // block fb < WAVES as (t0, rb, k2), by subtraction (no division)
     uint32_t t0 = fb, rb = 0, k2 = 0;
     while (t0 >= tw.n_t0) {
@@ -787,9 +787,7 @@ __device__ inline bool stream_slab(const char *__restrict__ p, const TileWalk &t
     };
     uint32_t v[UNROLL], n_u, n_ok;
     load(v, n_u, n_ok, t0, rb, k2);
-    uint32_t iter = 0;
     for (; fb < tw.n_blk; fb += WAVES) {
-        if ((++iter & 7u) == 0 && stop()) return false;
         // this wave's next block; after its last one, the current block again (loaded, unused)
         uint32_t nt0 = t0 + WAVES, nrb = rb, nk2 = k2;
         while (nt0 >= tw.n_t0) {
@@ -808,7 +806,6 @@ __device__ inline bool stream_slab(const char *__restrict__ p, const TileWalk &t
         n_u = w_n_u, n_ok = w_n_ok;
         t0 = nt0, rb = nrb, k2 = nk2;
     }
-    return true;
 }
 
 // Streams a slab of the 16-bit level-0 copy, two elements per unit; `use(lo, hi)`
@@ -818,11 +815,11 @@ __device__ inline bool stream_slab(const char *__restrict__ p, const TileWalk &t
 // wave's last one is replaced by the block before it (valid addresses, never consumed).
 template <int UNROLL, int WAVES, class Use>
 __device__ inline void stream_pairs(const char *__restrict__ p, const TileWalk &tw, uint32_t e0, uint32_t odd,
-                                    uint32_t first, Use use)
+                                    Use use)
 {
     const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
     const uint32_t lane_bytes = tile_lane_bytes(tw, lane);
-    uint32_t fb = (wave + WAVES - first) % WAVES;
+    uint32_t fb = wave;
     if (fb >= tw.n_blk) return;
     uint32_t t0 = fb, rb = 0, k2 = 0;
     while (t0 >= tw.n_t0) {
@@ -951,8 +948,8 @@ struct DeferRing {
 // whole number of voxels (w' is a ratio of voxel counts of the mixtures the node
 // serves) up to the fp32 rounding of w', which a distance to the nearest integer
 // of at most n 2^-22 bounds, and that integer is the split. Any other weight (as
-// in a quantized graph) pushes the mass instead. Ranks 1 and 2 share one triple
-// load; a rank-2 node's two predecessor triples are loaded together.
+// in a quantized graph) pushes the mass instead. Both ranks read the node's one
+// record (Leaf).
 template <bool SPARSE>
 __device__ inline void resolve_count(const QueryState &st, const GraphView &gv, uint32_t node, uint32_t len,
                                      uint32_t lev)
@@ -1605,7 +1602,6 @@ enum : uint32_t {
 };
 constexpr uint32_t kPartFlag = 0x80000000u;
 
-// LDS bytes of the query kernels' dynamic shared memory.
 // Dynamic LDS of the query kernels: per-source arrays (dense mode) and the table,
 // then the slab list (6 per level) at a 16-byte aligned offset.
 __host__ __device__ inline uint32_t lds_state_bytes(uint32_t nseg, uint32_t cap, bool sparse, bool counts)
@@ -2412,21 +2408,19 @@ __global__ __launch_bounds__(kBlock) void naive_kernel(NaiveArgs A)
         const uint32_t lane = threadIdx.x & 63;
         if (A.lt.use16) {
             stream_pairs<UNROLL, kBlock / 64>(reinterpret_cast<const char *>(A.map16) + base, tw, hi[0] - lo[0], odd,
-                                              0u, [&](uint32_t a, uint32_t b) { count_pairs(cnt, a, b, lane); });
+                                              [&](uint32_t a, uint32_t b) { count_pairs(cnt, a, b, lane); });
         } else {
-            // runs of equal IDs: -start lane at the start, end lane + 1 at the end (see scatter_slabs)
+            // runs of equal IDs: -start lane at the start, end lane + 1 at the end (as in stream_tiles)
             const uint32_t w_start = 0u - lane, w_end = lane + 1;
             stream_slab<UNROLL, kBlock / 64>(
-                reinterpret_cast<const char *>(A.map0) + base, tw, 0u,
-                [&](uint32_t v) {
+                reinterpret_cast<const char *>(A.map0) + base, tw, [&](uint32_t v) {
                     const uint32_t prev = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x138, 0xF, 0xF, true));
                     const uint32_t next = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x130, 0xF, 0xF, true));
                     if (v != kEmpty) {
                         if (v != prev || lane == 0) atomicAdd(&cnt[v], w_start);
                         if (v != next || lane == 63) atomicAdd(&cnt[v], w_end);
                     }
-                },
-                []() { return false; });
+                });
         }
     }
     __syncthreads();
@@ -2956,7 +2950,7 @@ inline uint32_t fallback_workers(const Graph &g)
 // where the final tables are larger than that.
 inline uint32_t mid_workers(const Graph &g) { return fallback_slots(g) > kHashGlobal ? kMidWorkers : 0u; }
 
-// Boxes that several workgroups may share in one call (each takes 12 bytes per source). None on
+// Boxes that several workgroups may share in one call (each takes 16 bytes per source). None on
 // graphs whose boxes can overflow even the final tables.
 inline uint32_t split_slots(const Graph &g)
 {
@@ -4271,7 +4265,7 @@ int dev_query_noalloc(Graph *g, const uint32_t *boxes, uint32_t n, float *out, v
     // one), none with mid-size tables (a speed-up only: every box fits the final tables)
     uint32_t workers = fallback_workers(*g), slots = std::min(split_slots(*g), kNoallocSlots);
     auto size = [&](uint32_t f, uint32_t ns) { return carve(*g, nullptr, n, f, 0, ns).bytes; };
-    if (size(std::min(workers, kMinSlots), slots) > kScratchBytes) slots = 0;  // room for the workers first
+    if (size(std::min(workers, kNoallocWorkers), slots) > kScratchBytes) slots = 0;  // room for the workers first
     while (workers > 1 && size(workers, slots) > kScratchBytes) --workers;
     if (size(workers, slots) > kScratchBytes) {
         const uint64_t fixed = carve(*g, nullptr, 1, 1, 0, 0).bytes;
