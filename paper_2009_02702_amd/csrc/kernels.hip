@@ -4232,7 +4232,10 @@ int query_in(Graph *g, const uint32_t *boxes, uint32_t n, float *out, const Spar
     else rc = sparse ? launch_query<true, false>(g, A, lt, w, n, s, variant, &began, err)
                      : launch_query<false, false>(g, A, lt, w, n, s, variant, &began, err);
     // a call that ends early does not reach the launches that leave the workspace clean
-    if (rc && began) clear_workspace(*g, w, s);
+    if (rc && began) {
+        clear_workspace(*g, w, s);
+        (void)hipGetLastError();  // *err already says what failed; nothing is left for the next call to find
+    }
     return rc;
 }
 
